@@ -31,6 +31,7 @@
 // a single pass.  TIA writes are queued during the pass and applied in one
 // shared block afterwards.
 #include "tia_draw.h"
+#include "hotloop.h"
 
 namespace vcs {
 
@@ -206,11 +207,17 @@ __device__ __forceinline__ uint32_t joy_pressed(uint32_t a) {
 }
 __device__ __forceinline__ bool fire_pressed(uint32_t a) { return a == 1 || a >= 10; }
 
+// Predecoded words, read through the scalar cache: they never change while a
+// kernel runs (the constant address space says so; the compiler could not
+// tell past the hot loop's assembly).
+typedef const __attribute__((address_space(4))) uint32_t* PreWords;
+
 struct Wave {                 // per-workgroup (uniform) data
     const uint8_t* rom;       // the tile's cartridge: its LDS copy, or its HBM slot
     uint8_t* ram;             // LDS, kRamStride bytes per lane
     uint8_t* tia;             // LDS, kTiaStride bytes per lane
-    const uint32_t* pre;      // the tile ROM's predecoded words
+    uint32_t ram_lds, tia_lds;   // their LDS addresses
+    PreWords pre;             // the tile ROM's predecoded words
     CartMap cm;               // its cartridge mapping
     uint32_t track;           // collision latches tracked
 };
@@ -1038,6 +1045,42 @@ __device__ __forceinline__ uint32_t store_class(uint32_t a) {
     return (a & 0x14) == 0x14 ? SC_EXIT : SC_IGNORE;
 }
 
+// The class on the tile's cartridge: on 3F cartridges a store to $00-$3F also
+// selects a slice (SC_3F when the TIA register it reaches is not emulated,
+// else left to the per-lane path); with a Superchip its RAM window is SC_XRAM.
+__device__ __forceinline__ uint32_t cart_store_class(uint32_t kind, uint32_t sc, uint32_t a) {
+    const uint32_t k = store_class(a);
+    if (kind == CART_3F && a <= 0x3F) return k == SC_IGNORE ? SC_3F : SC_EXIT;
+    return sc && (a & 0x1000) && !(a & 0xF00) ? SC_XRAM : k;
+}
+__device__ __forceinline__ uint32_t cart_store_class(const Wave& W, uint32_t a) {
+    return cart_store_class(cm_kind(W), cm_sc(W), a);
+}
+
+// Predecoded word: store class (7 bits) | slot << 7 | b1 << 16 | b2 << 24.  The
+// slot is the hot loop's handler (hotloop.h); a HOT_REAL word carries the
+// opcode in bits 0-6 and 15 instead of a class.
+struct HotOps {
+    uint32_t op[kHotSlots];                      // whole words: the scalar unit loads them
+    constexpr HotOps() : op() {
+        for (uint32_t i = 0; i < kHotSlots; ++i) op[i] = kHotSlotOp[i];
+    }
+};
+__constant__ HotOps kHotOps = HotOps();
+struct HotSlots {                                // an opcode's slot (hot_slot)
+    uint8_t s[256];
+    constexpr HotSlots() : s() {
+        for (uint32_t i = 0; i < 256; ++i) s[i] = (uint8_t)hot_slot(i);
+    }
+};
+__constant__ HotSlots kHotSlot = HotSlots();
+__device__ __forceinline__ uint32_t pre_slot(uint32_t q) { return (q >> 7) & 0xFF; }
+__device__ __forceinline__ uint32_t pre_op(uint32_t q) {
+    const uint32_t slot = pre_slot(q);
+    return slot == HOT_REAL ? (q & 0x7F) | ((q >> 8) & 0x80) : kHotOps.op[slot];
+}
+__device__ __forceinline__ uint32_t pre_class(uint32_t q) { return pre_slot(q) == HOT_REAL ? SC_EXIT : q & 0x7F; }
+
 // Write of per-lane value v to TIA register class `sc` (SC_TIA/S/G | code) at
 // scalar cycle t, with its row-log entry.  The scalar path takes the colour,
 // playfield, control, reflection, VBLANK and NUSIZ registers, the object
@@ -1047,10 +1090,9 @@ __device__ __forceinline__ uint32_t store_class(uint32_t a) {
 // registers (the other player's graphics; with GRP1, ENABL), which the
 // renderer repeats from its own state.  Returns 0, before changing anything,
 // when the row's entries are full (the per-lane path then records the error).
-// PLAIN 1: `sc` is known to be SC_TIA | code (a register stored as is); the
-// code may then differ between lanes.  PLAIN 2: `sc` is SC_TIA or SC_TIAG |
-// code (no object reset, enable or vertical-delay register).
-template <int PLAIN = 0>
+// PLAIN: `sc` is known to be SC_TIA | code (a register stored as is); the
+// code may then differ between lanes.
+template <bool PLAIN = false>
 __device__ __forceinline__ uint32_t fast_tia_code(Cpu& c, const Wave& W, Fast& F, uint32_t sc, uint32_t v,
                                                   uint32_t t) {
     const uint32_t ln = (t + 1) / 76;
@@ -1058,7 +1100,7 @@ __device__ __forceinline__ uint32_t fast_tia_code(Cpu& c, const Wave& W, Fast& F
     uint8_t* R = W.tia + c.tia_off;
     uint32_t code = sc & 0x1F;
     uint32_t v0 = v, full = 0;
-    if (PLAIN == 0 && sc >= SC_TIAS && sc < SC_TIAG) {
+    if (!PLAIN && sc >= SC_TIAS && sc < SC_TIAG) {
         if (code == R_P0X || code == R_P1X) {
             v0 = h < 68 ? 3u : (h - 68 + 5) % 160;
         } else if (code >= R_M0X && code <= R_BLX) {
@@ -1105,7 +1147,7 @@ __device__ __forceinline__ uint32_t fast_tia_code(Cpu& c, const Wave& W, Fast& F
             }
         }
     }
-    if (PLAIN != 1 && sc >= SC_TIAG) {
+    if (!PLAIN && sc >= SC_TIAG) {
         if (code == R_GRP0) {
             R[R_GRP1_OLD] = R[R_GRP1];
         } else {
@@ -1275,16 +1317,13 @@ __device__ __forceinline__ uint32_t fast_finish(Fast& F, uint32_t next, uint32_t
 
 // One instruction with opcode OP (a compile-time constant, so addressing
 // mode, operation and base cycles are folded) for every lane in exec;
-// TRACK: collision latches tracked.  HOT: run from the hot loop, so the
-// instruction is unmarked (it and a branch target stay inside the bank's
-// window, and the pc needs no 16-bit wrap).
-template <int OP, bool TRACK, bool HOT = false>
-__device__ __forceinline__ uint32_t fop(Cpu& c, const Wave& W, Fast& F, uint32_t b1, uint32_t b2, uint32_t aux) {
+// TRACK: collision latches tracked.
+template <int OP, bool TRACK>
+__device__ __forceinline__ uint32_t fop(Cpu& c, const Wave& W, Fast& F, uint32_t b1, uint32_t b2) {
     constexpr OpInfo I = decode(OP);
     constexpr int MD = I.md, MN = I.mn;
     constexpr uint32_t N = (uint32_t)I.cyc;
-    constexpr uint32_t kPcMask = HOT ? 0xFFFFFFFFu : 0xFFFFu;
-    const uint32_t next = (F.pc + (uint32_t)op_len(MD)) & kPcMask;
+    const uint32_t next = (F.pc + (uint32_t)op_len(MD)) & 0xFFFF;
     if constexpr (MN == ILL || MN == BRK || MN == RTI || MD == IZX || MD == IZY || MD == IND || MN >= SLO ||
                   (MN == NOP && MD != IMP)) {
         return FS_EXIT;   // left to the per-lane path (undocumented opcodes included)
@@ -1377,28 +1416,22 @@ __device__ __forceinline__ uint32_t fop(Cpu& c, const Wave& W, Fast& F, uint32_t
                 if (dm == 2) return FS_EXIT;
             }
             uint32_t v;
-            if constexpr (HOT && MD == ZP) {
-                // unmarked zero-page read: RAM (reads below $80 are marked)
-                v = W.ram[c.ram_off + (a & 0x7F)];
-            } else {
-                if (TRACK && aux == SC_EXIT) return FS_EXIT;   // a latch read: the per-lane path scans the log
-                if (MD == ABS && aux == SC_XRAM)      // Superchip RAM: read port, or the write port (0)
-                    v = (a & 0x80) ? (uint32_t)c.xram[a & 0x7F] : 0u;
-                else
-                    v = fast_rd(c, W, F, a, t);
-            }
+            if (TRACK && !(a & 0x1080) && (a & 0xF) < 8) return FS_EXIT;   // a latch read: the per-lane path scans the log
+            if (MD == ABS && (a & 0x1000) && sc_window(W, a))   // Superchip RAM: read port, or the write port (0)
+                v = (a & 0x80) ? (uint32_t)c.xram[a & 0x7F] : 0u;
+            else
+                v = fast_rd(c, W, F, a, t);
             fast_alu(c, MN, v, dm);
             F.pc = next;
             F.cyc += N;
             return FS_NEXT;
         } else if constexpr (store_mn(MN)) {
-            // aux is store_class(a), from the predecoded word
+            const uint32_t aux = cart_store_class(W, a);
             const uint32_t v = store_value<MN>(c);
             if (aux == SC_RAM) {
                 W.ram[c.ram_off + (a & 0x7F)] = (uint8_t)v;
             } else if (aux >= SC_TIA) {
-                // from the hot loop a zero-page store is not an object reset or enable (marked)
-                if (!fast_tia_code<(HOT && MD == ZP) ? 2 : 0>(c, W, F, aux, v & 0xFF, t)) return FS_EXIT;
+                if (!fast_tia_code(c, W, F, aux, v & 0xFF, t)) return FS_EXIT;
             } else if (aux == SC_WSYNC) {
                 return fast_finish(F, next, t, 1);
             } else if (aux == SC_EXIT) {
@@ -1423,7 +1456,7 @@ __device__ __forceinline__ uint32_t fop(Cpu& c, const Wave& W, Fast& F, uint32_t
             if (!(a & 0x1000) && !(a & 0x80)) return FS_EXIT;
             if (!fast_store_ok(a)) return FS_EXIT;
             if constexpr (MD == ABS) {
-                if (aux == SC_XRAM) return FS_EXIT;   // RMW on the Superchip RAM window
+                if ((a & 0x1000) && sc_window(W, a)) return FS_EXIT;   // RMW on the Superchip RAM window
             }
             const uint32_t v = fast_rd(c, W, F, a, t);
             const uint32_t r = fast_rmw(c, MN, v);
@@ -1487,7 +1520,7 @@ __device__ __forceinline__ uint32_t fop(Cpu& c, const Wave& W, Fast& F, uint32_t
         else if constexpr (MN == BCS) taken = (c.p & FC) != 0;
         else if constexpr (MN == BNE) taken = !(c.p & FZ);
         else taken = (c.p & FZ) != 0;
-        const uint32_t tgt = (next + (uint32_t)sext8(b1)) & kPcMask;
+        const uint32_t tgt = (next + (uint32_t)sext8(b1)) & 0xFFFF;
         const uint32_t extra = 1 + (((tgt ^ next) & 0xFF00) ? 1 : 0);
         const uint64_t tk = __builtin_amdgcn_ballot_w64(taken);
         if (tk == 0) {
@@ -1507,7 +1540,7 @@ __device__ __forceinline__ uint32_t fop(Cpu& c, const Wave& W, Fast& F, uint32_t
 }
 
 #define VCS_FAST_CASE(o) \
-    case (o): st = fop<(o), TRACK>(c, W, F, b1, b2, aux); break;
+    case (o): st = fop<(o), TRACK>(c, W, F, b1, b2); break;
 #define VCS_FAST_4(o) VCS_FAST_CASE(o) VCS_FAST_CASE((o) + 1) VCS_FAST_CASE((o) + 2) VCS_FAST_CASE((o) + 3)
 #define VCS_FAST_16(o) VCS_FAST_4(o) VCS_FAST_4((o) + 4) VCS_FAST_4((o) + 8) VCS_FAST_4((o) + 12)
 #define VCS_FAST_64(o) VCS_FAST_16(o) VCS_FAST_16((o) + 16) VCS_FAST_16((o) + 32) VCS_FAST_16((o) + 48)
@@ -1521,7 +1554,7 @@ __device__ __forceinline__ uint32_t fop(Cpu& c, const Wave& W, Fast& F, uint32_t
 // ended.  Returns false when it made no progress (the per-lane path must then
 // execute the instruction in the same iteration).
 template <bool TRACK>
-__device__ __forceinline__ bool run_fast(Cpu& c, const Wave& W, const uint32_t* pre, bool& ended, uint32_t& end_t,
+__device__ __forceinline__ bool run_fast(Cpu& c, const Wave& W, PreWords pre, bool& ended, uint32_t& end_t,
                                          uint32_t partial) {
     Fast F;
     F.partial = partial;
@@ -1539,21 +1572,13 @@ __device__ __forceinline__ bool run_fast(Cpu& c, const Wave& W, const uint32_t* 
     uint32_t done_n = 0;       // instructions executed on this path
     uint32_t st = FS_EXIT;
     uint32_t capped = 0;
-    // Two loops: the inner one handles only the most frequent opcodes of
-    // typical cartridge code, so few values merge at its back edge and the
-    // compiler keeps the state in place; any other opcode goes through the
-    // full dispatch once, then the inner loop resumes.  The pc is checked
-    // against the cartridge window only on entry and after a full-dispatch
-    // instruction: an instruction the inner loop runs is marked in the
-    // predecoded word (bit 31) when it could leave the window (it ends
-    // within 2 bytes of the bank's end, or is a branch whose target is
-    // outside), and a marked word never matches a frequent opcode.  Zero-
-    // page reads below $80 (TIA) are marked too, so the inner loop's reads
-    // are RAM reads.
+    const uint64_t pre_addr = (uint64_t)(uintptr_t)pre;
+    const uint64_t table = (uint64_t)rfl((uint32_t)pre_addr) | ((uint64_t)rfl((uint32_t)(pre_addr >> 32)) << 32);
+    // The hot loop runs until an instruction it does not cover (or the
+    // group's end); that one goes through the full dispatch, then the hot
+    // loop resumes.  In decimal mode every instruction takes the dispatch.
     for (;;) {
-        uint32_t op = 0, b1 = 0, b2 = 0, aux = 0;
-        uint32_t cold = 0;
-        if (F.cyc >= F.lim) {
+        if (F.cyc >= F.lim) {      // the frame's last cycle, or a stop
             capped = F.lim != 0;
             break;
         }
@@ -1561,37 +1586,38 @@ __device__ __forceinline__ bool run_fast(Cpu& c, const Wave& W, const uint32_t* 
             st = FS_EXIT;
             break;
         }
-        for (;;) {
-            if (F.cyc >= F.lim) {      // the frame's last cycle, or a stop
-                capped = F.lim != 0;
+        if (__builtin_amdgcn_ballot_w64((c.p & FD) != 0) == 0) {
+            const uint32_t line = F.cyc / 76, line_cyc = 76 * line;
+            const uint32_t lines = 320u + (uint32_t)F.fl - line;
+            HotRegs H;
+            H.po = ((F.bank << 12) | (F.pc & 0xFFF)) << 2;
+            H.acc = (kAccBias + (F.cyc - line_cyc)) << kAccShift;
+            H.lines = lines;
+            H.orow = F.orow;
+            H.pos = F.obase + F.ocnt + kSnapArea / 4;
+            H.obase = F.obase + kSnapArea / 4;
+            H.pchi = F.pc & 0xF000;
+            uint32_t nzv = ((c.p & FN) << 1) | (((c.p >> 1) & 1) ^ 1), cf = c.p & FC, vf = c.p << 1;
+            hot_loop(H, table, F.bank << 14, 0u - F.partial, F.logon, c.a, c.x, c.y, nzv, cf, vf, W.ram_lds + c.ram_off,
+                     W.tia_lds + c.tia_off, (uint64_t)c.log);
+            c.p = (c.p & ~(FN | FV | FZ | FC)) | cf | ((vf >> 1) & FV) | ((nzv & 0xFF) == 0 ? FZ : 0u) |
+                  ((nzv & 0x180) ? FN : 0u);
+            F.pc = H.pchi | ((H.po >> 2) & 0xFFF);
+            F.cyc = line_cyc + 76 * (lines - H.lines) + (H.acc >> kAccShift) - kAccBias;
+            F.orow = H.orow;
+            F.obase = H.obase - kSnapArea / 4;
+            F.ocnt = H.pos - H.obase;
+            const uint32_t ran = H.acc & kAccCount;
+            done_n += ran;
+            if (ran) st = FS_NEXT;
+            if (H.why == HOT_EXIT_LINE && F.partial) break;
+            if (F.cyc >= F.lim) {
+                capped = 1;
                 break;
             }
-            const uint32_t q = pre[(F.bank << 12) | (F.pc & 0xFFF)];
-            const uint32_t hq = q & 0x800000FFu;   // the opcode, or no frequent one when marked
-            b1 = (q >> 8) & 0xFF;
-            b2 = (q >> 16) & 0xFF;
-            aux = (q >> 24) & 0x7F;
-#define VCS_HOT(o)                                            \
-    if (hq == (o)) {                                          \
-        if ((st = fop<(o), TRACK, true>(c, W, F, b1, b2, aux)) != FS_NEXT) break; \
-    }
-            VCS_HOT(0x85)                    // STA zp
-            else VCS_HOT(0xA5)               // LDA zp
-            else VCS_HOT(0xD0)               // BNE
-            else VCS_HOT(0xCA)               // DEX
-            else VCS_HOT(0x25)               // AND zp
-            else VCS_HOT(0x65)               // ADC zp
-            else VCS_HOT(0x45)               // EOR zp
-            else VCS_HOT(0xA9)               // LDA #
-            else {
-                op = q & 0xFF;
-                cold = 1;
-                break;
-            }
-#undef VCS_HOT
-            ++done_n;
         }
-        if (!cold) break;
+        const uint32_t q = pre[(F.bank << 12) | (F.pc & 0xFFF)];
+        const uint32_t op = pre_op(q), b1 = (q >> 16) & 0xFF, b2 = q >> 24;
         switch (op) {
             VCS_FAST_64(0x00)
             VCS_FAST_64(0x40)
@@ -1647,13 +1673,13 @@ __device__ __forceinline__ uint32_t mop(Cpu& c, const Wave& W, Fast& F, bool in_
     constexpr int MD = I.md, MN = I.mn;
     constexpr uint32_t N = (uint32_t)I.cyc;
     const uint32_t next = (F.pc + (uint32_t)op_len(MD)) & 0xFFFF;
-    const uint32_t a1 = (qa >> 8) & 0xFF, a2 = (qa >> 16) & 0xFF;   // bank A's operand bytes
-    const uint32_t x1 = (qb >> 8) & 0xFF, x2 = (qb >> 16) & 0xFF;   // bank B's
+    const uint32_t a1 = (qa >> 16) & 0xFF, a2 = qa >> 24;           // bank A's operand bytes
+    const uint32_t x1 = (qb >> 16) & 0xFF, x2 = qb >> 24;           // bank B's
     const uint32_t b1 = in_b ? x1 : a1;                              // the lane's
     if constexpr (MN == ILL || MN == BRK || MN == RTI || MN >= SLO || (MN == NOP && MD != IMP)) {
         return FS_EXIT;
     } else if constexpr (MD == IMP || MD == ACC) {
-        return fop<OP, false>(c, W, F, 0, 0, 0);   // no operand bytes; memory only through the stack
+        return fop<OP, false>(c, W, F, 0, 0);   // no operand bytes; memory only through the stack
     } else if constexpr (MD == IMM) {
         uint32_t dm = 0;
         if constexpr (MN == ADC || MN == SBC) {
@@ -1676,7 +1702,7 @@ __device__ __forceinline__ uint32_t mop(Cpu& c, const Wave& W, Fast& F, bool in_
         F.cyc += N;
         return FS_NEXT;
     } else if constexpr (MD == ZP && store_mn(MN)) {
-        const uint32_t auxa = (qa >> 24) & 0x7F, auxb = (qb >> 24) & 0x7F;      // store classes
+        const uint32_t auxa = pre_class(qa), auxb = pre_class(qb);      // store classes
         const uint32_t cat = auxa < SC_TIA ? auxa : (auxa & 0xE0);
         if (cat != (auxb < SC_TIA ? auxb : (auxb & 0xE0))) return FS_EXIT;
         const uint32_t t = F.cyc + N - 1;
@@ -1684,7 +1710,7 @@ __device__ __forceinline__ uint32_t mop(Cpu& c, const Wave& W, Fast& F, bool in_
         if (cat == SC_RAM) {
             W.ram[c.ram_off + (b1 & 0x7F)] = (uint8_t)v;
         } else if (cat == SC_TIA) {
-            if (!fast_tia_code<1>(c, W, F, in_b ? auxb : auxa, v & 0xFF, t)) return FS_EXIT;
+            if (!fast_tia_code<true>(c, W, F, in_b ? auxb : auxa, v & 0xFF, t)) return FS_EXIT;
         } else if (cat == SC_WSYNC) {
             return fast_finish(F, next, t, 1);
         } else if (cat != SC_IGNORE) {
@@ -1755,7 +1781,7 @@ __device__ __forceinline__ uint32_t mop(Cpu& c, const Wave& W, Fast& F, bool in_
 // position; each in bank `ba` or `bb` of a linearly mapped cartridge, both
 // present) while the opcode agrees and mop covers it.  Same contract as
 // run_fast; `in_b`: the lane is in bank bb.
-__device__ __forceinline__ bool run_mb(Cpu& c, const Wave& W, const uint32_t* pre, bool& ended, uint32_t& end_t,
+__device__ __forceinline__ bool run_mb(Cpu& c, const Wave& W, PreWords pre, bool& ended, uint32_t& end_t,
                                        uint32_t partial, uint32_t ba, uint32_t bb, bool in_b) {
     Fast F;
     F.partial = partial;
@@ -1784,8 +1810,8 @@ __device__ __forceinline__ bool run_mb(Cpu& c, const Wave& W, const uint32_t* pr
         }
         const uint32_t qa = pre[(ba << 12) | (F.pc & 0xFFF)];
         const uint32_t qb = pre[(bb << 12) | (F.pc & 0xFFF)];
-        const uint32_t op = qa & 0xFF;
-        if ((qb & 0xFF) != op) {
+        const uint32_t op = pre_op(qa);
+        if (pre_op(qb) != op) {
             st = FS_EXIT;
             break;
         }
@@ -1886,8 +1912,10 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
         }
         W.ram = reinterpret_cast<uint8_t*>(s_ram);
         W.tia = reinterpret_cast<uint8_t*>(s_tia);
+        W.ram_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)s_ram;
+        W.tia_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)s_tia;
         W.cm = A.cmap[rom_id];
-        W.pre = pre_all + A.pre_off[rom_id];
+        W.pre = (PreWords)(pre_all + A.pre_off[rom_id]);
         W.track = TRACK ? 1u : 0u;
 
         const int env = lane < T.count ? T.env[lane] : -1;
@@ -2070,7 +2098,8 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
                             const uint32_t w0 = rw[boff >> 2], w1 = rw[(boff >> 2) + 1];
                             v = __builtin_amdgcn_alignbyte(w1, w0, boff & 3);
                         } else {                          // segments: the predecoded word
-                            v = W.pre[(c.bank << 12) | off];
+                            const uint32_t q = W.pre[(c.bank << 12) | off];
+                            v = pre_op(q) | ((q >> 8) & 0xFFFF00u);
                         }
                         op = v & 0xFF;
                         b1 = (v >> 8) & 0xFF;
@@ -2229,22 +2258,17 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
     }
 }
 
-// Predecoded ROM: for every virtual bank and offset, opcode | b1 << 8 |
-// b2 << 16 | aux << 24 for the instruction that starts there (each byte read
-// through the bank's mapping, so instructions that cross an E0 or 3F segment
-// boundary decode exactly).  aux is the store class of the address of a
-// zero-page or absolute STA/STX/STY; on 3F cartridges a store to $00-$3F
-// (which also selects a slice) is SC_3F when the TIA register it reaches is
-// not emulated, else SC_EXIT (left to the per-lane path); on Superchip
-// cartridges an absolute access to the RAM window is SC_XRAM; with tracked
-// collisions a zero-page / absolute read of a latch register is SC_EXIT
-// (aux takes 7 bits).  Bit 31 marks an instruction the scalar hot loop
-// leaves to the full dispatch: one after which the pc may leave the window
-// $000-$FFD of the bank (it ends past $FFD, or is a branch whose target is
-// outside), a zero-page read below $80 (a TIA read, not RAM), or a
-// zero-page store to an object reset, enable or vertical-delay register.
-// Entries past offset $FFD are never used.
-__global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre, uint32_t track) {
+// Predecoded ROM: for every virtual bank and offset, the word (pre_op) of the
+// instruction that starts there, each byte read through the bank's mapping, so
+// instructions that cross an E0 or 3F segment boundary decode exactly.  An
+// instruction gets a hot-loop slot when the loop runs it and leaves the pc
+// inside the window $000-$FFD of the bank: it does not end past $FFD, and a
+// branch's or jump's target is inside; zero-page accesses are to RAM (a read
+// below $80 is a TIA read, perhaps a tracked latch), or stores to TIA
+// registers kept as they are, GRP0 / GRP1, WSYNC or nothing emulated (object
+// resets, enables and what the per-lane path takes are not).  Entries past
+// offset $FFD are never used.
+__global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= R.n_vbanks * 4096u) return;
     const uint32_t bank = i >> 12, off = i & 0xFFF;
@@ -2252,33 +2276,38 @@ __global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre, uint32
     const uint32_t b1 = off + 1 < 4096 ? rom[cart_rom_off(R, bank, 0x1000 | (off + 1))] : 0;
     const uint32_t b2 = off + 2 < 4096 ? rom[cart_rom_off(R, bank, 0x1000 | (off + 2))] : 0;
     const uint32_t d = kDecode.w[op];
-    const uint32_t md = d & 15, abs_addr = (b1 | (b2 << 8)) & 0x1FFF;
-    uint32_t aux = 0;
-    const bool st = op == 0x84 || op == 0x85 || op == 0x86 || op == 0x8C || op == 0x8D || op == 0x8E;
-    const uint32_t a = (op == 0x84 || op == 0x85 || op == 0x86) ? b1 : abs_addr;
-    if (st) {
-        aux = store_class(a);
-        if (R.kind == CART_3F && a <= 0x3F) aux = aux == SC_IGNORE ? SC_3F : SC_EXIT;
+    const uint32_t md = d & 15, len = (d >> DW_LEN) & 3;
+    uint32_t slot = HOT_REAL, cls = 0;
+    if (off + len <= 0xFFD) {
+        const bool st = op == 0x84 || op == 0x85 || op == 0x86;
+        if (st) {
+            cls = cart_store_class(R.kind, R.sc, b1);
+            const uint32_t k = op == 0x85 ? 0 : op == 0x86 ? HOT_STX_TIA : HOT_STY_TIA;
+            if (cls == SC_RAM) slot = kHotSlot.s[op];
+            else if (cls == SC_WSYNC) slot = HOT_WSYNC;
+            else if (cls == SC_IGNORE) slot = HOT_ST_NOP;
+            else if (cls >= SC_TIA && cls < SC_TIAS) slot = k ? k : HOT_STA_TIA;
+            else if (cls == (SC_TIAG | R_GRP0)) slot = k ? k + 1 : HOT_STA_GRP0;
+            else if (cls == (SC_TIAG | R_GRP1)) slot = k ? k + 2 : HOT_STA_GRP1;
+        } else if ((op & 0x1F) == 0x10) {              // conditional branch
+            const uint32_t next = off + 2, t = next + (uint32_t)(int32_t)(int8_t)b1;
+            const uint32_t k = op >> 5;
+            const uint32_t cross = HOT_BPL_X + k;
+            if (t <= 0xFFD) slot = ((t ^ next) & 0xF00) ? cross : kHotSlot.s[op];
+        } else if (op == 0x4C) {                       // JMP: the target's window
+            const uint32_t t = (b1 | (b2 << 8)) & 0x1FFF;
+            if (t - 0x1000u <= 0xFFDu) slot = kHotSlot.s[op];
+        } else if (md != ZP || b1 >= 0x80) {
+            slot = kHotSlot.s[op];
+        }
     }
-    if (R.sc && md == ABS && ((d >> DW_RD) & 1 || (d >> DW_WR) & 1) && (abs_addr & 0x1000) && !(abs_addr & 0xF00))
-        aux = SC_XRAM;
-    // tracked collision latches: zero-page / absolute reads of CXM0P..CXPPMM
-    const uint32_t ra = md == ZP ? b1 : abs_addr;
-    if (track && (md == ZP || md == ABS) && ((d >> DW_RD) & 1) && !((d >> DW_WR) & 1) && !(ra & 0x1080) && (ra & 0xF) < 8)
-        aux = SC_EXIT;
-    bool edge = off + ((d >> DW_LEN) & 3) > 0xFFD;
-    if ((op & 0x1F) == 0x10) {             // conditional branch: its target
-        const int32_t t = (int32_t)off + 2 + (int32_t)(int8_t)b1;
-        edge = edge || t < 0 || t > 0xFFD;
-    }
-    if (md == ZP && ((d >> DW_RD) & 1) && b1 < 0x80) edge = true;   // a TIA read
-    if (md == ZP && st && aux >= SC_TIAS && aux < SC_TIAG) edge = true;   // an object reset or enable
-    pre[i] = op | (b1 << 8) | (b2 << 16) | (aux << 24) | ((edge ? 1u : 0u) << 31);
+    const uint32_t low = slot == HOT_REAL ? (op & 0x7F) | ((op & 0x80) << 8) : cls;
+    pre[i] = low | (slot << 7) | (b1 << 16) | (b2 << 24);
 }
 
-void launch_predecode(const uint8_t* rom, const RomInfo& info, uint32_t* pre, uint32_t track, hipStream_t s) {
+void launch_predecode(const uint8_t* rom, const RomInfo& info, uint32_t* pre, hipStream_t s) {
     const uint32_t n = info.n_vbanks * 4096u;
-    hipLaunchKernelGGL(k_predecode, dim3((n + 255) / 256), dim3(256), 0, s, rom, info, pre, track);
+    hipLaunchKernelGGL(k_predecode, dim3((n + 255) / 256), dim3(256), 0, s, rom, info, pre);
 }
 
 template <bool TRACK, bool NOOPS>
