@@ -1586,7 +1586,7 @@ __device__ __forceinline__ bool run_fast(Cpu& c, const Wave& W, PreWords pre, bo
             st = FS_EXIT;
             break;
         }
-        if (__builtin_amdgcn_ballot_w64((c.p & FD) != 0) == 0) {
+        if ((F.pc & 0xFFF) <= 0xFFC && __builtin_amdgcn_ballot_w64((c.p & FD) != 0) == 0) {
             const uint32_t line = F.cyc / 76, line_cyc = 76 * line;
             const uint32_t lines = 320u + (uint32_t)F.fl - line;
             HotRegs H;
@@ -2262,7 +2262,7 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
 // instruction that starts there, each byte read through the bank's mapping, so
 // instructions that cross an E0 or 3F segment boundary decode exactly.  An
 // instruction gets a hot-loop slot when the loop runs it and leaves the pc
-// inside the window $000-$FFD of the bank: it does not end past $FFD, and a
+// inside $000-$FFC of the bank: it does not end past $FFC, and a
 // branch's or jump's target is inside; zero-page accesses are to RAM (a read
 // below $80 is a TIA read, perhaps a tracked latch), or stores to TIA
 // registers kept as they are, GRP0 / GRP1, WSYNC or nothing emulated (object
@@ -2278,25 +2278,25 @@ __global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre) {
     const uint32_t d = kDecode.w[op];
     const uint32_t md = d & 15, len = (d >> DW_LEN) & 3;
     uint32_t slot = HOT_REAL, cls = 0;
-    if (off + len <= 0xFFD) {
+    if (off + len <= 0xFFC) {                          // (the hot loop loads four words from there)
         const bool st = op == 0x84 || op == 0x85 || op == 0x86;
         if (st) {
             cls = cart_store_class(R.kind, R.sc, b1);
-            const uint32_t k = op == 0x85 ? 0 : op == 0x86 ? HOT_STX_TIA : HOT_STY_TIA;
+            const uint32_t k = op == 0x85 ? 0 : op == 0x86 ? HOT_STX_TIA : HOT_STY_TIA;   // then + 1 GRP0, + 2 GRP1
             if (cls == SC_RAM) slot = kHotSlot.s[op];
             else if (cls == SC_WSYNC) slot = HOT_WSYNC;
             else if (cls == SC_IGNORE) slot = HOT_ST_NOP;
-            else if (cls >= SC_TIA && cls < SC_TIAS) slot = k ? k : HOT_STA_TIA;
+            else if (cls >= SC_TIA && cls < SC_TIAS) slot = k ? k : hot_tia_slot(cls & 0x1F);
             else if (cls == (SC_TIAG | R_GRP0)) slot = k ? k + 1 : HOT_STA_GRP0;
             else if (cls == (SC_TIAG | R_GRP1)) slot = k ? k + 2 : HOT_STA_GRP1;
         } else if ((op & 0x1F) == 0x10) {              // conditional branch
             const uint32_t next = off + 2, t = next + (uint32_t)(int32_t)(int8_t)b1;
             const uint32_t k = op >> 5;
             const uint32_t cross = HOT_BPL_X + k;
-            if (t <= 0xFFD) slot = ((t ^ next) & 0xF00) ? cross : kHotSlot.s[op];
+            if (t <= 0xFFC) slot = ((t ^ next) & 0xF00) ? cross : kHotSlot.s[op];
         } else if (op == 0x4C) {                       // JMP: the target's window
             const uint32_t t = (b1 | (b2 << 8)) & 0x1FFF;
-            if (t - 0x1000u <= 0xFFDu) slot = kHotSlot.s[op];
+            if (t - 0x1000u <= 0xFFCu) slot = kHotSlot.s[op];
         } else if (md != ZP || b1 >= 0x80) {
             slot = kHotSlot.s[op];
         }
