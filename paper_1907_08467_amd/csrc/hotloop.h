@@ -1,10 +1,10 @@
 // The scalar path's hot loop: threaded code for the instructions that make up
 // almost all of a cartridge's work, written as one block of gfx950 assembly.
 //
-// What it computes: the same instructions, in the same order, as run_fast's
-// full dispatch (interp.hip) -- the wave's group of lanes stands at one place,
-// so program counter, cycle and row-log position are scalars and only A, X, Y,
-// the flags, RAM, TIA registers and log stores are per lane.
+// What it computes: the same instructions, in the same order in every lane, as
+// the full dispatch (run_cold, interp.hip) -- a group of lanes that stands at
+// one place shares program counter, cycle and row-log position as scalars, and
+// only A, X, Y, the flags, RAM, TIA registers and log stores are per lane.
 //
 // What bounds it: the latency of one wave's instruction stream (at most one
 // wave per SIMD runs, and each pass depends on the one before).  On gfx950 an
@@ -33,10 +33,8 @@
 //    and the frame row of the current line is 286 - L.
 //
 // It stops before an instruction it does not cover (any word whose slot is
-// HOT_REAL), a branch whose lanes part, a store whose effect falls on the next
-// line or finds its log row full, and after a WSYNC when the group is not the
-// whole wave.  Decimal mode is off in every lane on entry and nothing here
-// turns it on.
+// HOT_REAL), an ADC or SBC in decimal mode, a store whose effect falls on the
+// next line or finds its log row full, and at the frame's cycle cap.
 //
 // Every wait that a load needs is inside the block, in the handler that uses
 // the value or before the block's end.
@@ -47,20 +45,29 @@ namespace vcs {
 // Slots, and the opcode each runs (HOT_REAL: the word carries it).  Zero-page
 // operands are RAM; a store of A to a TIA register that is kept as is has a
 // slot per register (hot_tia_slot), one of X or Y takes the register's code
-// from the word; GRP0 / GRP1 stores also update the delayed copies; HOT_WSYNC
+// from the word; GRP0 / GRP1 stores also update the delayed copies; HOT_FLAG + i
+// is a store of A to ENAM0, ENAM1, ENABL, VDELP0, VDELP1, VDELBL (two slots
+// each); HOT_XR_* and HOT_XW access Superchip RAM through its read and write
+// port; HOT_ABS is LDA from a linearly mapped cartridge, HOT_HS the same from a
+// bank hotspot (the new bank in the word's low bits); HOT_WSYNC
 // and HOT_ST_NOP (nothing emulated changes) stand for a store of A, X or Y; the
 // *_X branches cross a page when taken.  Long handlers have several slots.
 constexpr uint32_t HOT_REAL = 0, HOT_STA_TIA = 1,
-                   HOT_STA_GRP0 = 14, HOT_STA_GRP1 = 16, HOT_STX_TIA = 19, HOT_STX_GRP0 = 20, HOT_STX_GRP1 = 21, HOT_STY_TIA = 22, HOT_STY_GRP0 = 23, HOT_STY_GRP1 = 24,
-                   HOT_WSYNC = 27, HOT_ST_NOP = 28, HOT_BPL_X = 29, kHotPlain = 37;
-constexpr uint32_t kHotSlots = 95;
+                   HOT_STA_GRP0 = 14, HOT_STA_GRP1 = 16, HOT_STX_TIA = 19, HOT_STX_GRP0 = 20, HOT_STX_GRP1 = 21,
+                   HOT_STY_TIA = 22, HOT_STY_GRP0 = 23, HOT_STY_GRP1 = 24, HOT_FLAG = 27, HOT_XR_LDA = 39,
+                   HOT_XR_ADC = 40, HOT_XR_AND = 41, HOT_XR_EOR = 42, HOT_XR_ORA = 43, HOT_XW = 44,
+                   HOT_ABS = 45, HOT_HS = 46, HOT_WSYNC = 47, HOT_ST_NOP = 48, HOT_BPL_X = 49,
+                   kHotPlain = 57;
+constexpr uint32_t kHotSlots = 116;
 constexpr uint8_t kHotSlotOp[kHotSlots] = {
     0x00, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85,
-    0x85, 0x85, 0x85, 0x86, 0x86, 0x86, 0x84, 0x84, 0x84, 0x00, 0x00, 0x85, 0x85, 0x10, 0x30, 0x50,
-    0x70, 0x90, 0xB0, 0xD0, 0xF0, 0x05, 0x06, 0x09, 0x0A, 0x10, 0x18, 0x24, 0x25, 0x26, 0x29, 0x2A,
-    0x30, 0x38, 0x45, 0x46, 0x49, 0x4A, 0x4C, 0x50, 0x65, 0x66, 0x69, 0x6A, 0x70, 0x84, 0x85, 0x86,
-    0x88, 0x8A, 0x90, 0x98, 0xA0, 0xA2, 0xA4, 0xA5, 0xA6, 0xA8, 0xA9, 0xAA, 0xB0, 0xB8, 0xC0, 0xC4,
-    0xC5, 0xC6, 0xC8, 0xC9, 0xCA, 0xD0, 0xD8, 0xE0, 0xE4, 0xE5, 0xE6, 0xE8, 0xE9, 0xEA, 0xF0,
+    0x85, 0x85, 0x85, 0x86, 0x86, 0x86, 0x84, 0x84, 0x84, 0x00, 0x00, 0x85, 0x85, 0x85, 0x85, 0x85,
+    0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0xAD, 0x6D, 0x2D, 0x4D, 0x0D, 0x8D, 0xAD, 0xAD, 0x85,
+    0x85, 0x10, 0x30, 0x50, 0x70, 0x90, 0xB0, 0xD0, 0xF0, 0x05, 0x06, 0x09, 0x0A, 0x10, 0x18, 0x24,
+    0x25, 0x26, 0x29, 0x2A, 0x30, 0x38, 0x45, 0x46, 0x49, 0x4A, 0x4C, 0x50, 0x65, 0x66, 0x69, 0x6A,
+    0x70, 0x84, 0x85, 0x86, 0x88, 0x8A, 0x90, 0x98, 0xA0, 0xA2, 0xA4, 0xA5, 0xA6, 0xA8, 0xA9, 0xAA,
+    0xB0, 0xB8, 0xC0, 0xC4, 0xC5, 0xC6, 0xC8, 0xC9, 0xCA, 0xD0, 0xD8, 0xE0, 0xE4, 0xE5, 0xE6, 0xE8,
+    0xE9, 0xEA, 0xF0, 0xF8,
 };
 // The slot that runs opcode `op` without a page-crossing branch or a TIA store
 // (HOT_REAL: none).
@@ -77,10 +84,6 @@ __host__ __device__ constexpr uint32_t hot_tia_slot(uint32_t code) {
 
 // ACC: cycle in the line + 52 in the top 7 bits, instructions below
 constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) - 1;
-
-// what ended the block
-constexpr uint32_t HOT_EXIT_NEXT = 0;     // before the instruction at PO
-constexpr uint32_t HOT_EXIT_LINE = 1;     // after a WSYNC: a partial group stops, or the cap is reached
 
 #define HL_ORG(B, slot) ".org " B "%= + 128*" #slot "\n"
 #define HL_WAIT "s_waitcnt lgkmcnt(0)\n"
@@ -105,11 +108,14 @@ constexpr uint32_t HOT_EXIT_LINE = 1;     // after a WSYNC: a partial group stop
 // implied
 #define HL_IMP(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_TGT("s77") HL_FETCH(1) work HL_GO(2)
 // immediate: operand in s86
-#define HL_IMM(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_B1_8 HL_TGT("s78") HL_FETCH(2) work HL_GO(2)
+#define HL_IMM_(work) HL_B1_8 HL_TGT("s78") HL_FETCH(2) work HL_GO(2)
+#define HL_IMM(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_IMM_(work)
+#define HL_IMMD(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_BIN HL_IMM_(work)
 // zero-page read whose result the handler needs: operand in v123
-#define HL_ZPR(B, slot, work)                                                                      \
-    HL_ORG(B, slot) HL_WAIT HL_B1_7 HL_RAMADDR "ds_read_u8 v123, v122\n" HL_TGT("s78") HL_FETCH(2) \
-    HL_ACC(3) HL_WAIT work HL_JUMP
+#define HL_ZPR_(work)                                                                              \
+    HL_B1_7 HL_RAMADDR "ds_read_u8 v123, v122\n" HL_TGT("s78") HL_FETCH(2) HL_ACC(3) HL_WAIT work HL_JUMP
+#define HL_ZPR(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_ZPR_(work)
+#define HL_ZPRD(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_BIN HL_ZPR_(work)
 // zero-page load: lands in the register and nz before the next handler's wait ends
 #define HL_ZPL(B, slot, reg)                                                                       \
     HL_ORG(B, slot) HL_WAIT HL_B1_7 HL_RAMADDR "ds_read_u8 " reg ", v122\n"                        \
@@ -122,7 +128,12 @@ constexpr uint32_t HOT_EXIT_LINE = 1;     // after a WSYNC: a partial group stop
     HL_ACC(5) HL_WAIT work "ds_write_b8 v122, v123\n" HL_JUMP
 
 #define HL_NZ(reg) "v_mov_b32 %[nz], " reg "\n"
+#define HL_LDV "v_mov_b32 %[a], v123\nv_mov_b32 %[nz], v123\n"
 #define HL_LDI(reg) "v_mov_b32 " reg ", s86\nv_mov_b32 %[nz], s86\n"
+// ADC and SBC leave groups with a lane in decimal mode (s[50:51]) to the full dispatch
+#define HL_BIN                                             \
+    "s_and_b64 s[96:97], s[50:51], exec\n"                 \
+    "s_cbranch_scc1 .Lout%=\n"
 // arithmetic on A and operand `m` (a register or s86)
 #define HL_AND(m) "v_and_b32 %[a], " m ", %[a]\n" HL_NZ("%[a]")
 #define HL_ORA(m) "v_or_b32 %[a], " m ", %[a]\n" HL_NZ("%[a]")
@@ -171,8 +182,8 @@ constexpr uint32_t HOT_EXIT_LINE = 1;     // after a WSYNC: a partial group stop
     "v_and_b32 %[c], 1, " r "\n"                           \
     "v_lshrrev_b32 " r ", 1, v124\n" HL_NZ(r)
 
-// branch: `test` sets vcc in the lanes that take it; taken: cycles' ACC step
-// in scalar `tk`.  Both successors' words are loaded before the test is known.
+// branch: `test` sets vcc in the lanes that take it, for the ACC step in s98 (3
+// cycles) or s99 (4).  Both successors' words are loaded before the test is known.
 #define HL_BR(B, slot, test, tk)                           \
     HL_ORG(B, slot) HL_WAIT                                \
     "s_bfe_i32 s86, s76, 0x80010\n"                        \
@@ -182,10 +193,10 @@ constexpr uint32_t HOT_EXIT_LINE = 1;     // after a WSYNC: a partial group stop
     "s_load_dwordx4 s[76:79], s[70:71], s88\n" test        \
     "s_cmp_eq_u64 vcc, exec\n"                             \
     "s_cselect_b32 s72, s89, s88\n"                        \
-    "s_cselect_b32 s87, " tk ", (2<<25)+1\n"               \
+    "s_cselect_b32 s87, s9" tk ", (2<<25)+1\n"             \
     "s_cselect_b64 s[96:97], exec, 0\n"                    \
     "s_cmp_lg_u64 vcc, s[96:97]\n"                         \
-    "s_cbranch_scc1 .Lpart%=\n"                            \
+    "s_cbranch_scc1 .Lpart" tk "%=\n"                      \
     "s_cmp_eq_u64 s[96:97], exec\n" HL_WAIT                \
     "s_cselect_b64 s[76:77], s[60:61], s[76:77]\n"         \
     "s_cselect_b64 s[78:79], s[62:63], s[78:79]\n"         \
@@ -195,14 +206,56 @@ constexpr uint32_t HOT_EXIT_LINE = 1;     // after a WSYNC: a partial group stop
 #define HL_T_NE(mask, src) "v_and_b32 v122, " mask ", " src "\nv_cmp_ne_u32 vcc, 0, v122\n"
 #define HL_T_EQ(mask, src) "v_and_b32 v122, " mask ", " src "\nv_cmp_eq_u32 vcc, 0, v122\n"
 
-// absolute jump (the target lies in the cartridge window; pc bits 12-15 kept apart)
+// absolute jump (the target lies in the cartridge window; one that changes pc
+// bits 12-15, kept in KEY, is left to the full dispatch)
 #define HL_JMP(B, slot)                                    \
     HL_ORG(B, slot) HL_WAIT                                \
-    "s_lshr_b32 s86, s76, 16\n"                            \
-    "s_and_b32 s93, s86, 0xf000\n"                         \
-    "s_and_b32 s86, s86, 0xfff\n"                          \
-    "s_lshl2_add_u32 s72, s86, s68\n"                      \
+    "s_xor_b32 s86, s76, s59\n"                            \
+    "s_lshr_b32 s86, s86, 28\n"                            \
+    "s_cbranch_scc1 .Lout%=\n"                             \
+    "s_bfe_u32 s86, s76, 0xc0010\n"                        \
+    "s_and_b32 s72, s72, 0xffffc000\n"                     \
+    "s_lshl2_add_u32 s72, s86, s72\n"                      \
     "s_load_dwordx4 s[76:79], s[70:71], s72\n" HL_WAIT HL_TGT("s76") HL_GO(3)
+
+// LDA absolute from the tile's cartridge s[40:41] (linear: bank << 12 | offset)
+#define HL_ABSBYTE                                         \
+    "s_and_b32 s87, s86, -4\n"                             \
+    "s_load_dword s94, s[40:41], s87\n"                    \
+    "s_lshl_b32 s86, s86, 3\n" HL_WAIT                     \
+    "s_lshr_b32 s94, s94, s86\n"                           \
+    "s_and_b32 s86, s94, 0xff\n" HL_LDI("%[a]")
+#define HL_ABS(B, slot)                                    \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "s_lshr_b32 s87, s72, 14\n"                            \
+    "s_bfe_u32 s86, s76, 0xc0010\n"                        \
+    "s_lshl_b32 s87, s87, 12\n"                            \
+    "s_or_b32 s86, s86, s87\n" HL_TGT("s79") HL_FETCH(3)   \
+    HL_ABSBYTE HL_GO(4)
+#define HL_HS(B, slot)                                     \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "s_and_b32 s87, s76, 7\n"                              \
+    "s_bfe_u32 s86, s76, 0xc0010\n"                        \
+    "s_lshl_b32 s88, s87, 14\n"                            \
+    "s_lshl_b32 s87, s87, 12\n"                            \
+    "s_add_u32 s72, s72, 12\n"                             \
+    "s_and_b32 s72, s72, 0x3fff\n"                         \
+    "s_or_b32 s72, s72, s88\n"                             \
+    "s_or_b32 s86, s86, s87\n"                             \
+    "s_load_dwordx4 s[76:79], s[70:71], s72\n" HL_ABSBYTE HL_TGT("s76") HL_GO(4)
+// Superchip RAM of the lane's env, in HBM: operand in v123 (the wait includes
+// the log stores before it)
+#define HL_XADDR                                           \
+    "s_bfe_u32 s66, s76, 0x70010\n"                        \
+    "v_lshl_add_u64 v[120:121], s[66:67], 0, %[xram]\n"
+#define HL_XR_(work)                                       \
+    HL_XADDR "global_load_ubyte v123, v[120:121], off\n" HL_TGT("s79") HL_FETCH(3) HL_ACC(4)        \
+    "s_waitcnt vmcnt(0)\n" work HL_JUMP
+#define HL_XR(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_XR_(work)
+#define HL_XRD(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_BIN HL_XR_(work)
+#define HL_XW(B, slot)                                     \
+    HL_ORG(B, slot) HL_WAIT HL_XADDR                       \
+    "global_store_byte v[120:121], %[a], off\n" HL_TGT("s79") HL_FETCH(3) HL_GO(4)
 
 // WSYNC: on to the next line's start.  Left (.Lsync) when the run stops there
 // or a write at the line's last cycles stalls a line longer.
@@ -219,22 +272,24 @@ constexpr uint32_t HOT_EXIT_LINE = 1;     // after a WSYNC: a partial group stop
 // TIA register stores (2 bytes, 3 cycles).  `val`: the stored register.
 //
 // Logged: the entry goes into the open row when that is the line's row and the
-// line has not ended (s87 = the line's number, or -1 past its end, against the
-// open row's); else .Lsnap opens rows first, or leaves the store to the full
-// dispatch.  `code8`: the entry's register code << 8 less 3 * 52 + 68.
+// line has not ended (the line's number, or -1 past its end, against the open
+// row's); else .Lsnap opens rows first, or leaves the store to the full
+// dispatch.  `code8`: the entry's register code << 8 less 3 * 52 + 68.  Where
+// the entry goes is per lane: lanes whose earlier writes fell on different
+// sides of a line's visible part have logged different numbers of entries, and
+// still run as one group.
 #define HL_LOGGED(id, val, code8, write)                   \
     "s_add_u32 s73, s73, (3<<25)+1\n"                      \
     "s_cselect_b32 s87, -1, s80\n"                         \
     "s_lshr_b32 s88, s73, 25\n"                            \
     "s_cmp_lg_u32 s87, s83\n"                              \
-    "v_lshl_add_u64 v[120:121], s[90:91], 2, %[log]\n"     \
+    "s_mul_i32 s87, s88, 3\n"                              \
     "s_cbranch_scc1 .Lrow" id "%=\n"                       \
     ".Lent" id "%=:\n"                                     \
-    "s_mul_i32 s87, s88, 3\n"                              \
-    "s_add_u32 s90, s90, 1\n"                              \
     "s_add_u32 s87, s87, " code8 "\n"                      \
     "v_lshl_or_b32 v123, " val ", 16, s87\n"               \
-    "global_store_dword v[120:121], v123, off\n"           \
+    "global_store_dword v[100:101], v123, off\n"           \
+    "v_lshl_add_u64 v[100:101], 1, 2, v[100:101]\n"        \
     ".Lreg" id "%=:\n" write HL_JUMP                       \
     ".Lrow" id "%=:\n"                                     \
     "s_swappc_b64 s[96:97], s[64:65]\n"                    \
@@ -296,12 +351,25 @@ constexpr uint32_t HOT_EXIT_LINE = 1;     // after a WSYNC: a partial group stop
     HL_ORG(B, slot) HL_WAIT "v_mov_b32 v125, %[a]\n"       \
     ".Lbhu%=:\n" HL_GRP1_READ HL_TGT("s78") HL_FETCH(2)     \
     HL_ACC(3) HL_GRP1_WRITE HL_JUMP
+// ENAMx, ENABL (bit 1), VDELx (bit 0): bit k of the flags byte and the full byte 32 + k
+#define HL_FLAG_(slot, B, k, bit)                          \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "ds_read_u8 v124, %[tia] offset:23\n"                  \
+    "v_bfe_u32 v122, %[a], " #bit ", 1\n" HL_TGT("s78") HL_FETCH(2) HL_WAIT \
+    "v_and_b32 v124, ~(1<<" #k "), v124\n"                 \
+    "v_lshl_or_b32 v125, v122, " #k ", v124\n"
+#define HL_FLAG_WRITE(k)                                   \
+    "ds_write_b8 %[tia], v125 offset:23\n"                 \
+    "ds_write_b8 %[tia], %[a] offset:32+" #k "\n"
+#define HL_FLAG_LOG(B, slot, k, bit)                       \
+    HL_FLAG_(slot, B, k, bit) HL_LOGGED("f" #k, "v125", "23*256-224", HL_FLAG_WRITE(k))
+#define HL_FLAG_NOLOG(B, slot, k, bit) HL_FLAG_(slot, B, k, bit) HL_FLAG_WRITE(k) HL_GO(3)
 #define HL_XY_LOG(B, slot, reg, body) HL_XY_(B, slot, reg, ".Lb" body "l")
 #define HL_XY_NOLOG(B, slot, reg, body) HL_XY_(B, slot, reg, ".Lb" body "u")
 
 // Every handler of one of the two blocks (frames whose writes are logged, and
 // the others: dispatch by block spares each TIA store the question).
-#define HL_BLOCK(B, TIA, TIAX, GRP0, GRP1, HL_XY) \
+#define HL_BLOCK(B, TIA, TIAX, GRP0, GRP1, HL_XY, FLAG) \
     HL_ORG(B, 0) "s_branch .Lout%=\n"                                                                /* HOT_REAL */ \
     TIA(B, 1, 0)                                                                                     /* STA COLUP0 */ \
     TIA(B, 2, 1)                                                                                     /* STA COLUP1 */ \
@@ -325,148 +393,363 @@ constexpr uint32_t HOT_EXIT_LINE = 1;     // after a WSYNC: a partial group stop
     HL_XY(B, 23, "%[y]", "g")                                                                        /* STY GRP0 */ \
     HL_XY(B, 24, "%[y]", "h")                                                                        /* STY GRP1 */ \
     TIAX(B, 25)                                                                                      /* the body of the two stores to a TIA register */ \
-    HL_SYNC(B, 27)                                                                                   /* WSYNC */ \
-    HL_ORG(B, 28) HL_WAIT HL_TGT("s78") HL_FETCH(2) HL_GO(3)                                         /* store without effect */ \
-    HL_BR(B, 29, HL_T_EQ("0x180", "%[nz]"), "s99")                                                   /* BPL across a page */ \
-    HL_BR(B, 30, HL_T_NE("0x180", "%[nz]"), "s99")                                                   /* BMI across a page */ \
-    HL_BR(B, 31, HL_T_EQ("0x80", "%[v]"), "s99")                                                     /* BVC across a page */ \
-    HL_BR(B, 32, HL_T_NE("0x80", "%[v]"), "s99")                                                     /* BVS across a page */ \
-    HL_BR(B, 33, "v_cmp_eq_u32 vcc, 0, %[c]\n", "s99")                                               /* BCC across a page */ \
-    HL_BR(B, 34, "v_cmp_ne_u32 vcc, 0, %[c]\n", "s99")                                               /* BCS across a page */ \
-    HL_BR(B, 35, HL_T_NE("0xff", "%[nz]"), "s99")                                                    /* BNE across a page */ \
-    HL_BR(B, 36, HL_T_EQ("0xff", "%[nz]"), "s99")                                                    /* BEQ across a page */ \
-    HL_ZPR(B, 37, HL_ORA("v123"))                                                                    /* $05 */ \
-    HL_ZPM(B, 38, HL_ASL("v123"))                                                                    /* $06 */ \
-    HL_IMM(B, 39, HL_ORA("s86"))                                                                     /* $09 */ \
-    HL_IMP(B, 40, HL_ASL("%[a]"))                                                                    /* $0A */ \
-    HL_BR(B, 41, HL_T_EQ("0x180", "%[nz]"), "s98")                                                   /* $10 */ \
-    HL_IMP(B, 42, "v_mov_b32 %[c], 0\n")                                                             /* $18 */ \
-    HL_ZPR(B, 43, HL_BIT)                                                                            /* $24 */ \
-    HL_ZPR(B, 44, HL_AND("v123"))                                                                    /* $25 */ \
-    HL_ZPM(B, 45, HL_ROL("v123"))                                                                    /* $26 */ \
-    HL_IMM(B, 46, HL_AND("s86"))                                                                     /* $29 */ \
-    HL_IMP(B, 47, HL_ROL("%[a]"))                                                                    /* $2A */ \
-    HL_BR(B, 48, HL_T_NE("0x180", "%[nz]"), "s98")                                                   /* $30 */ \
-    HL_IMP(B, 49, "v_mov_b32 %[c], 1\n")                                                             /* $38 */ \
-    HL_ZPR(B, 50, HL_EOR("v123"))                                                                    /* $45 */ \
-    HL_ZPM(B, 51, HL_LSR("v123"))                                                                    /* $46 */ \
-    HL_IMM(B, 52, HL_EOR("s86"))                                                                     /* $49 */ \
-    HL_IMP(B, 53, HL_LSR("%[a]"))                                                                    /* $4A */ \
-    HL_JMP(B, 54)                                                                                    /* $4C */ \
-    HL_BR(B, 55, HL_T_EQ("0x80", "%[v]"), "s98")                                                     /* $50 */ \
-    HL_ZPR(B, 56, HL_ADC("v123"))                                                                    /* $65 */ \
-    HL_ZPM(B, 57, HL_ROR("v123"))                                                                    /* $66 */ \
-    HL_IMM(B, 58, HL_ADC("s86"))                                                                     /* $69 */ \
-    HL_IMP(B, 59, HL_ROR("%[a]"))                                                                    /* $6A */ \
-    HL_BR(B, 60, HL_T_NE("0x80", "%[v]"), "s98")                                                     /* $70 */ \
-    HL_ZPS(B, 61, "%[y]")                                                                            /* $84 */ \
-    HL_ZPS(B, 62, "%[a]")                                                                            /* $85 */ \
-    HL_ZPS(B, 63, "%[x]")                                                                            /* $86 */ \
-    HL_IMP(B, 64, HL_DEC("%[y]"))                                                                    /* $88 */ \
-    HL_IMP(B, 65, "v_mov_b32 %[a], %[x]\n" HL_NZ("%[x]"))                                            /* $8A */ \
-    HL_BR(B, 66, "v_cmp_eq_u32 vcc, 0, %[c]\n", "s98")                                               /* $90 */ \
-    HL_IMP(B, 67, "v_mov_b32 %[a], %[y]\n" HL_NZ("%[y]"))                                            /* $98 */ \
-    HL_IMM(B, 68, HL_LDI("%[y]"))                                                                    /* $A0 */ \
-    HL_IMM(B, 69, HL_LDI("%[x]"))                                                                    /* $A2 */ \
-    HL_ZPL(B, 70, "%[y]")                                                                            /* $A4 */ \
-    HL_ZPL(B, 71, "%[a]")                                                                            /* $A5 */ \
-    HL_ZPL(B, 72, "%[x]")                                                                            /* $A6 */ \
-    HL_IMP(B, 73, "v_mov_b32 %[y], %[a]\n" HL_NZ("%[a]"))                                            /* $A8 */ \
-    HL_IMM(B, 74, HL_LDI("%[a]"))                                                                    /* $A9 */ \
-    HL_IMP(B, 75, "v_mov_b32 %[x], %[a]\n" HL_NZ("%[a]"))                                            /* $AA */ \
-    HL_BR(B, 76, "v_cmp_ne_u32 vcc, 0, %[c]\n", "s98")                                               /* $B0 */ \
-    HL_IMP(B, 77, "v_mov_b32 %[v], 0\n")                                                             /* $B8 */ \
-    HL_IMM(B, 78, HL_CMP_S("%[y]"))                                                                  /* $C0 */ \
-    HL_ZPR(B, 79, HL_CMP("%[y]", "v123"))                                                            /* $C4 */ \
-    HL_ZPR(B, 80, HL_CMP("%[a]", "v123"))                                                            /* $C5 */ \
-    HL_ZPM(B, 81, HL_DEC("v123"))                                                                    /* $C6 */ \
-    HL_IMP(B, 82, HL_INC("%[y]"))                                                                    /* $C8 */ \
-    HL_IMM(B, 83, HL_CMP_S("%[a]"))                                                                  /* $C9 */ \
-    HL_IMP(B, 84, HL_DEC("%[x]"))                                                                    /* $CA */ \
-    HL_BR(B, 85, HL_T_NE("0xff", "%[nz]"), "s98")                                                    /* $D0 */ \
-    HL_IMP(B, 86, "")                                                                                /* $D8 */ \
-    HL_IMM(B, 87, HL_CMP_S("%[x]"))                                                                  /* $E0 */ \
-    HL_ZPR(B, 88, HL_CMP("%[x]", "v123"))                                                            /* $E4 */ \
-    HL_ZPR(B, 89, "v_xor_b32 v123, 0xff, v123\n" HL_ADC("v123"))                                     /* $E5 */ \
-    HL_ZPM(B, 90, HL_INC("v123"))                                                                    /* $E6 */ \
-    HL_IMP(B, 91, HL_INC("%[x]"))                                                                    /* $E8 */ \
-    HL_IMM(B, 92, "s_xor_b32 s86, s86, 0xff\n" HL_ADC("s86"))                                        /* $E9 */ \
-    HL_IMP(B, 93, "")                                                                                /* $EA */ \
-    HL_BR(B, 94, HL_T_EQ("0xff", "%[nz]"), "s98")                                                    /* $F0 */
+    FLAG(B, 27, 0, 1)                                                                                /* STA ENAM0 */ \
+    FLAG(B, 29, 1, 1)                                                                                /* STA ENAM1 */ \
+    FLAG(B, 31, 2, 1)                                                                                /* STA ENABL */ \
+    FLAG(B, 33, 4, 0)                                                                                /* STA VDELP0 */ \
+    FLAG(B, 35, 5, 0)                                                                                /* STA VDELP1 */ \
+    FLAG(B, 37, 6, 0)                                                                                /* STA VDELBL */ \
+    HL_XR(B, 39, HL_LDV)                                                                             /* LDA from Superchip RAM */ \
+    HL_XRD(B, 40, HL_ADC("v123"))                                                                    /* ADC from Superchip RAM */ \
+    HL_XR(B, 41, HL_AND("v123"))                                                                     /* AND from Superchip RAM */ \
+    HL_XR(B, 42, HL_EOR("v123"))                                                                     /* EOR from Superchip RAM */ \
+    HL_XR(B, 43, HL_ORA("v123"))                                                                     /* ORA from Superchip RAM */ \
+    HL_XW(B, 44)                                                                                     /* STA to Superchip RAM */ \
+    HL_ABS(B, 45)                                                                                    /* LDA from the cartridge */ \
+    HL_HS(B, 46)                                                                                     /* LDA from a bank hotspot */ \
+    HL_SYNC(B, 47)                                                                                   /* WSYNC */ \
+    HL_ORG(B, 48) HL_WAIT HL_TGT("s78") HL_FETCH(2) HL_GO(3)                                         /* store without effect */ \
+    HL_BR(B, 49, HL_T_EQ("0x180", "%[nz]"), "9")                                                     /* BPL across a page */ \
+    HL_BR(B, 50, HL_T_NE("0x180", "%[nz]"), "9")                                                     /* BMI across a page */ \
+    HL_BR(B, 51, HL_T_EQ("0x80", "%[v]"), "9")                                                       /* BVC across a page */ \
+    HL_BR(B, 52, HL_T_NE("0x80", "%[v]"), "9")                                                       /* BVS across a page */ \
+    HL_BR(B, 53, "v_cmp_eq_u32 vcc, 0, %[c]\n", "9")                                                 /* BCC across a page */ \
+    HL_BR(B, 54, "v_cmp_ne_u32 vcc, 0, %[c]\n", "9")                                                 /* BCS across a page */ \
+    HL_BR(B, 55, HL_T_NE("0xff", "%[nz]"), "9")                                                      /* BNE across a page */ \
+    HL_BR(B, 56, HL_T_EQ("0xff", "%[nz]"), "9")                                                      /* BEQ across a page */ \
+    HL_ZPR(B, 57, HL_ORA("v123"))                                                                    /* $05 */ \
+    HL_ZPM(B, 58, HL_ASL("v123"))                                                                    /* $06 */ \
+    HL_IMM(B, 59, HL_ORA("s86"))                                                                     /* $09 */ \
+    HL_IMP(B, 60, HL_ASL("%[a]"))                                                                    /* $0A */ \
+    HL_BR(B, 61, HL_T_EQ("0x180", "%[nz]"), "8")                                                     /* $10 */ \
+    HL_IMP(B, 62, "v_mov_b32 %[c], 0\n")                                                             /* $18 */ \
+    HL_ZPR(B, 63, HL_BIT)                                                                            /* $24 */ \
+    HL_ZPR(B, 64, HL_AND("v123"))                                                                    /* $25 */ \
+    HL_ZPM(B, 65, HL_ROL("v123"))                                                                    /* $26 */ \
+    HL_IMM(B, 66, HL_AND("s86"))                                                                     /* $29 */ \
+    HL_IMP(B, 67, HL_ROL("%[a]"))                                                                    /* $2A */ \
+    HL_BR(B, 68, HL_T_NE("0x180", "%[nz]"), "8")                                                     /* $30 */ \
+    HL_IMP(B, 69, "v_mov_b32 %[c], 1\n")                                                             /* $38 */ \
+    HL_ZPR(B, 70, HL_EOR("v123"))                                                                    /* $45 */ \
+    HL_ZPM(B, 71, HL_LSR("v123"))                                                                    /* $46 */ \
+    HL_IMM(B, 72, HL_EOR("s86"))                                                                     /* $49 */ \
+    HL_IMP(B, 73, HL_LSR("%[a]"))                                                                    /* $4A */ \
+    HL_JMP(B, 74)                                                                                    /* $4C */ \
+    HL_BR(B, 75, HL_T_EQ("0x80", "%[v]"), "8")                                                       /* $50 */ \
+    HL_ZPRD(B, 76, HL_ADC("v123"))                                                                   /* $65 */ \
+    HL_ZPM(B, 77, HL_ROR("v123"))                                                                    /* $66 */ \
+    HL_IMMD(B, 78, HL_ADC("s86"))                                                                    /* $69 */ \
+    HL_IMP(B, 79, HL_ROR("%[a]"))                                                                    /* $6A */ \
+    HL_BR(B, 80, HL_T_NE("0x80", "%[v]"), "8")                                                       /* $70 */ \
+    HL_ZPS(B, 81, "%[y]")                                                                            /* $84 */ \
+    HL_ZPS(B, 82, "%[a]")                                                                            /* $85 */ \
+    HL_ZPS(B, 83, "%[x]")                                                                            /* $86 */ \
+    HL_IMP(B, 84, HL_DEC("%[y]"))                                                                    /* $88 */ \
+    HL_IMP(B, 85, "v_mov_b32 %[a], %[x]\n" HL_NZ("%[x]"))                                            /* $8A */ \
+    HL_BR(B, 86, "v_cmp_eq_u32 vcc, 0, %[c]\n", "8")                                                 /* $90 */ \
+    HL_IMP(B, 87, "v_mov_b32 %[a], %[y]\n" HL_NZ("%[y]"))                                            /* $98 */ \
+    HL_IMM(B, 88, HL_LDI("%[y]"))                                                                    /* $A0 */ \
+    HL_IMM(B, 89, HL_LDI("%[x]"))                                                                    /* $A2 */ \
+    HL_ZPL(B, 90, "%[y]")                                                                            /* $A4 */ \
+    HL_ZPL(B, 91, "%[a]")                                                                            /* $A5 */ \
+    HL_ZPL(B, 92, "%[x]")                                                                            /* $A6 */ \
+    HL_IMP(B, 93, "v_mov_b32 %[y], %[a]\n" HL_NZ("%[a]"))                                            /* $A8 */ \
+    HL_IMM(B, 94, HL_LDI("%[a]"))                                                                    /* $A9 */ \
+    HL_IMP(B, 95, "v_mov_b32 %[x], %[a]\n" HL_NZ("%[a]"))                                            /* $AA */ \
+    HL_BR(B, 96, "v_cmp_ne_u32 vcc, 0, %[c]\n", "8")                                                 /* $B0 */ \
+    HL_IMP(B, 97, "v_mov_b32 %[v], 0\n")                                                             /* $B8 */ \
+    HL_IMM(B, 98, HL_CMP_S("%[y]"))                                                                  /* $C0 */ \
+    HL_ZPR(B, 99, HL_CMP("%[y]", "v123"))                                                            /* $C4 */ \
+    HL_ZPR(B, 100, HL_CMP("%[a]", "v123"))                                                           /* $C5 */ \
+    HL_ZPM(B, 101, HL_DEC("v123"))                                                                   /* $C6 */ \
+    HL_IMP(B, 102, HL_INC("%[y]"))                                                                   /* $C8 */ \
+    HL_IMM(B, 103, HL_CMP_S("%[a]"))                                                                 /* $C9 */ \
+    HL_IMP(B, 104, HL_DEC("%[x]"))                                                                   /* $CA */ \
+    HL_BR(B, 105, HL_T_NE("0xff", "%[nz]"), "8")                                                     /* $D0 */ \
+    HL_IMP(B, 106, "s_andn2_b64 s[50:51], s[50:51], exec\n")                                         /* $D8 */ \
+    HL_IMM(B, 107, HL_CMP_S("%[x]"))                                                                 /* $E0 */ \
+    HL_ZPR(B, 108, HL_CMP("%[x]", "v123"))                                                           /* $E4 */ \
+    HL_ZPRD(B, 109, "v_xor_b32 v123, 0xff, v123\n" HL_ADC("v123"))                                   /* $E5 */ \
+    HL_ZPM(B, 110, HL_INC("v123"))                                                                   /* $E6 */ \
+    HL_IMP(B, 111, HL_INC("%[x]"))                                                                   /* $E8 */ \
+    HL_IMMD(B, 112, "s_xor_b32 s86, s86, 0xff\n" HL_ADC("s86"))                                      /* $E9 */ \
+    HL_IMP(B, 113, "")                                                                               /* $EA */ \
+    HL_BR(B, 114, HL_T_EQ("0xff", "%[nz]"), "8")                                                     /* $F0 */ \
+    HL_IMP(B, 115, "s_or_b64 s[50:51], s[50:51], exec\n")                                            /* $F8 */
 
-// Scalars of a run, in the registers the block uses.
-struct HotRegs {
-    uint32_t po;         // byte offset of the instruction's word in the ROM's table (bank and pc)
-    uint32_t acc;        // ACC
-    uint32_t lines;      // lines until the cap
+// Fold the current group's instruction count into its lanes' counts and the
+// wave's passes (exec: the group).
+#define HL_FOLD(extra)                                     \
+    "s_and_b32 s86, s73, 0x1ffffff\n"                      \
+    "s_and_b32 s73, s73, 0xfe000000\n" extra               \
+    "s_add_u32 s57, s57, s86\n"                            \
+    "v_add_u32 %[ic], s86, %[ic]\n"
+// The group's place in time: its lines left less the frame's first line (more
+// is earlier; lanes of one wave may be in different frames)
+#define HL_TIME                                            \
+    "s_bfe_i32 s86, s59, 0x1b0000\n"                       \
+    "s_sub_u32 s86, s80, s86\n"
+#define HL_LINES                                           \
+    "s_bfe_i32 s86, s59, 0x1b0000\n"                       \
+    "s_add_u32 s80, s80, s86\n"
+// Put the current group, its count folded, into a free lane of the table.
+#define HL_PUT HL_TIME                                     \
+    "s_ff0_i32_b64 s93, s[54:55]\n"                        \
+    "s_bitset1_b64 s[54:55], s93\n"                        \
+    "s_mov_b32 m0, s93\n"                                  \
+    "s_nop 0\n"                                            \
+    "v_writelane_b32 v102, s52, m0\n"                      \
+    "v_writelane_b32 v103, s53, m0\n"                      \
+    "v_writelane_b32 v104, s72, m0\n"                      \
+    "v_writelane_b32 v105, s73, m0\n"                      \
+    "v_writelane_b32 v106, s86, m0\n"                      \
+    "v_writelane_b32 v107, s82, m0\n"                      \
+    "v_writelane_b32 v108, s59, m0\n"
+// Lanes whose fields equal the current group's: vcc
+#define HL_SAME(po, acc, lines, of, orow, key)                 \
+    "v_xor_b32 v122, s72, " po "\n"                        \
+    "v_xor_b32 v123, s73, " acc "\n"                       \
+    "v_xor_b32 v124, " lines ", " of "\n"                     \
+    "v_or3_b32 v122, v122, v123, v124\n"                   \
+    "v_xor_b32 v123, s82, " orow "\n"                      \
+    "v_xor_b32 v124, s59, " key "\n"                       \
+    "v_or3_b32 v122, v122, v123, v124\n"                   \
+    "v_cmp_eq_u32 vcc, 0, v122\n"
+#define HL_TOLANES                                         \
+    "v_mov_b32 %[po], s72\n"                               \
+    "v_mov_b32 %[acc], s73\n"                              \
+    "v_mov_b32 %[lines], s80\n"                            \
+    "v_mov_b32 %[orow], s82\n"
+
+// Where a lane stands, as the block keeps it.
+struct HotLane {
+    uint32_t po;         // byte offset of its instruction's word in the ROM's table (virtual bank and
+                         // pc), or kHotNone: the block does not run it
+    uint32_t acc;        // ACC, count 0
+    uint32_t lines;      // lines until the frame's cap
     uint32_t orow;       // open row + 1 (0 = none)
-    uint32_t pos;        // next entry's dword in the frame's log
-    uint32_t obase;      // the open row's first entry's dword
-    uint32_t pchi;       // pc bits 12-15
-    uint32_t why;        // HOT_EXIT_*
+    uint32_t key;        // pc bits 12-15 << 28 | frame logged << 27 | frame line (27 bits)
+    uint64_t lp;         // where the next entry goes (not part of the place)
+    uint32_t obase;      // the open row's first entry, in dwords from the log's start (nor this)
 };
+constexpr uint32_t kHotNone = 0xFFFFFFFFu;
+constexpr uint32_t kHotLogged = 1u << 27;
 
-// Runs the block for the lanes in exec.  ram, tia: LDS addresses; log: the
-// lane's row log (used only when logon); table: the ROM's predecoded words;
-// bankpo: the bank's first word's byte offset; partial: all ones when the run
-// must stop at the next WSYNC, else 0.
-__device__ __forceinline__ void hot_loop(HotRegs& H, uint64_t table, uint32_t bankpo, uint32_t partial,
-                                         uint32_t logon, uint32_t& a, uint32_t& x, uint32_t& y, uint32_t& nz,
-                                         uint32_t& c, uint32_t& v, uint32_t ram, uint32_t tia, uint64_t log) {
+// Runs the wave's lanes in `lanes` until a group of them meets an instruction
+// the block does not run; returns that group (0: the block cannot run where it
+// was loaded, nothing done).  Call it with every lane of the
+// wave in exec.  table: the ROM's predecoded words; rom: the cartridge in HBM
+// (linear schemes); ram, tia: LDS addresses of the lane's RAM and TIA
+// registers; log, xram: its row log and Superchip RAM; ic: instructions run
+// (added to); passes, rounds: of the wave (added to).
+//
+// Groups.  Lanes that stand at one place (HotLane fields po to key equal) run as
+// one group: exec is the group, its place is in scalars.  The other groups wait
+// in a table, one group per lane of v102-v108 (its lanes, then its place), bit k
+// of s[54:55] for table lane k.  A branch whose lanes part puts the lanes that
+// do not take it into the table and goes on with the others; a group that
+// reaches a WSYNC while others wait joins the waiting group at the same place,
+// or waits itself, and the group at the earliest line runs next -- so
+// groups that part in a scanline meet again at the next line's start.  All of
+// it stays in registers: a switch costs about 40 instructions, where leaving
+// the block and forming a group from per-lane state took some 2,000 cycles.
+__device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uint64_t rom, HotLane& H, uint32_t& a,
+                                             uint32_t& x, uint32_t& y, uint32_t& p, uint32_t& nz, uint32_t& c,
+                                             uint32_t& v, uint32_t& ic, uint32_t& passes, uint32_t& rounds,
+                                             uint32_t ram, uint32_t tia, uint64_t log, uint64_t xram) {
     static_assert(kSnapArea == 1696 * 4 && kCountMask == 31 && kFrameEntries == 5280 && kRows == 210 &&
                       kFirstRow == 34 && kSnapBytes == 32,
                   "the block's constants");
     static_assert(R_GRP0 == 10 && R_GRP1 == 11 && R_GRP0_OLD == 16 && R_GRP1_OLD == 17 && R_FLAGS == 23 &&
-                      R_ENABL == 34 && R_ENABL_OLD == 35,
+                      R_ENAM0 == 32 && R_ENABL == 34 && R_ENABL_OLD == 35 && R_VDELBL == 38,
                   "the block's register offsets");
     asm volatile(
-        // --- entry: block base, line-change and row addresses, constants
+        // --- entry: block bases, line-change and row addresses, constants
+        "s_mov_b64 s[44:45], exec\n"
+        "s_mov_b32 s43, m0\n"
+        "s_mov_b64 exec, -1\n"
+        "s_mov_b64 s[54:55], 0\n"
         "s_getpc_b64 s[74:75]\n"
         ".Lpc%=:\n"
-        "s_load_dwordx4 s[76:79], s[70:71], s72\n"
+        "v_and_b32 v122, 8, %[p]\n"
+        "v_cmp_ne_u32 s[50:51], 0, v122\n"         // lanes in decimal mode
         // (the blocks must lie in one 4 GB half: a handler's address is a 32-bit sum)
         "s_add_u32 s88, s74, .Lhu%=-.Lpc%=+0x8000\n"
-        "s_cbranch_scc1 .Lout%=\n"
-        "s_add_u32 s84, s74, .Lhb%=-.Lpc%=\n"
-        "s_add_u32 s88, s74, .Lhu%=-.Lpc%=\n"
-        "s_cmp_eq_u32 s59, 0\n"
-        "s_cselect_b32 s84, s88, s84\n"
+        "s_cbranch_scc1 .Lnone%=\n"
+        "s_add_u32 s46, s74, .Lhb%=-.Lpc%=\n"
+        "s_add_u32 s47, s74, .Lhu%=-.Lpc%=\n"
         "s_add_u32 s85, s74, .Lline%=-.Lpc%=\n"
         "s_add_u32 s64, s74, .Lsnap%=-.Lpc%=\n"
         "s_mov_b32 s65, s75\n"
-        "s_mov_b32 s91, 0\n"
         "s_mov_b32 s67, 0\n"
+        "s_movk_i32 s68, 1696\n"
+        "s_movk_i32 s69, 1696+5280-31\n"
         "s_mov_b32 s98, (3<<25)+1\n"
         "s_mov_b32 s99, (4<<25)+1\n"
+        // --- groups of the lanes in s[48:49]
+        ".Lform%=:\n"
+        "s_ff1_i32_b64 s93, s[48:49]\n"
+        "s_nop 3\n"
+        "v_readlane_b32 s72, %[po], s93\n"
+        "v_readlane_b32 s73, %[acc], s93\n"
+        "v_readlane_b32 s80, %[lines], s93\n"
+        "v_readlane_b32 s82, %[orow], s93\n"
+        "v_readlane_b32 s59, %[key], s93\n"
+        HL_SAME("%[po]", "%[acc]", "s80", "%[lines]", "%[orow]", "%[key]")
+        "s_and_b64 s[52:53], vcc, s[48:49]\n"
+        "s_andn2_b64 s[48:49], s[48:49], s[52:53]\n"
+        "s_cbranch_scc1 .Lforw%=\n"
+        "s_cmp_lg_u64 s[54:55], 0\n"
+        "s_cbranch_scc0 .Lrun%=\n"                 // one group, none waiting
+        ".Lforw%=:\n"
+        HL_PUT
+        "s_mov_b32 s56, 0x7fffffff\n"
+        "s_cmp_lg_u64 s[48:49], 0\n"
+        "s_cbranch_scc1 .Lform%=\n"
+        // --- the next group: the earliest (s56: the last one's time)
+        ".Lpick%=:\n"
+        "v_cmp_eq_u32 vcc, s56, v106\n"
+        "s_and_b64 s[60:61], vcc, s[54:55]\n"
+        "s_cbranch_scc1 .Lgot%=\n"
+        "s_sub_u32 s56, s56, 1\n"                 // (none waits at s56, so none before s56 - 1)
+        "v_cmp_eq_u32 vcc, s56, v106\n"
+        "s_and_b64 s[60:61], vcc, s[54:55]\n"
+        "s_cbranch_scc1 .Lgot%=\n"
+        "s_mov_b64 s[88:89], s[54:55]\n"
+        "s_mov_b32 s56, 0x80000000\n"
+        ".Lscan%=:\n"
+        "s_ff1_i32_b64 s93, s[88:89]\n"
+        "s_bitset0_b64 s[88:89], s93\n"
+        "s_nop 3\n"
+        "v_readlane_b32 s86, v106, s93\n"
+        "s_max_i32 s56, s56, s86\n"
+        "s_cmp_lg_u64 s[88:89], 0\n"
+        "s_cbranch_scc1 .Lscan%=\n"
+        "s_branch .Lpick%=\n"
+        ".Lgot%=:\n"
+        "s_ff1_i32_b64 s93, s[60:61]\n"
+        "s_bitset0_b64 s[54:55], s93\n"
+        "s_nop 3\n"
+        "v_readlane_b32 s72, v104, s93\n"
+        "v_readlane_b32 s52, v102, s93\n"
+        "v_readlane_b32 s53, v103, s93\n"
+        "v_readlane_b32 s73, v105, s93\n"
+        "v_readlane_b32 s80, v106, s93\n"
+        "v_readlane_b32 s82, v107, s93\n"
+        "v_readlane_b32 s59, v108, s93\n"
+        HL_LINES
+        ".Lrun%=:\n"
+        "s_add_u32 s58, s58, 1\n"
+        "s_mov_b64 exec, s[52:53]\n"
+        "s_cmp_eq_u32 s72, -1\n"                   // not run here
+        "s_cbranch_scc1 .Lout%=\n"
+        "s_load_dwordx4 s[76:79], s[70:71], s72\n"
+        "s_cmp_eq_u32 s80, 0\n"                    // at the cap
+        "s_cbranch_scc1 .Lout%=\n"
+        "s_cmp_lg_u64 s[54:55], 0\n"               // stop at the next WSYNC while others wait
+        "s_cselect_b32 s81, -1, 0\n"
+        "s_bitcmp1_b32 s59, 27\n"
+        "s_cselect_b32 s84, s46, s47\n"
         // s83: lines left in the open row's line; -2 (no line's) when none is open
-        // or its entries might not all fit (.Lsnap then leaves the store)
         "s_sub_u32 s83, 287, s82\n"
         "s_cmp_eq_u32 s82, 0\n"
         "s_cselect_b32 s83, -2, s83\n"
-        "s_cmp_gt_u32 s69, 1696+5280-31\n"
-        "s_cselect_b32 s83, -2, s83\n"
         HL_WAIT HL_TGT("s76") HL_JUMP
-        // --- leaving
-        ".Lundo%=:\n"                              // a 2-byte, 3-cycle store was fetched past and counted: take it back
-        "s_sub_u32 s73, s73, (3<<25)+1\n"
-        "s_sub_u32 s72, s72, 8\n"
-        "s_branch .Lout%=\n"
-        ".Lpart%=:\n"                              // the lanes part at the branch
-        "s_sub_u32 s72, s88, 8\n"
-        ".Lout%=:\n"
-        "s_mov_b32 s92, 0\n"
-        "s_branch .Lend%=\n"
+        // --- lanes part at a branch (vcc: taken): the others wait
+        ".Lpart8%=:\n"
+        "s_mov_b32 s94, 3<<25\n"
+        "s_branch .Lpart%=\n"
+        ".Lpart9%=:\n"
+        "s_mov_b32 s94, 4<<25\n"
+        ".Lpart%=:\n"
+        HL_WAIT
+        HL_FOLD("s_add_u32 s86, s86, 1\n")
+        "s_mov_b32 s95, s73\n"
+        "s_mov_b32 s66, s80\n"
+        "s_andn2_b64 s[52:53], exec, vcc\n"
+        "s_mov_b32 s72, s88\n"
+        "s_add_u32 s73, s95, 2<<25\n"
+        "s_cbranch_scc0 .Lpn%=\n"
+        "s_add_u32 s73, s73, 52<<25\n"             // into the next line
+        "s_sub_u32 s80, s80, 1\n"
+        ".Lpn%=:\n"
+        HL_PUT
+        "s_mov_b64 s[52:53], vcc\n"
+        "s_mov_b64 exec, vcc\n"
+        "s_mov_b32 s72, s89\n"
+        "s_mov_b32 s80, s66\n"
+        "s_mov_b32 s81, -1\n"
+        "s_add_u32 s73, s95, s94\n"
+        "s_cbranch_scc0 .Lpt%=\n"
+        "s_add_u32 s73, s73, 52<<25\n"
+        "s_sub_u32 s80, s80, 1\n"
+        "s_cmp_eq_u32 s80, 0\n"
+        "s_cbranch_scc1 .Lout%=\n"
+        ".Lpt%=:\n"
+        "s_add_u32 s58, s58, 1\n"
+        "s_mov_b64 s[76:77], s[60:61]\n"
+        "s_mov_b64 s[78:79], s[62:63]\n" HL_TGT("s76") HL_JUMP
+        // --- a WSYNC that is not simply the next line (s80 counted down, not yet ACC)
         ".Lsync%=:\n"
+        HL_WAIT
         "s_add_u32 s87, s73, 2<<25\n"
         "s_cbranch_scc1 .Lsync2%=\n"
         "s_and_b32 s73, s73, 0x1ffffff\n"
         "s_add_u32 s73, s73, (52<<25)+1\n"
-        "s_mov_b32 s92, 1\n"
-        "s_branch .Lend%=\n"
-        ".Lsync2%=:\n"
+        "s_cmp_eq_u32 s80, 0\n"
+        "s_cbranch_scc1 .Lout%=\n"                 // the cap
+        // others wait: join the one at this place, or wait too
+        HL_FOLD("")
+        "s_mov_b64 exec, -1\n"
+        HL_TIME HL_SAME("v104", "v105", "s86", "v106", "v107", "v108")
+        "s_and_b64 s[60:61], vcc, s[54:55]\n"
+        "s_cbranch_scc1 .Ljoin%=\n"
+        HL_PUT
+        "s_branch .Lpick%=\n"
+        ".Ljoin%=:\n"
+        "s_ff1_i32_b64 s93, s[60:61]\n"
+        "s_nop 3\n"
+        "v_readlane_b32 s86, v102, s93\n"
+        "v_readlane_b32 s87, v103, s93\n"
+        "s_mov_b32 m0, s93\n"
+        "s_or_b32 s86, s86, s52\n"
+        "s_or_b32 s87, s87, s53\n"
+        "v_writelane_b32 v102, s86, m0\n"
+        "v_writelane_b32 v103, s87, m0\n"
+        "s_branch .Lpick%=\n"
+        ".Lsync2%=:\n"                             // a write at the line's end stalls a line longer
         "s_add_u32 s80, s80, 1\n"
         "s_sub_u32 s72, s72, 8\n"
         "s_branch .Lout%=\n"
+        // --- leaving: every group's place back to its lanes
+        ".Lnone%=:\n"
+        "s_mov_b64 s[48:49], 0\n"
+        "s_branch .Lend%=\n"
+        ".Lundo%=:\n"                              // a 2-byte, 3-cycle store was fetched past and counted: take it back
+        "s_sub_u32 s73, s73, (3<<25)+1\n"
+        "s_sub_u32 s72, s72, 8\n"
+        ".Lout%=:\n"
+        HL_WAIT
+        HL_FOLD("")
+        HL_TOLANES
+        "s_mov_b64 s[48:49], s[52:53]\n"
+        ".Lflush%=:\n"
+        "s_cmp_eq_u64 s[54:55], 0\n"
+        "s_cbranch_scc1 .Lend%=\n"
+        "s_ff1_i32_b64 s93, s[54:55]\n"
+        "s_bitset0_b64 s[54:55], s93\n"
+        "s_nop 3\n"
+        "v_readlane_b32 s52, v102, s93\n"
+        "v_readlane_b32 s53, v103, s93\n"
+        "v_readlane_b32 s72, v104, s93\n"
+        "v_readlane_b32 s73, v105, s93\n"
+        "v_readlane_b32 s80, v106, s93\n"
+        "v_readlane_b32 s82, v107, s93\n"
+        "v_readlane_b32 s59, v108, s93\n"
+        "s_mov_b64 exec, s[52:53]\n"
+        HL_LINES
+        HL_TOLANES
+        "s_branch .Lflush%=\n"
         // --- line change without a WSYNC: ACC's cycle has wrapped past the bias
         ".Lline%=:\n"
         "s_add_u32 s73, s73, 52<<25\n"
@@ -475,10 +758,10 @@ __device__ __forceinline__ void hot_loop(HotRegs& H, uint64_t table, uint32_t ba
         "s_cbranch_scc1 .Lout%=\n"
         HL_WAIT HL_TGT("s76") HL_JUMP
         // --- a logged TIA store at cycle s88 - 52 of its line, which is not the open row's
-        // (s87 = -1: past the line's end): snapshots of the rows before it, and its own
+        // (s88 < 52: past the line's end): snapshots of the rows before it, and its own
         // when it lands in the visible part.  SCC = 0 on return: its entry goes into the open row.
         ".Lsnap%=:\n"
-        "s_cmp_eq_u32 s87, -1\n"
+        "s_cmp_lt_u32 s88, 52\n"
         "s_cbranch_scc1 .Lundo%=\n"
         "s_sub_u32 s89, 287, s80\n"                // the line's row + 1
         "s_cmp_ge_u32 s88, 75\n"                   // visible: 3 (cycle + 1) >= 68
@@ -492,19 +775,20 @@ __device__ __forceinline__ void hot_loop(HotRegs& H, uint64_t table, uint32_t ba
         "ds_read2_b32 v[116:117], %[tia] offset0:4 offset1:5\n"
         "ds_read2_b32 v[118:119], %[tia] offset0:6 offset1:7\n"
         "s_lshl_b32 s66, s82, 5\n"                 // the open row's end
-        "s_cmp_eq_u32 s90, s69\n"                  // the open row's entry count (none: nothing to store)
+        "v_sub_u32 v111, v100, %[log0]\n"        // entries so far: the open row's count, the new row's first
+        "v_lshrrev_b32 v111, 2, v111\n"
         "v_lshl_add_u64 v[120:121], s[66:67], 0, %[log]\n"   // (its shift goes to 4)
+        "v_sub_u32 v123, v111, %[obase]\n"
+        "v_mov_b32 %[obase], v111\n"
+        "v_subrev_u32 v111, s68, v111\n"
+        "s_cmp_eq_u32 s82, 0\n"
         "s_cbranch_scc1 .Lcnt%=\n"
-        "s_sub_u32 s69, s90, s69\n"
-        "v_mov_b32 v123, s69\n"
         "global_store_byte v[120:121], v123, off offset:-17\n"
-        "s_mov_b32 s69, s90\n"
         ".Lcnt%=:\n"
-        "s_sub_u32 s87, s69, 1696\n"
         HL_WAIT
         "v_and_b32 v115, 0xffffff, v115\n"
         "v_and_b32 v119, 0xffff0000, v119\n"
-        "v_or_b32 v119, s87, v119\n"
+        "v_or_b32 v119, v111, v119\n"
         ".Lsrow%=:\n"
         "global_store_dwordx4 v[120:121], v[112:115], off\n"
         "global_store_dwordx4 v[120:121], v[116:119], off offset:16\n"
@@ -515,32 +799,40 @@ __device__ __forceinline__ void hot_loop(HotRegs& H, uint64_t table, uint32_t ba
         "s_cbranch_scc1 .Lsrow%=\n"
         "s_sub_u32 s83, 287, s82\n"
         ".Lopen%=:\n"
-        "s_cmp_gt_u32 s69, 1696+5280-31\n"         // a row's entries might not fit
-        "s_cbranch_scc1 .Lundo%=\n"
-        "v_lshl_add_u64 v[120:121], s[90:91], 2, %[log]\n"
+        "v_cmp_lt_u32 vcc, s69, %[obase]\n"        // a row's entries might not fit
         "s_sub_u32 s95, s89, 1\n"                  // not in the visible part of a frame row: no entry
         "s_cmp_ge_u32 s95, 210\n"
         "s_cselect_b32 s95, 1, s94\n"
+        "s_mul_i32 s87, s88, 3\n"
+        "s_cbranch_vccnz .Lundo%=\n"
         "s_cmp_lg_u32 s95, 0\n"
         "s_setpc_b64 s[96:97]\n"
         // --- handlers
         ".p2align 7\n"
         ".Lhb%=:\n"
-        HL_BLOCK(".Lhb", HL_TIA_LOG, HL_TIAX_LOG, HL_GRP0_LOG, HL_GRP1_LOG, HL_XY_LOG)
+        HL_BLOCK(".Lhb", HL_TIA_LOG, HL_TIAX_LOG, HL_GRP0_LOG, HL_GRP1_LOG, HL_XY_LOG, HL_FLAG_LOG)
         ".p2align 7\n"
         ".Lhu%=:\n"
-        HL_BLOCK(".Lhu", HL_TIA_NOLOG, HL_TIAX_NOLOG, HL_GRP0_NOLOG, HL_GRP1_NOLOG, HL_XY_NOLOG)
+        HL_BLOCK(".Lhu", HL_TIA_NOLOG, HL_TIAX_NOLOG, HL_GRP0_NOLOG, HL_GRP1_NOLOG, HL_XY_NOLOG, HL_FLAG_NOLOG)
         ".Lend%=:\n"
-        HL_WAIT
-        : "+{s72}"(H.po), "+{s73}"(H.acc), "+{s80}"(H.lines), "+{s82}"(H.orow), "+{s90}"(H.pos), "+{s69}"(H.obase),
-          "+{s93}"(H.pchi), "={s92}"(H.why), [a] "+v"(a), [x] "+v"(x), [y] "+v"(y), [nz] "+v"(nz), [c] "+v"(c),
-          [v] "+v"(v)
-        : "{s[70:71]}"(table), "{s68}"(bankpo), "{s81}"(partial), "{s59}"(logon), [ram] "v"(ram), [tia] "v"(tia),
-          [log] "v"(log)
-        : "memory", "scc", "vcc", "s60", "s61", "s62", "s63", "s64", "s65", "s66", "s67", "s74", "s75", "s76", "s77",
-          "s78", "s79", "s83", "s84", "s85", "s86", "s87", "s88", "s89", "s91", "s94", "s95", "s96", "s97", "s98",
-          "s99", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123",
-          "v124", "v125", "v126");
+        "s_mov_b64 exec, s[44:45]\n"
+        "s_mov_b32 m0, s43\n"
+        "v_mov_b32 v122, 8\n"
+        "v_and_b32 %[p], ~8, %[p]\n"
+        "v_cndmask_b32 v122, 0, v122, s[50:51]\n"
+        "v_or_b32 %[p], %[p], v122\n"
+        : "+{s[48:49]}"(lanes), "+{s57}"(passes), "+{s58}"(rounds), [po] "+v"(H.po), [acc] "+v"(H.acc),
+          [lines] "+v"(H.lines), [orow] "+v"(H.orow), "+{v[100:101]}"(H.lp), [obase] "+v"(H.obase), [a] "+v"(a),
+          [x] "+v"(x), [y] "+v"(y), [p] "+v"(p), [nz] "+v"(nz), [c] "+v"(c), [v] "+v"(v), [ic] "+v"(ic)
+        : "{s[70:71]}"(table), "{s[40:41]}"(rom), [key] "v"(H.key), [ram] "v"(ram), [tia] "v"(tia), [log] "v"(log),
+          [log0] "v"((uint32_t)log), [xram] "v"(xram)
+        : "memory", "scc", "vcc", "s43", "s44", "s45", "s46", "s47", "s50", "s51", "s52", "s53", "s54", "s55", "s56",
+          "s59", "s60", "s61", "s62", "s63", "s64", "s65", "s66", "s67", "s68", "s69", "s72", "s73", "s74", "s75",
+          "s76", "s77", "s78", "s79", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89", "s93",
+          "s94", "s95", "s96", "s97", "s98", "s99", "v102", "v103", "v104", "v105", "v106", "v107", "v108", "v111", "v112",
+          "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123", "v124", "v125",
+          "v126");
+    return lanes;
 }
 
 }  // namespace vcs

@@ -981,12 +981,9 @@ __device__ __forceinline__ int32_t rfl(int32_t v) { return __builtin_amdgcn_read
 // instructions this path does not cover (indirect modes, JMP (ind), RTI, BRK,
 // indexed accesses outside RAM/cartridge), which the per-lane path executes.
 struct Fast {
-    uint32_t pc, bank, cyc, cap, orow, ocnt, obase;
+    uint32_t pc, bank, cyc, orow;
     int32_t fl;
     uint32_t logon;
-    uint32_t partial;   // 1: other running lanes are elsewhere; stop at the next line start
-    uint32_t stop;
-    uint32_t lim;       // cap, or 0 once the run must stop: one compare ends the run for either
 };
 
 __device__ __forceinline__ bool all_lanes(bool p) { return __builtin_amdgcn_ballot_w64(!p) == 0; }
@@ -1079,7 +1076,6 @@ __device__ __forceinline__ uint32_t pre_op(uint32_t q) {
     const uint32_t slot = pre_slot(q);
     return slot == HOT_REAL ? (q & 0x7F) | ((q >> 8) & 0x80) : kHotOps.op[slot];
 }
-__device__ __forceinline__ uint32_t pre_class(uint32_t q) { return pre_slot(q) == HOT_REAL ? SC_EXIT : q & 0x7F; }
 
 // Write of per-lane value v to TIA register class `sc` (SC_TIA/S/G | code) at
 // scalar cycle t, with its row-log entry.  The scalar path takes the colour,
@@ -1088,11 +1084,8 @@ __device__ __forceinline__ uint32_t pre_class(uint32_t q) { return pre_slot(q) =
 // (logged as the new flags byte); motion, HMOVE, RESMP and CXCLR go to the
 // per-lane path.  A GRP0 / GRP1 entry also stands for the copy to the delayed
 // registers (the other player's graphics; with GRP1, ENABL), which the
-// renderer repeats from its own state.  Returns 0, before changing anything,
-// when the row's entries are full (the per-lane path then records the error).
-// PLAIN: `sc` is known to be SC_TIA | code (a register stored as is); the
-// code may then differ between lanes.
-template <bool PLAIN = false>
+// renderer repeats from its own state.  Returns 0, before changing a register,
+// when a lane's row is full (the per-lane path then records the error).
 __device__ __forceinline__ uint32_t fast_tia_code(Cpu& c, const Wave& W, Fast& F, uint32_t sc, uint32_t v,
                                                   uint32_t t) {
     const uint32_t ln = (t + 1) / 76;
@@ -1100,7 +1093,7 @@ __device__ __forceinline__ uint32_t fast_tia_code(Cpu& c, const Wave& W, Fast& F
     uint8_t* R = W.tia + c.tia_off;
     uint32_t code = sc & 0x1F;
     uint32_t v0 = v, full = 0;
-    if (!PLAIN && sc >= SC_TIAS && sc < SC_TIAG) {
+    if (sc >= SC_TIAS && sc < SC_TIAG) {
         if (code == R_P0X || code == R_P1X) {
             v0 = h < 68 ? 3u : (h - 68 + 5) % 160;
         } else if (code >= R_M0X && code <= R_BLX) {
@@ -1122,14 +1115,12 @@ __device__ __forceinline__ uint32_t fast_tia_code(Cpu& c, const Wave& W, Fast& F
         int32_t target = row - 1 + vis;
         target = target > kRows - 1 ? kRows - 1 : target;
         if ((int32_t)F.orow <= target) {
-            if (F.orow > 0) {
-                if (F.ocnt) c.log[(F.orow - 1) * kSnapBytes + 15] = (uint8_t)F.ocnt;
-            }
-            F.obase += F.ocnt;       // the new rows' entries start after the open row's
-            F.ocnt = 0;
+            if (F.orow > 0) c.log[(F.orow - 1) * kSnapBytes + 15] = (uint8_t)c.open_cnt;
+            c.open_base += c.open_cnt;   // the new rows' entries start after the open row's
+            c.open_cnt = 0;
             const uint32_t* src = reinterpret_cast<const uint32_t*>(R);
             const uint4 snap0 = make_uint4(src[0], src[1], src[2], src[3] & 0x00FFFFFFu);
-            const uint4 snap1 = make_uint4(src[4], src[5], src[6], (src[7] & 0xFFFF0000u) | F.obase);
+            const uint4 snap1 = make_uint4(src[4], src[5], src[6], (src[7] & 0xFFFF0000u) | c.open_base);
             do {    // F.orow holds the open row + 1 (0 = none)
                 uint4* d = reinterpret_cast<uint4*>(c.log + F.orow * kSnapBytes);
                 d[0] = snap0;
@@ -1140,14 +1131,14 @@ __device__ __forceinline__ uint32_t fast_tia_code(Cpu& c, const Wave& W, Fast& F
         if (vis) {
             if ((uint32_t)row < (uint32_t)kRows) {
                 // the row is the open one here; past the guard the per-lane path records the error
-                if (F.ocnt >= kCountMask || F.obase + F.ocnt >= (uint32_t)kFrameEntries) return 0;
-                *reinterpret_cast<uint32_t*>(c.log + kSnapArea + 4 * (F.obase + F.ocnt)) =
+                if (!all_lanes(c.open_cnt < kCountMask && c.open_base + c.open_cnt < (uint32_t)kFrameEntries)) return 0;
+                *reinterpret_cast<uint32_t*>(c.log + kSnapArea + 4 * (c.open_base + c.open_cnt)) =
                     (h - 68) | (code << 8) | (v0 << 16);
-                F.ocnt++;
+                c.open_cnt++;
             }
         }
     }
-    if (!PLAIN && sc >= SC_TIAG) {
+    if (sc >= SC_TIAG) {
         if (code == R_GRP0) {
             R[R_GRP1_OLD] = R[R_GRP1];
         } else {
@@ -1309,9 +1300,6 @@ __device__ __forceinline__ uint32_t store_value(const Cpu& c) {
 __device__ __forceinline__ uint32_t fast_finish(Fast& F, uint32_t next, uint32_t t, uint32_t wsync) {
     F.pc = next;
     F.cyc = wsync ? 76 * (t / 76 + 1) : t + 1;
-    const uint32_t s = wsync & F.partial;
-    F.stop = s;
-    F.lim &= s - 1u;
     return FS_NEXT;
 }
 
@@ -1545,329 +1533,44 @@ __device__ __forceinline__ uint32_t fop(Cpu& c, const Wave& W, Fast& F, uint32_t
 #define VCS_FAST_16(o) VCS_FAST_4(o) VCS_FAST_4((o) + 4) VCS_FAST_4((o) + 8) VCS_FAST_4((o) + 12)
 #define VCS_FAST_64(o) VCS_FAST_16(o) VCS_FAST_16((o) + 16) VCS_FAST_16((o) + 32) VCS_FAST_16((o) + 48)
 
-// Runs instructions for the lanes in exec (which agree on the control
-// state) until they part, a frame ends, or an instruction this path leaves
-// to the per-lane path comes up; when other running lanes of the wave are
-// elsewhere (`partial`), also at the first WSYNC, so that lanes that took
-// different paths through a scanline meet again at the next line start.  On
-// return `c` holds every lane's state; `ended`/`end_t` mark lanes whose frame
-// ended.  Returns false when it made no progress (the per-lane path must then
-// execute the instruction in the same iteration).
+// Runs the instruction at the place of the lanes in exec (one group of the hot
+// loop, at a place inside the cartridge window) through the full dispatch.
+// Returns false when the per-lane path must execute it.
 template <bool TRACK>
-__device__ __forceinline__ bool run_fast(Cpu& c, const Wave& W, PreWords pre, bool& ended, uint32_t& end_t,
-                                         uint32_t partial) {
+__device__ __forceinline__ bool run_cold(Cpu& c, const Wave& W) {
     Fast F;
-    F.partial = partial;
-    F.stop = 0;
     F.pc = rfl(c.pc);
     F.bank = rfl(c.bank);
     F.cyc = rfl(c.cyc);
-    F.cap = rfl(c.cap);
-    F.lim = F.cap;
     F.fl = rfl(c.fl);
     F.orow = (uint32_t)(rfl(c.open_row) + 1);
-    F.ocnt = rfl(c.open_cnt);
-    F.obase = rfl(c.open_base);
     F.logon = rfl(c.log != nullptr ? 1u : 0u);
-    uint32_t done_n = 0;       // instructions executed on this path
     uint32_t st = FS_EXIT;
-    uint32_t capped = 0;
-    const uint64_t pre_addr = (uint64_t)(uintptr_t)pre;
-    const uint64_t table = (uint64_t)rfl((uint32_t)pre_addr) | ((uint64_t)rfl((uint32_t)(pre_addr >> 32)) << 32);
-    // The hot loop runs until an instruction it does not cover (or the
-    // group's end); that one goes through the full dispatch, then the hot
-    // loop resumes.  In decimal mode every instruction takes the dispatch.
-    for (;;) {
-        if (F.cyc >= F.lim) {      // the frame's last cycle, or a stop
-            capped = F.lim != 0;
-            break;
-        }
-        if ((F.pc & 0x1FFF) - 0x1000u > 0xFFDu) {   // outside the cartridge, or too close to its end
-            st = FS_EXIT;
-            break;
-        }
-        if ((F.pc & 0xFFF) <= 0xFFC && __builtin_amdgcn_ballot_w64((c.p & FD) != 0) == 0) {
-            const uint32_t line = F.cyc / 76, line_cyc = 76 * line;
-            const uint32_t lines = 320u + (uint32_t)F.fl - line;
-            HotRegs H;
-            H.po = ((F.bank << 12) | (F.pc & 0xFFF)) << 2;
-            H.acc = (kAccBias + (F.cyc - line_cyc)) << kAccShift;
-            H.lines = lines;
-            H.orow = F.orow;
-            H.pos = F.obase + F.ocnt + kSnapArea / 4;
-            H.obase = F.obase + kSnapArea / 4;
-            H.pchi = F.pc & 0xF000;
-            uint32_t nzv = ((c.p & FN) << 1) | (((c.p >> 1) & 1) ^ 1), cf = c.p & FC, vf = c.p << 1;
-            hot_loop(H, table, F.bank << 14, 0u - F.partial, F.logon, c.a, c.x, c.y, nzv, cf, vf, W.ram_lds + c.ram_off,
-                     W.tia_lds + c.tia_off, (uint64_t)c.log);
-            c.p = (c.p & ~(FN | FV | FZ | FC)) | cf | ((vf >> 1) & FV) | ((nzv & 0xFF) == 0 ? FZ : 0u) |
-                  ((nzv & 0x180) ? FN : 0u);
-            F.pc = H.pchi | ((H.po >> 2) & 0xFFF);
-            F.cyc = line_cyc + 76 * (lines - H.lines) + (H.acc >> kAccShift) - kAccBias;
-            F.orow = H.orow;
-            F.obase = H.obase - kSnapArea / 4;
-            F.ocnt = H.pos - H.obase;
-            const uint32_t ran = H.acc & kAccCount;
-            done_n += ran;
-            if (ran) st = FS_NEXT;
-            if (H.why == HOT_EXIT_LINE && F.partial) break;
-            if (F.cyc >= F.lim) {
-                capped = 1;
-                break;
-            }
-        }
-        const uint32_t q = pre[(F.bank << 12) | (F.pc & 0xFFF)];
-        const uint32_t op = pre_op(q), b1 = (q >> 16) & 0xFF, b2 = q >> 24;
-        switch (op) {
-            VCS_FAST_64(0x00)
-            VCS_FAST_64(0x40)
-            VCS_FAST_64(0x80)
-            VCS_FAST_64(0xC0)
-        }
-        if (st != FS_NEXT) break;
-        ++done_n;
+    const uint32_t q = rfl(W.pre[(F.bank << 12) | (F.pc & 0xFFF)]);
+    const uint32_t op = pre_op(q), b1 = (q >> 16) & 0xFF, b2 = q >> 24;
+    switch (op) {
+        VCS_FAST_64(0x00)
+        VCS_FAST_64(0x40)
+        VCS_FAST_64(0x80)
+        VCS_FAST_64(0xC0)
     }
-    if (capped) {
-        c.err |= ERR_FRAME_CAP;
-        ended = true;
-        end_t = F.cyc - 1;
-    }
-    if (st == FS_LANE) ++done_n;
-    if (st != FS_LANE) {                      // pc and cycle are still common to all lanes
+    if (st == FS_EXIT) return false;
+    if (st == FS_NEXT) {                      // pc and cycle are still common to all lanes
         c.pc = F.pc;
         c.cyc = F.cyc;
     }
-    c.icount += done_n;
-    c.ucount += done_n;
+    c.icount++;
+    c.ucount++;
     c.bank = F.bank;
     c.open_row = (int32_t)F.orow - 1;
-    c.open_cnt = F.ocnt;
-    c.open_base = F.obase;
-    return done_n > 0 || capped;
+    return true;
 }
 #undef VCS_FAST_64
 #undef VCS_FAST_16
 #undef VCS_FAST_4
 #undef VCS_FAST_CASE
 
-// ------------------------------------------------- two-bank group runs
-//
-// On bank-switched cartridges, lanes can stand at the same address and cycle
-// in two different banks.  Where the instruction there has the same opcode
-// in both banks (operands may differ), the lanes still run it as one group:
-// the predecoded words of both banks come from two scalar loads, dispatch,
-// store class and timing stay scalar, and each lane takes its bank's
-// operand bytes.  Covered: implied and accumulator instructions, immediates,
-// zero-page reads of RAM, zero-page stores whose target class agrees (RAM,
-// WSYNC, a TIA register stored as is, or one with no emulated effect),
-// relative branches and absolute jumps (the lanes part where their targets
-// differ), and absolute reads of the cartridge at one address in both banks
-// (a bank hotspot among them: the run ends after it).  Anything else ends
-// the run before executing it.
-
-// One instruction with opcode OP; qa / qb: its predecoded word in bank A /
-// bank B; in_b: the lane is in bank B.
-template <int OP>
-__device__ __forceinline__ uint32_t mop(Cpu& c, const Wave& W, Fast& F, bool in_b, uint32_t qa, uint32_t qb) {
-    constexpr OpInfo I = decode(OP);
-    constexpr int MD = I.md, MN = I.mn;
-    constexpr uint32_t N = (uint32_t)I.cyc;
-    const uint32_t next = (F.pc + (uint32_t)op_len(MD)) & 0xFFFF;
-    const uint32_t a1 = (qa >> 16) & 0xFF, a2 = qa >> 24;           // bank A's operand bytes
-    const uint32_t x1 = (qb >> 16) & 0xFF, x2 = qb >> 24;           // bank B's
-    const uint32_t b1 = in_b ? x1 : a1;                              // the lane's
-    if constexpr (MN == ILL || MN == BRK || MN == RTI || MN >= SLO || (MN == NOP && MD != IMP)) {
-        return FS_EXIT;
-    } else if constexpr (MD == IMP || MD == ACC) {
-        return fop<OP, false>(c, W, F, 0, 0);   // no operand bytes; memory only through the stack
-    } else if constexpr (MD == IMM) {
-        uint32_t dm = 0;
-        if constexpr (MN == ADC || MN == SBC) {
-            dm = dec_mode(c);
-            if (dm == 2) return FS_EXIT;
-        }
-        fast_alu(c, MN, b1, dm);
-        F.pc = next;
-        F.cyc += N;
-        return FS_NEXT;
-    } else if constexpr (MD == ZP && read_mn(MN)) {
-        if (!(a1 & x1 & 0x80)) return FS_EXIT;    // RAM in both banks' operands
-        uint32_t dm = 0;
-        if constexpr (MN == ADC || MN == SBC) {
-            dm = dec_mode(c);
-            if (dm == 2) return FS_EXIT;
-        }
-        fast_alu(c, MN, W.ram[c.ram_off + (b1 & 0x7F)], dm);
-        F.pc = next;
-        F.cyc += N;
-        return FS_NEXT;
-    } else if constexpr (MD == ZP && store_mn(MN)) {
-        const uint32_t auxa = pre_class(qa), auxb = pre_class(qb);      // store classes
-        const uint32_t cat = auxa < SC_TIA ? auxa : (auxa & 0xE0);
-        if (cat != (auxb < SC_TIA ? auxb : (auxb & 0xE0))) return FS_EXIT;
-        const uint32_t t = F.cyc + N - 1;
-        const uint32_t v = store_value<MN>(c);
-        if (cat == SC_RAM) {
-            W.ram[c.ram_off + (b1 & 0x7F)] = (uint8_t)v;
-        } else if (cat == SC_TIA) {
-            if (!fast_tia_code<true>(c, W, F, in_b ? auxb : auxa, v & 0xFF, t)) return FS_EXIT;
-        } else if (cat == SC_WSYNC) {
-            return fast_finish(F, next, t, 1);
-        } else if (cat != SC_IGNORE) {
-            return FS_EXIT;
-        }
-        F.pc = next;
-        F.cyc += N;
-        return FS_NEXT;
-    } else if constexpr (MD == REL) {
-        bool taken;
-        if constexpr (MN == BPL) taken = !(c.p & FN);
-        else if constexpr (MN == BMI) taken = (c.p & FN) != 0;
-        else if constexpr (MN == BVC) taken = !(c.p & FV);
-        else if constexpr (MN == BVS) taken = (c.p & FV) != 0;
-        else if constexpr (MN == BCC) taken = !(c.p & FC);
-        else if constexpr (MN == BCS) taken = (c.p & FC) != 0;
-        else if constexpr (MN == BNE) taken = !(c.p & FZ);
-        else taken = (c.p & FZ) != 0;
-        const uint32_t tgt = (next + (uint32_t)sext8(b1)) & 0xFFFF;
-        const uint32_t npc = taken ? tgt : next;
-        const uint32_t ncyc = F.cyc + N + (taken ? 1 + (((tgt ^ next) & 0xFF00) ? 1 : 0) : 0);
-        const uint32_t p0 = rfl(npc), c0 = rfl(ncyc);
-        if (all_lanes(npc == p0 && ncyc == c0)) {
-            F.pc = p0;
-            F.cyc = c0;
-            return FS_NEXT;
-        }
-        c.pc = npc;                           // the lanes part here
-        c.cyc = ncyc;
-        return FS_LANE;
-    } else if constexpr (MN == JMP && MD == ABS) {
-        const uint32_t ta = a1 | (a2 << 8), tb = x1 | (x2 << 8);
-        if (ta == tb) {
-            F.pc = ta;
-            F.cyc += N;
-            return FS_NEXT;
-        }
-        c.pc = in_b ? tb : ta;
-        c.cyc = F.cyc + N;
-        return FS_LANE;
-    } else if constexpr (MD == ABS && read_mn(MN)) {
-        const uint32_t a = (a1 | (a2 << 8)) & 0x1FFF;
-        if (a1 != x1 || a2 != x2 || !(a & 0x1000) || cm_sc(W)) return FS_EXIT;
-        uint32_t dm = 0;
-        if constexpr (MN == ADC || MN == SBC) {
-            dm = dec_mode(c);
-            if (dm == 2) return FS_EXIT;
-        }
-        // each lane reads its own bank, after the access's bank switch
-        c.bank = hotspot(W, c.bank, a);
-        fast_alu(c, MN, W.rom[rom_off(W, c.bank, a)], dm);
-        F.pc = next;
-        F.cyc += N;
-        F.stop = 1;                           // the banks may have changed: regroup
-        return FS_NEXT;
-    } else {
-        return FS_EXIT;
-    }
-}
-
-#define VCS_MB_CASE(o) \
-    case (o): st = mop<(o)>(c, W, F, in_b, qa, qb); break;
-#define VCS_MB_4(o) VCS_MB_CASE(o) VCS_MB_CASE((o) + 1) VCS_MB_CASE((o) + 2) VCS_MB_CASE((o) + 3)
-#define VCS_MB_16(o) VCS_MB_4(o) VCS_MB_4((o) + 4) VCS_MB_4((o) + 8) VCS_MB_4((o) + 12)
-#define VCS_MB_64(o) VCS_MB_16(o) VCS_MB_16((o) + 16) VCS_MB_16((o) + 32) VCS_MB_16((o) + 48)
-
-// Runs the lanes in exec (same address, cycle, frame line and row-log
-// position; each in bank `ba` or `bb` of a linearly mapped cartridge, both
-// present) while the opcode agrees and mop covers it.  Same contract as
-// run_fast; `in_b`: the lane is in bank bb.
-__device__ __forceinline__ bool run_mb(Cpu& c, const Wave& W, PreWords pre, bool& ended, uint32_t& end_t,
-                                       uint32_t partial, uint32_t ba, uint32_t bb, bool in_b) {
-    Fast F;
-    F.partial = partial;
-    F.stop = 0;
-    F.pc = rfl(c.pc);
-    F.bank = ba;
-    F.cyc = rfl(c.cyc);
-    F.cap = rfl(c.cap);
-    F.lim = F.cap;
-    F.fl = rfl(c.fl);
-    F.orow = (uint32_t)(rfl(c.open_row) + 1);
-    F.ocnt = rfl(c.open_cnt);
-    F.obase = rfl(c.open_base);
-    F.logon = rfl(c.log != nullptr ? 1u : 0u);
-    uint32_t done_n = 0;
-    uint32_t st = FS_EXIT;
-    uint32_t capped = 0;
-    for (;;) {
-        if (F.cyc >= F.cap) {
-            capped = 1;
-            break;
-        }
-        if ((F.pc & 0x1FFF) - 0x1000u > 0xFFDu) {
-            st = FS_EXIT;
-            break;
-        }
-        const uint32_t qa = pre[(ba << 12) | (F.pc & 0xFFF)];
-        const uint32_t qb = pre[(bb << 12) | (F.pc & 0xFFF)];
-        const uint32_t op = pre_op(qa);
-        if (pre_op(qb) != op) {
-            st = FS_EXIT;
-            break;
-        }
-        switch (op) {
-            VCS_MB_64(0x00)
-            VCS_MB_64(0x40)
-            VCS_MB_64(0x80)
-            VCS_MB_64(0xC0)
-        }
-        if (st != FS_NEXT) break;
-        ++done_n;
-        if (F.stop) break;
-    }
-    if (capped) {
-        c.err |= ERR_FRAME_CAP;
-        ended = true;
-        end_t = F.cyc - 1;
-    }
-    if (st == FS_LANE) ++done_n;
-    if (st != FS_LANE) {
-        c.pc = F.pc;
-        c.cyc = F.cyc;
-    }
-    c.icount += done_n;
-    c.ucount += done_n;
-    c.open_row = (int32_t)F.orow - 1;
-    c.open_cnt = F.ocnt;
-    c.open_base = F.obase;
-    return done_n > 0 || capped;
-}
-#undef VCS_MB_64
-#undef VCS_MB_16
-#undef VCS_MB_4
-#undef VCS_MB_CASE
-
 __device__ __forceinline__ uint32_t bcd_value(uint32_t b) { return 10 * (b >> 4) + (b & 15); }
-
-// Minimum of v over the 64 lanes (call with every lane active): DPP swaps
-// within quads, 8- and 16-lane mirrors, then row broadcasts; lane 63 ends up
-// with the minimum.
-__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
-    // the old value of a lane a step does not write is all ones (min's identity),
-    // so each step folds into one DPP min
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x141, 0xF, 0xF, false));  // row_half_mirror
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x140, 0xF, 0xF, false));  // row_mirror
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x142, 0xA, 0xF, false));  // row_bcast:15
-    v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x143, 0xC, 0xF, false));  // row_bcast:31
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
-}
-
-// Lanes whose next instruction starts within this many cycles of the wave's
-// earliest lane run together; the others wait.  Lanes of one ROM then meet
-// again at every WSYNC line start and share one dispatch pass per instruction.
-constexpr uint32_t kSchedWindow = 6;
 
 // Next tile of a persistent launch (lane 0 takes it, the wave shares it).
 __device__ __forceinline__ uint32_t take_tile(uint32_t* queue) {
@@ -2027,61 +1730,59 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
             }
         }
 
+        const uint64_t pre_addr = (uint64_t)W.pre, rom_addr = (uint64_t)(A.roms + (size_t)rom_id * kRomSlot);
+        const uint64_t table = (uint64_t)rfl((uint32_t)pre_addr) | ((uint64_t)rfl((uint32_t)(pre_addr >> 32)) << 32);
+        const uint64_t rom_hbm = (uint64_t)rfl((uint32_t)rom_addr) | ((uint64_t)rfl((uint32_t)(rom_addr >> 32)) << 32);
         // ---------------------------------------------------------- main loop
         while (__any(active)) {
             uint32_t op = 0, b1 = 0, b2 = 0;
             bool want = false, ended = false;
             uint32_t end_t = 0;
-            // Scalar mode for the group of running lanes at exactly the place
-            // of the earliest one (the whole wave when all lanes agree).
-            bool uni = false;
-            ++rounds;
-            const uint32_t tmin = wave_min(active ? c.cyc : 0xFFFFFFFFu);
-            const int lead = (int)__builtin_ctzll(__builtin_amdgcn_ballot_w64(active && c.cyc == tmin));
-            uint32_t ran = 0;          // instructions the group ran on the scalar path
+            // The hot loop runs every group of lanes as far as it can, to the
+            // first one at an instruction it does not run (`in`).
+            const bool hot = active && (c.pc & 0x1000) && (c.pc & 0xFFF) <= 0xFFC && c.cyc < c.cap;
+            const uint32_t line = c.cyc / 76;
+            HotLane H;
+            H.po = hot ? ((c.bank << 12) | (c.pc & 0xFFF)) << 2 : kHotNone;
+            H.acc = (kAccBias + (c.cyc - 76 * line)) << kAccShift;
+            H.lines = 320u + (uint32_t)c.fl - line;
+            H.orow = (uint32_t)(c.open_row + 1);
+            H.obase = c.open_base + kSnapArea / 4;
+            H.lp = (uint64_t)c.log + 4 * (H.obase + c.open_cnt);
+            H.key = ((c.pc >> 12) << 28) | (c.log ? kHotLogged : 0u) | ((uint32_t)c.fl & (kHotLogged - 1));
+            uint32_t nzv = ((c.p & FN) << 1) | (((c.p >> 1) & 1) ^ 1), cf = c.p & FC, vf = c.p << 1;
+            uint32_t ic = 0, hot_passes = 0, hot_rounds = 0;
+            const uint64_t group =
+                hot_wave(__builtin_amdgcn_ballot_w64(active), table, rom_hbm, H, c.a, c.x, c.y, c.p, nzv, cf, vf, ic,
+                         hot_passes, hot_rounds, W.ram_lds + c.ram_off, W.tia_lds + c.tia_off, (uint64_t)c.log,
+                         (uint64_t)c.xram);
+            passes += hot_passes;
+            rounds += hot_rounds;
             if (active) {
-                const uint32_t pc0 = rdl(c.pc, lead), bk0 = rdl(c.bank, lead);
-                const int32_t fl0 = rdl(c.fl, lead), or0 = rdl(c.open_row, lead);
-                const uint32_t oc0 = rdl(c.open_cnt, lead), ob0 = rdl(c.open_base, lead);
-                const uint32_t lg0 = rdl(c.log != nullptr ? 1u : 0u, lead);
-                const bool here = c.pc == pc0 && c.cyc == tmin && c.fl == fl0 && c.open_row == or0 &&
-                                  c.open_cnt == oc0 && c.open_base == ob0 && (c.log != nullptr ? 1u : 0u) == lg0;
-                const bool same = here && c.bank == bk0;
-                bool mixed_ran = false;
-                if constexpr (!TRACK && RC > 0) {
-                    // lanes at the same place in a second bank: one group while the opcode agrees
-                    // (launches with the cartridge staged in LDS: the 4 KB and 8 KB schemes; the
-                    // instantiation for larger cartridges keeps its code without it)
-                    const uint64_t other = __builtin_amdgcn_ballot_w64(here && !same);
-                    if (cm_kind(W) == CART_LINEAR && other != 0) {
-                        const uint32_t bb = rdl(c.bank, (int)__builtin_ctzll(other));
-                        const bool grp = here && (c.bank == bk0 || c.bank == bb);
-                        const uint32_t partial_grp = __builtin_amdgcn_ballot_w64(!grp) != 0 ? 1u : 0u;
-                        if (grp) {
-                            const uint32_t ic0 = c.icount;
-                            uni = run_mb(c, W, W.pre, ended, end_t, partial_grp, bk0, bb, c.bank == bb);
-                            ran = c.icount - ic0;
-                        }
-                        mixed_ran = __builtin_amdgcn_ballot_w64(uni) != 0;
-                    }
-                }
-                if (!mixed_ran) {
-                    const uint32_t partial = __builtin_amdgcn_ballot_w64(!same) != 0 ? 1u : 0u;
-                    if (same) {
-                        const uint32_t ic0 = c.icount;
-                        uni = run_fast<TRACK>(c, W, W.pre, ended, end_t, partial);
-                        ran = c.icount - ic0;
-                    }
-                }
+                c.p = (c.p & ~(FN | FV | FZ | FC)) | cf | ((vf >> 1) & FV) | ((nzv & 0xFF) == 0 ? FZ : 0u) |
+                      ((nzv & 0x180) ? FN : 0u);
+                c.icount += ic;
+                c.ucount += ic;
             }
-            passes += (uint32_t)__builtin_amdgcn_readlane((int)ran, lead);
+            if (hot) {
+                c.pc = ((H.key >> 28) << 12) | ((H.po >> 2) & 0xFFF);
+                c.bank = H.po >> 14;
+                c.cyc = 76 * (320u + (uint32_t)c.fl - H.lines) + (H.acc >> kAccShift) - kAccBias;
+                c.open_row = (int32_t)H.orow - 1;
+                c.open_cnt = ((uint32_t)(H.lp - (uint64_t)c.log) >> 2) - H.obase;
+                c.open_base = H.obase - kSnapArea / 4;
+            }
+            const bool in = group ? __builtin_amdgcn_inverse_ballot_w64(group) : active;
+            bool uni = false;
+            if (group != 0 && in && hot && c.cyc < c.cap) uni = run_cold<TRACK>(c, W);
             const bool ran_uniform = __any(uni);
-            // A group ran and no lane's frame ended: nothing else happens this
-            // round (no per-lane pass, no frame change), so the next round
-            // starts at once; the short path back spares the common round
-            // most of its bookkeeping.
-            if (ran_uniform && !__any(ended)) continue;
-            const bool go = !ran_uniform && active && c.cyc <= tmin + kSchedWindow;
+            if (ran_uniform) {
+                // Nothing else happens this round (no per-lane pass, no frame
+                // change): the next one starts at once.
+                ++passes;
+                continue;
+            }
+            const bool go = in;
             if (go) {
                 if (c.cyc >= c.cap) {
                     c.err |= ERR_FRAME_CAP;
@@ -2287,6 +1988,7 @@ __global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre) {
             else if (cls == SC_WSYNC) slot = HOT_WSYNC;
             else if (cls == SC_IGNORE) slot = HOT_ST_NOP;
             else if (cls >= SC_TIA && cls < SC_TIAS) slot = k ? k : hot_tia_slot(cls & 0x1F);
+            else if (op == 0x85 && cls >= (SC_TIAS | kScFlag0) && cls < SC_TIAG) slot = HOT_FLAG + 2 * ((cls & 0x1F) - kScFlag0);
             else if (cls == (SC_TIAG | R_GRP0)) slot = k ? k + 1 : HOT_STA_GRP0;
             else if (cls == (SC_TIAG | R_GRP1)) slot = k ? k + 2 : HOT_STA_GRP1;
         } else if ((op & 0x1F) == 0x10) {              // conditional branch
@@ -2297,6 +1999,19 @@ __global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre) {
         } else if (op == 0x4C) {                       // JMP: the target's window
             const uint32_t t = (b1 | (b2 << 8)) & 0x1FFF;
             if (t - 0x1000u <= 0xFFCu) slot = kHotSlot.s[op];
+        } else if (md == ABS) {
+            const uint32_t a = (b1 | (b2 << 8)) & 0x1FFF;
+            if ((a & 0x1000) && R.sc && !(a & 0xF00)) {    // Superchip RAM: reads of the read port, writes of the other
+                if (a & 0x80)
+                    slot = op == 0xAD ? HOT_XR_LDA : op == 0x6D ? HOT_XR_ADC : op == 0x2D ? HOT_XR_AND
+                         : op == 0x4D ? HOT_XR_EOR : op == 0x0D ? HOT_XR_ORA : HOT_REAL;
+                else if (op == 0x8D)
+                    slot = HOT_XW;
+            } else if ((a & 0x1000) && op == 0xAD && R.kind == CART_LINEAR) {
+                const uint32_t to = cart_hotspot(R.kind, R.hs_first, R.hs_n, 8, a);
+                slot = to < 8 ? HOT_HS : HOT_ABS;
+                cls = to & 7;
+            }
         } else if (md != ZP || b1 >= 0x80) {
             slot = kHotSlot.s[op];
         }
