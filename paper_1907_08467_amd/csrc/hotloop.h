@@ -44,30 +44,35 @@ namespace vcs {
 
 // Slots, and the opcode each runs (HOT_REAL: the word carries it).  Zero-page
 // operands are RAM; a store of A to a TIA register that is kept as is has a
-// slot per register (hot_tia_slot), one of X or Y takes the register's code
+// pair of slots per register (hot_tia_slot), one of X or Y takes the register's code
 // from the word; GRP0 / GRP1 stores also update the delayed copies; HOT_FLAG + i
 // is a store of A to ENAM0, ENAM1, ENABL, VDELP0, VDELP1, VDELBL (two slots
 // each); HOT_XR_* and HOT_XW access Superchip RAM through its read and write
 // port; HOT_ABS is LDA from a linearly mapped cartridge, HOT_HS the same from a
-// bank hotspot (the new bank in the word's low bits); HOT_WSYNC
+// bank hotspot (the new bank in the word's low bits); HOT_HMP + 2 r + i is a
+// store of A, X, Y (r) to HMP0 / HMP1 (i), HOT_VSYNC one of A to VSYNC (left to
+// the full dispatch when a lane sets bit 1), HOT_INPT4 and HOT_SWCHA_* read the
+// joystick; HOT_WSYNC
 // and HOT_ST_NOP (nothing emulated changes) stand for a store of A, X or Y; the
 // *_X branches cross a page when taken.  Long handlers have several slots.
 constexpr uint32_t HOT_REAL = 0, HOT_STA_TIA = 1,
-                   HOT_STA_GRP0 = 14, HOT_STA_GRP1 = 16, HOT_STX_TIA = 19, HOT_STX_GRP0 = 20, HOT_STX_GRP1 = 21,
-                   HOT_STY_TIA = 22, HOT_STY_GRP0 = 23, HOT_STY_GRP1 = 24, HOT_FLAG = 27, HOT_XR_LDA = 39,
-                   HOT_XR_ADC = 40, HOT_XR_AND = 41, HOT_XR_EOR = 42, HOT_XR_ORA = 43, HOT_XW = 44,
-                   HOT_ABS = 45, HOT_HS = 46, HOT_WSYNC = 47, HOT_ST_NOP = 48, HOT_BPL_X = 49,
-                   kHotPlain = 57;
-constexpr uint32_t kHotSlots = 116;
+                   HOT_STA_GRP0 = 27, HOT_STA_GRP1 = 30, HOT_STX_TIA = 33, HOT_STX_GRP0 = 34, HOT_STX_GRP1 = 35,
+                   HOT_STY_TIA = 36, HOT_STY_GRP0 = 37, HOT_STY_GRP1 = 38, HOT_FLAG = 41, HOT_XR_LDA = 53,
+                   HOT_XR_ADC = 54, HOT_XR_AND = 55, HOT_XR_EOR = 56, HOT_XR_ORA = 57, HOT_XW = 58,
+                   HOT_ABS = 59, HOT_HS = 60, HOT_HMP = 61, HOT_VSYNC = 67, HOT_INPT4 = 68,
+                   HOT_SWCHA_LDA = 69, HOT_SWCHA_EOR = 70, HOT_WSYNC = 71, HOT_ST_NOP = 72, HOT_BPL_X = 73,
+                   kHotPlain = 81;
+constexpr uint32_t kHotSlots = 140;
 constexpr uint8_t kHotSlotOp[kHotSlots] = {
     0x00, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85,
-    0x85, 0x85, 0x85, 0x86, 0x86, 0x86, 0x84, 0x84, 0x84, 0x00, 0x00, 0x85, 0x85, 0x85, 0x85, 0x85,
-    0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0xAD, 0x6D, 0x2D, 0x4D, 0x0D, 0x8D, 0xAD, 0xAD, 0x85,
-    0x85, 0x10, 0x30, 0x50, 0x70, 0x90, 0xB0, 0xD0, 0xF0, 0x05, 0x06, 0x09, 0x0A, 0x10, 0x18, 0x24,
-    0x25, 0x26, 0x29, 0x2A, 0x30, 0x38, 0x45, 0x46, 0x49, 0x4A, 0x4C, 0x50, 0x65, 0x66, 0x69, 0x6A,
-    0x70, 0x84, 0x85, 0x86, 0x88, 0x8A, 0x90, 0x98, 0xA0, 0xA2, 0xA4, 0xA5, 0xA6, 0xA8, 0xA9, 0xAA,
-    0xB0, 0xB8, 0xC0, 0xC4, 0xC5, 0xC6, 0xC8, 0xC9, 0xCA, 0xD0, 0xD8, 0xE0, 0xE4, 0xE5, 0xE6, 0xE8,
-    0xE9, 0xEA, 0xF0, 0xF8,
+    0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85,
+    0x85, 0x86, 0x86, 0x86, 0x84, 0x84, 0x84, 0x00, 0x00, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85,
+    0x85, 0x85, 0x85, 0x85, 0x85, 0xAD, 0x6D, 0x2D, 0x4D, 0x0D, 0x8D, 0xAD, 0xAD, 0x85, 0x85, 0x86,
+    0x86, 0x84, 0x84, 0x85, 0xA5, 0xAD, 0x4D, 0x85, 0x85, 0x10, 0x30, 0x50, 0x70, 0x90, 0xB0, 0xD0,
+    0xF0, 0x05, 0x06, 0x09, 0x0A, 0x10, 0x18, 0x24, 0x25, 0x26, 0x29, 0x2A, 0x30, 0x38, 0x45, 0x46,
+    0x49, 0x4A, 0x4C, 0x50, 0x65, 0x66, 0x69, 0x6A, 0x70, 0x84, 0x85, 0x86, 0x88, 0x8A, 0x90, 0x98,
+    0xA0, 0xA2, 0xA4, 0xA5, 0xA6, 0xA8, 0xA9, 0xAA, 0xB0, 0xB8, 0xC0, 0xC4, 0xC5, 0xC6, 0xC8, 0xC9,
+    0xCA, 0xD0, 0xD8, 0xE0, 0xE4, 0xE5, 0xE6, 0xE8, 0xE9, 0xEA, 0xF0, 0xF8,
 };
 // The slot that runs opcode `op` without a page-crossing branch or a TIA store
 // (HOT_REAL: none).
@@ -79,7 +84,7 @@ constexpr uint32_t hot_slot(uint32_t op) {
 // The slot of a store of A to the TIA register with code `code` (R_COLUP0 ..
 // R_PF2, R_VBLANK, R_NUSIZ0, R_NUSIZ1)
 __host__ __device__ constexpr uint32_t hot_tia_slot(uint32_t code) {
-    return HOT_STA_TIA + (code <= R_PF2 ? code : code == R_VBLANK ? 10 : code - R_NUSIZ0 + 11);
+    return HOT_STA_TIA + 2 * (code <= R_PF2 ? code : code == R_VBLANK ? 10 : code - R_NUSIZ0 + 11);
 }
 
 // ACC: cycle in the line + 52 in the top 7 bits, instructions below
@@ -243,6 +248,17 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     "s_or_b32 s72, s72, s88\n"                             \
     "s_or_b32 s86, s86, s87\n"                             \
     "s_load_dwordx4 s[76:79], s[70:71], s72\n" HL_ABSBYTE HL_TGT("s76") HL_GO(4)
+// motion registers and VSYNC: no log entry, kept per lane
+#define HL_HMP(B, slot, reg, hmp) HL_ORG(B, slot) HL_WAIT HL_TGT("s78") HL_FETCH(2) "v_mov_b32 " hmp ", " reg "\n" HL_GO(3)
+#define HL_VSYNC(B, slot)                                  \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "v_and_b32 v122, 2, %[a]\n"                            \
+    "v_cmp_ne_u32 vcc, 0, v122\n"                          \
+    "s_cbranch_vccnz .Lout%=\n" HL_TGT("s78") HL_FETCH(2)  \
+    "v_mov_b32 %[vsync], %[a]\n" HL_GO(3)
+// the joystick, held per lane for the frame
+#define HL_LDR(reg) "v_mov_b32 %[a], " reg "\nv_mov_b32 %[nz], " reg "\n"
+#define HL_IN(B, slot, len, next, cyc, work) HL_ORG(B, slot) HL_WAIT HL_TGT(next) HL_FETCH(len) work HL_GO(cyc)
 // Superchip RAM of the lane's env, in HBM: operand in v123 (the wait includes
 // the log stores before it)
 #define HL_XADDR                                           \
@@ -273,15 +289,18 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
 //
 // Logged: the entry goes into the open row when that is the line's row and the
 // line has not ended (the line's number, or -1 past its end, against the open
-// row's); else .Lsnap opens rows first, or leaves the store to the full
-// dispatch.  `code8`: the entry's register code << 8 less 3 * 52 + 68.  Where
+// row's); before the visible part it only changes the register when the row
+// before is open (about half the stores of the plain workload).  Else .Lsnap
+// opens rows first, or leaves the store to the full dispatch.  `code8`: the entry's register code << 8 less 3 * 52 + 68.  Where
 // the entry goes is per lane: lanes whose earlier writes fell on different
 // sides of a line's visible part have logged different numbers of entries, and
 // still run as one group.
 #define HL_LOGGED(id, val, code8, write)                   \
     "s_add_u32 s73, s73, (3<<25)+1\n"                      \
-    "s_cselect_b32 s87, -1, s80\n"                         \
+    "s_cselect_b32 s87, -9, s80\n"                         \
     "s_lshr_b32 s88, s73, 25\n"                            \
+    "s_cmp_lt_u32 s88, 75\n"                               \
+    "s_cbranch_scc1 .Lhbl" id "%=\n"                       \
     "s_cmp_lg_u32 s87, s83\n"                              \
     "s_mul_i32 s87, s88, 3\n"                              \
     "s_cbranch_scc1 .Lrow" id "%=\n"                       \
@@ -291,6 +310,10 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     "global_store_dword v[100:101], v123, off\n"           \
     "v_lshl_add_u64 v[100:101], 1, 2, v[100:101]\n"        \
     ".Lreg" id "%=:\n" write HL_JUMP                       \
+    ".Lhbl" id "%=:\n"                                     \
+    "s_add_u32 s87, s87, 1\n"                              \
+    "s_cmp_lg_u32 s87, s83\n"                              \
+    "s_cbranch_scc1 .Lrow" id "%=\n" write HL_JUMP         \
     ".Lrow" id "%=:\n"                                     \
     "s_swappc_b64 s[96:97], s[64:65]\n"                    \
     "s_cbranch_scc0 .Lent" id "%=\n"                       \
@@ -372,110 +395,120 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
 #define HL_BLOCK(B, TIA, TIAX, GRP0, GRP1, HL_XY, FLAG) \
     HL_ORG(B, 0) "s_branch .Lout%=\n"                                                                /* HOT_REAL */ \
     TIA(B, 1, 0)                                                                                     /* STA COLUP0 */ \
-    TIA(B, 2, 1)                                                                                     /* STA COLUP1 */ \
-    TIA(B, 3, 2)                                                                                     /* STA COLUPF */ \
-    TIA(B, 4, 3)                                                                                     /* STA COLUBK */ \
-    TIA(B, 5, 4)                                                                                     /* STA CTRLPF */ \
-    TIA(B, 6, 5)                                                                                     /* STA REFP0 */ \
-    TIA(B, 7, 6)                                                                                     /* STA REFP1 */ \
-    TIA(B, 8, 7)                                                                                     /* STA PF0 */ \
-    TIA(B, 9, 8)                                                                                     /* STA PF1 */ \
-    TIA(B, 10, 9)                                                                                    /* STA PF2 */ \
-    TIA(B, 11, 14)                                                                                   /* STA VBLANK */ \
-    TIA(B, 12, 18)                                                                                   /* STA NUSIZ0 */ \
-    TIA(B, 13, 19)                                                                                   /* STA NUSIZ1 */ \
-    GRP0(B, 14)                                                                                      /* STA GRP0 */ \
-    GRP1(B, 16)                                                                                      /* STA GRP1 */ \
-    HL_XY(B, 19, "%[x]", "t")                                                                        /* STX to a TIA register */ \
-    HL_XY(B, 20, "%[x]", "g")                                                                        /* STX GRP0 */ \
-    HL_XY(B, 21, "%[x]", "h")                                                                        /* STX GRP1 */ \
-    HL_XY(B, 22, "%[y]", "t")                                                                        /* STY to a TIA register */ \
-    HL_XY(B, 23, "%[y]", "g")                                                                        /* STY GRP0 */ \
-    HL_XY(B, 24, "%[y]", "h")                                                                        /* STY GRP1 */ \
-    TIAX(B, 25)                                                                                      /* the body of the two stores to a TIA register */ \
-    FLAG(B, 27, 0, 1)                                                                                /* STA ENAM0 */ \
-    FLAG(B, 29, 1, 1)                                                                                /* STA ENAM1 */ \
-    FLAG(B, 31, 2, 1)                                                                                /* STA ENABL */ \
-    FLAG(B, 33, 4, 0)                                                                                /* STA VDELP0 */ \
-    FLAG(B, 35, 5, 0)                                                                                /* STA VDELP1 */ \
-    FLAG(B, 37, 6, 0)                                                                                /* STA VDELBL */ \
-    HL_XR(B, 39, HL_LDV)                                                                             /* LDA from Superchip RAM */ \
-    HL_XRD(B, 40, HL_ADC("v123"))                                                                    /* ADC from Superchip RAM */ \
-    HL_XR(B, 41, HL_AND("v123"))                                                                     /* AND from Superchip RAM */ \
-    HL_XR(B, 42, HL_EOR("v123"))                                                                     /* EOR from Superchip RAM */ \
-    HL_XR(B, 43, HL_ORA("v123"))                                                                     /* ORA from Superchip RAM */ \
-    HL_XW(B, 44)                                                                                     /* STA to Superchip RAM */ \
-    HL_ABS(B, 45)                                                                                    /* LDA from the cartridge */ \
-    HL_HS(B, 46)                                                                                     /* LDA from a bank hotspot */ \
-    HL_SYNC(B, 47)                                                                                   /* WSYNC */ \
-    HL_ORG(B, 48) HL_WAIT HL_TGT("s78") HL_FETCH(2) HL_GO(3)                                         /* store without effect */ \
-    HL_BR(B, 49, HL_T_EQ("0x180", "%[nz]"), "9")                                                     /* BPL across a page */ \
-    HL_BR(B, 50, HL_T_NE("0x180", "%[nz]"), "9")                                                     /* BMI across a page */ \
-    HL_BR(B, 51, HL_T_EQ("0x80", "%[v]"), "9")                                                       /* BVC across a page */ \
-    HL_BR(B, 52, HL_T_NE("0x80", "%[v]"), "9")                                                       /* BVS across a page */ \
-    HL_BR(B, 53, "v_cmp_eq_u32 vcc, 0, %[c]\n", "9")                                                 /* BCC across a page */ \
-    HL_BR(B, 54, "v_cmp_ne_u32 vcc, 0, %[c]\n", "9")                                                 /* BCS across a page */ \
-    HL_BR(B, 55, HL_T_NE("0xff", "%[nz]"), "9")                                                      /* BNE across a page */ \
-    HL_BR(B, 56, HL_T_EQ("0xff", "%[nz]"), "9")                                                      /* BEQ across a page */ \
-    HL_ZPR(B, 57, HL_ORA("v123"))                                                                    /* $05 */ \
-    HL_ZPM(B, 58, HL_ASL("v123"))                                                                    /* $06 */ \
-    HL_IMM(B, 59, HL_ORA("s86"))                                                                     /* $09 */ \
-    HL_IMP(B, 60, HL_ASL("%[a]"))                                                                    /* $0A */ \
-    HL_BR(B, 61, HL_T_EQ("0x180", "%[nz]"), "8")                                                     /* $10 */ \
-    HL_IMP(B, 62, "v_mov_b32 %[c], 0\n")                                                             /* $18 */ \
-    HL_ZPR(B, 63, HL_BIT)                                                                            /* $24 */ \
-    HL_ZPR(B, 64, HL_AND("v123"))                                                                    /* $25 */ \
-    HL_ZPM(B, 65, HL_ROL("v123"))                                                                    /* $26 */ \
-    HL_IMM(B, 66, HL_AND("s86"))                                                                     /* $29 */ \
-    HL_IMP(B, 67, HL_ROL("%[a]"))                                                                    /* $2A */ \
-    HL_BR(B, 68, HL_T_NE("0x180", "%[nz]"), "8")                                                     /* $30 */ \
-    HL_IMP(B, 69, "v_mov_b32 %[c], 1\n")                                                             /* $38 */ \
-    HL_ZPR(B, 70, HL_EOR("v123"))                                                                    /* $45 */ \
-    HL_ZPM(B, 71, HL_LSR("v123"))                                                                    /* $46 */ \
-    HL_IMM(B, 72, HL_EOR("s86"))                                                                     /* $49 */ \
-    HL_IMP(B, 73, HL_LSR("%[a]"))                                                                    /* $4A */ \
-    HL_JMP(B, 74)                                                                                    /* $4C */ \
-    HL_BR(B, 75, HL_T_EQ("0x80", "%[v]"), "8")                                                       /* $50 */ \
-    HL_ZPRD(B, 76, HL_ADC("v123"))                                                                   /* $65 */ \
-    HL_ZPM(B, 77, HL_ROR("v123"))                                                                    /* $66 */ \
-    HL_IMMD(B, 78, HL_ADC("s86"))                                                                    /* $69 */ \
-    HL_IMP(B, 79, HL_ROR("%[a]"))                                                                    /* $6A */ \
-    HL_BR(B, 80, HL_T_NE("0x80", "%[v]"), "8")                                                       /* $70 */ \
-    HL_ZPS(B, 81, "%[y]")                                                                            /* $84 */ \
-    HL_ZPS(B, 82, "%[a]")                                                                            /* $85 */ \
-    HL_ZPS(B, 83, "%[x]")                                                                            /* $86 */ \
-    HL_IMP(B, 84, HL_DEC("%[y]"))                                                                    /* $88 */ \
-    HL_IMP(B, 85, "v_mov_b32 %[a], %[x]\n" HL_NZ("%[x]"))                                            /* $8A */ \
-    HL_BR(B, 86, "v_cmp_eq_u32 vcc, 0, %[c]\n", "8")                                                 /* $90 */ \
-    HL_IMP(B, 87, "v_mov_b32 %[a], %[y]\n" HL_NZ("%[y]"))                                            /* $98 */ \
-    HL_IMM(B, 88, HL_LDI("%[y]"))                                                                    /* $A0 */ \
-    HL_IMM(B, 89, HL_LDI("%[x]"))                                                                    /* $A2 */ \
-    HL_ZPL(B, 90, "%[y]")                                                                            /* $A4 */ \
-    HL_ZPL(B, 91, "%[a]")                                                                            /* $A5 */ \
-    HL_ZPL(B, 92, "%[x]")                                                                            /* $A6 */ \
-    HL_IMP(B, 93, "v_mov_b32 %[y], %[a]\n" HL_NZ("%[a]"))                                            /* $A8 */ \
-    HL_IMM(B, 94, HL_LDI("%[a]"))                                                                    /* $A9 */ \
-    HL_IMP(B, 95, "v_mov_b32 %[x], %[a]\n" HL_NZ("%[a]"))                                            /* $AA */ \
-    HL_BR(B, 96, "v_cmp_ne_u32 vcc, 0, %[c]\n", "8")                                                 /* $B0 */ \
-    HL_IMP(B, 97, "v_mov_b32 %[v], 0\n")                                                             /* $B8 */ \
-    HL_IMM(B, 98, HL_CMP_S("%[y]"))                                                                  /* $C0 */ \
-    HL_ZPR(B, 99, HL_CMP("%[y]", "v123"))                                                            /* $C4 */ \
-    HL_ZPR(B, 100, HL_CMP("%[a]", "v123"))                                                           /* $C5 */ \
-    HL_ZPM(B, 101, HL_DEC("v123"))                                                                   /* $C6 */ \
-    HL_IMP(B, 102, HL_INC("%[y]"))                                                                   /* $C8 */ \
-    HL_IMM(B, 103, HL_CMP_S("%[a]"))                                                                 /* $C9 */ \
-    HL_IMP(B, 104, HL_DEC("%[x]"))                                                                   /* $CA */ \
-    HL_BR(B, 105, HL_T_NE("0xff", "%[nz]"), "8")                                                     /* $D0 */ \
-    HL_IMP(B, 106, "s_andn2_b64 s[50:51], s[50:51], exec\n")                                         /* $D8 */ \
-    HL_IMM(B, 107, HL_CMP_S("%[x]"))                                                                 /* $E0 */ \
-    HL_ZPR(B, 108, HL_CMP("%[x]", "v123"))                                                           /* $E4 */ \
-    HL_ZPRD(B, 109, "v_xor_b32 v123, 0xff, v123\n" HL_ADC("v123"))                                   /* $E5 */ \
-    HL_ZPM(B, 110, HL_INC("v123"))                                                                   /* $E6 */ \
-    HL_IMP(B, 111, HL_INC("%[x]"))                                                                   /* $E8 */ \
-    HL_IMMD(B, 112, "s_xor_b32 s86, s86, 0xff\n" HL_ADC("s86"))                                      /* $E9 */ \
-    HL_IMP(B, 113, "")                                                                               /* $EA */ \
-    HL_BR(B, 114, HL_T_EQ("0xff", "%[nz]"), "8")                                                     /* $F0 */ \
-    HL_IMP(B, 115, "s_or_b64 s[50:51], s[50:51], exec\n")                                            /* $F8 */
+    TIA(B, 3, 1)                                                                                     /* STA COLUP1 */ \
+    TIA(B, 5, 2)                                                                                     /* STA COLUPF */ \
+    TIA(B, 7, 3)                                                                                     /* STA COLUBK */ \
+    TIA(B, 9, 4)                                                                                     /* STA CTRLPF */ \
+    TIA(B, 11, 5)                                                                                    /* STA REFP0 */ \
+    TIA(B, 13, 6)                                                                                    /* STA REFP1 */ \
+    TIA(B, 15, 7)                                                                                    /* STA PF0 */ \
+    TIA(B, 17, 8)                                                                                    /* STA PF1 */ \
+    TIA(B, 19, 9)                                                                                    /* STA PF2 */ \
+    TIA(B, 21, 14)                                                                                   /* STA VBLANK */ \
+    TIA(B, 23, 18)                                                                                   /* STA NUSIZ0 */ \
+    TIA(B, 25, 19)                                                                                   /* STA NUSIZ1 */ \
+    GRP0(B, 27)                                                                                      /* STA GRP0 */ \
+    GRP1(B, 30)                                                                                      /* STA GRP1 */ \
+    HL_XY(B, 33, "%[x]", "t")                                                                        /* STX to a TIA register */ \
+    HL_XY(B, 34, "%[x]", "g")                                                                        /* STX GRP0 */ \
+    HL_XY(B, 35, "%[x]", "h")                                                                        /* STX GRP1 */ \
+    HL_XY(B, 36, "%[y]", "t")                                                                        /* STY to a TIA register */ \
+    HL_XY(B, 37, "%[y]", "g")                                                                        /* STY GRP0 */ \
+    HL_XY(B, 38, "%[y]", "h")                                                                        /* STY GRP1 */ \
+    TIAX(B, 39)                                                                                      /* the body of the two stores to a TIA register */ \
+    FLAG(B, 41, 0, 1)                                                                                /* STA ENAM0 */ \
+    FLAG(B, 43, 1, 1)                                                                                /* STA ENAM1 */ \
+    FLAG(B, 45, 2, 1)                                                                                /* STA ENABL */ \
+    FLAG(B, 47, 4, 0)                                                                                /* STA VDELP0 */ \
+    FLAG(B, 49, 5, 0)                                                                                /* STA VDELP1 */ \
+    FLAG(B, 51, 6, 0)                                                                                /* STA VDELBL */ \
+    HL_XR(B, 53, HL_LDV)                                                                             /* LDA from Superchip RAM */ \
+    HL_XRD(B, 54, HL_ADC("v123"))                                                                    /* ADC from Superchip RAM */ \
+    HL_XR(B, 55, HL_AND("v123"))                                                                     /* AND from Superchip RAM */ \
+    HL_XR(B, 56, HL_EOR("v123"))                                                                     /* EOR from Superchip RAM */ \
+    HL_XR(B, 57, HL_ORA("v123"))                                                                     /* ORA from Superchip RAM */ \
+    HL_XW(B, 58)                                                                                     /* STA to Superchip RAM */ \
+    HL_ABS(B, 59)                                                                                    /* LDA from the cartridge */ \
+    HL_HS(B, 60)                                                                                     /* LDA from a bank hotspot */ \
+    HL_HMP(B, 61, "%[a]", "%[hmp0]")                                                                 /* STA HMP0 */ \
+    HL_HMP(B, 62, "%[a]", "%[hmp1]")                                                                 /* STA HMP1 */ \
+    HL_HMP(B, 63, "%[x]", "%[hmp0]")                                                                 /* STX HMP0 */ \
+    HL_HMP(B, 64, "%[x]", "%[hmp1]")                                                                 /* STX HMP1 */ \
+    HL_HMP(B, 65, "%[y]", "%[hmp0]")                                                                 /* STY HMP0 */ \
+    HL_HMP(B, 66, "%[y]", "%[hmp1]")                                                                 /* STY HMP1 */ \
+    HL_VSYNC(B, 67)                                                                                  /* STA VSYNC without bit 1 */ \
+    HL_IN(B, 68, 2, "s78", 3, HL_LDR("%[inpt4]"))                                                    /* LDA INPT4 */ \
+    HL_IN(B, 69, 3, "s79", 4, HL_LDR("%[swcha]"))                                                    /* LDA SWCHA */ \
+    HL_IN(B, 70, 3, "s79", 4, HL_EOR("%[swcha]"))                                                    /* EOR SWCHA */ \
+    HL_SYNC(B, 71)                                                                                   /* WSYNC */ \
+    HL_ORG(B, 72) HL_WAIT HL_TGT("s78") HL_FETCH(2) HL_GO(3)                                         /* store without effect */ \
+    HL_BR(B, 73, HL_T_EQ("0x180", "%[nz]"), "9")                                                     /* BPL across a page */ \
+    HL_BR(B, 74, HL_T_NE("0x180", "%[nz]"), "9")                                                     /* BMI across a page */ \
+    HL_BR(B, 75, HL_T_EQ("0x80", "%[v]"), "9")                                                       /* BVC across a page */ \
+    HL_BR(B, 76, HL_T_NE("0x80", "%[v]"), "9")                                                       /* BVS across a page */ \
+    HL_BR(B, 77, "v_cmp_eq_u32 vcc, 0, %[c]\n", "9")                                                 /* BCC across a page */ \
+    HL_BR(B, 78, "v_cmp_ne_u32 vcc, 0, %[c]\n", "9")                                                 /* BCS across a page */ \
+    HL_BR(B, 79, HL_T_NE("0xff", "%[nz]"), "9")                                                      /* BNE across a page */ \
+    HL_BR(B, 80, HL_T_EQ("0xff", "%[nz]"), "9")                                                      /* BEQ across a page */ \
+    HL_ZPR(B, 81, HL_ORA("v123"))                                                                    /* $05 */ \
+    HL_ZPM(B, 82, HL_ASL("v123"))                                                                    /* $06 */ \
+    HL_IMM(B, 83, HL_ORA("s86"))                                                                     /* $09 */ \
+    HL_IMP(B, 84, HL_ASL("%[a]"))                                                                    /* $0A */ \
+    HL_BR(B, 85, HL_T_EQ("0x180", "%[nz]"), "8")                                                     /* $10 */ \
+    HL_IMP(B, 86, "v_mov_b32 %[c], 0\n")                                                             /* $18 */ \
+    HL_ZPR(B, 87, HL_BIT)                                                                            /* $24 */ \
+    HL_ZPR(B, 88, HL_AND("v123"))                                                                    /* $25 */ \
+    HL_ZPM(B, 89, HL_ROL("v123"))                                                                    /* $26 */ \
+    HL_IMM(B, 90, HL_AND("s86"))                                                                     /* $29 */ \
+    HL_IMP(B, 91, HL_ROL("%[a]"))                                                                    /* $2A */ \
+    HL_BR(B, 92, HL_T_NE("0x180", "%[nz]"), "8")                                                     /* $30 */ \
+    HL_IMP(B, 93, "v_mov_b32 %[c], 1\n")                                                             /* $38 */ \
+    HL_ZPR(B, 94, HL_EOR("v123"))                                                                    /* $45 */ \
+    HL_ZPM(B, 95, HL_LSR("v123"))                                                                    /* $46 */ \
+    HL_IMM(B, 96, HL_EOR("s86"))                                                                     /* $49 */ \
+    HL_IMP(B, 97, HL_LSR("%[a]"))                                                                    /* $4A */ \
+    HL_JMP(B, 98)                                                                                    /* $4C */ \
+    HL_BR(B, 99, HL_T_EQ("0x80", "%[v]"), "8")                                                       /* $50 */ \
+    HL_ZPRD(B, 100, HL_ADC("v123"))                                                                  /* $65 */ \
+    HL_ZPM(B, 101, HL_ROR("v123"))                                                                   /* $66 */ \
+    HL_IMMD(B, 102, HL_ADC("s86"))                                                                   /* $69 */ \
+    HL_IMP(B, 103, HL_ROR("%[a]"))                                                                   /* $6A */ \
+    HL_BR(B, 104, HL_T_NE("0x80", "%[v]"), "8")                                                      /* $70 */ \
+    HL_ZPS(B, 105, "%[y]")                                                                           /* $84 */ \
+    HL_ZPS(B, 106, "%[a]")                                                                           /* $85 */ \
+    HL_ZPS(B, 107, "%[x]")                                                                           /* $86 */ \
+    HL_IMP(B, 108, HL_DEC("%[y]"))                                                                   /* $88 */ \
+    HL_IMP(B, 109, "v_mov_b32 %[a], %[x]\n" HL_NZ("%[x]"))                                           /* $8A */ \
+    HL_BR(B, 110, "v_cmp_eq_u32 vcc, 0, %[c]\n", "8")                                                /* $90 */ \
+    HL_IMP(B, 111, "v_mov_b32 %[a], %[y]\n" HL_NZ("%[y]"))                                           /* $98 */ \
+    HL_IMM(B, 112, HL_LDI("%[y]"))                                                                   /* $A0 */ \
+    HL_IMM(B, 113, HL_LDI("%[x]"))                                                                   /* $A2 */ \
+    HL_ZPL(B, 114, "%[y]")                                                                           /* $A4 */ \
+    HL_ZPL(B, 115, "%[a]")                                                                           /* $A5 */ \
+    HL_ZPL(B, 116, "%[x]")                                                                           /* $A6 */ \
+    HL_IMP(B, 117, "v_mov_b32 %[y], %[a]\n" HL_NZ("%[a]"))                                           /* $A8 */ \
+    HL_IMM(B, 118, HL_LDI("%[a]"))                                                                   /* $A9 */ \
+    HL_IMP(B, 119, "v_mov_b32 %[x], %[a]\n" HL_NZ("%[a]"))                                           /* $AA */ \
+    HL_BR(B, 120, "v_cmp_ne_u32 vcc, 0, %[c]\n", "8")                                                /* $B0 */ \
+    HL_IMP(B, 121, "v_mov_b32 %[v], 0\n")                                                            /* $B8 */ \
+    HL_IMM(B, 122, HL_CMP_S("%[y]"))                                                                 /* $C0 */ \
+    HL_ZPR(B, 123, HL_CMP("%[y]", "v123"))                                                           /* $C4 */ \
+    HL_ZPR(B, 124, HL_CMP("%[a]", "v123"))                                                           /* $C5 */ \
+    HL_ZPM(B, 125, HL_DEC("v123"))                                                                   /* $C6 */ \
+    HL_IMP(B, 126, HL_INC("%[y]"))                                                                   /* $C8 */ \
+    HL_IMM(B, 127, HL_CMP_S("%[a]"))                                                                 /* $C9 */ \
+    HL_IMP(B, 128, HL_DEC("%[x]"))                                                                   /* $CA */ \
+    HL_BR(B, 129, HL_T_NE("0xff", "%[nz]"), "8")                                                     /* $D0 */ \
+    HL_IMP(B, 130, "s_andn2_b64 s[50:51], s[50:51], exec\n")                                         /* $D8 */ \
+    HL_IMM(B, 131, HL_CMP_S("%[x]"))                                                                 /* $E0 */ \
+    HL_ZPR(B, 132, HL_CMP("%[x]", "v123"))                                                           /* $E4 */ \
+    HL_ZPRD(B, 133, "v_xor_b32 v123, 0xff, v123\n" HL_ADC("v123"))                                   /* $E5 */ \
+    HL_ZPM(B, 134, HL_INC("v123"))                                                                   /* $E6 */ \
+    HL_IMP(B, 135, HL_INC("%[x]"))                                                                   /* $E8 */ \
+    HL_IMMD(B, 136, "s_xor_b32 s86, s86, 0xff\n" HL_ADC("s86"))                                      /* $E9 */ \
+    HL_IMP(B, 137, "")                                                                               /* $EA */ \
+    HL_BR(B, 138, HL_T_EQ("0xff", "%[nz]"), "8")                                                     /* $F0 */ \
+    HL_IMP(B, 139, "s_or_b64 s[50:51], s[50:51], exec\n")                                            /* $F8 */
 
 // Fold the current group's instruction count into its lanes' counts and the
 // wave's passes (exec: the group).
@@ -555,7 +588,8 @@ constexpr uint32_t kHotLogged = 1u << 27;
 // the block and forming a group from per-lane state took some 2,000 cycles.
 __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uint64_t rom, HotLane& H, uint32_t& a,
                                              uint32_t& x, uint32_t& y, uint32_t& p, uint32_t& nz, uint32_t& c,
-                                             uint32_t& v, uint32_t& ic, uint32_t& passes, uint32_t& rounds,
+                                             uint32_t& v, uint32_t& hmp0, uint32_t& hmp1, uint32_t& vsync,
+                                             uint32_t inpt4, uint32_t swcha, uint32_t& ic, uint32_t& passes, uint32_t& rounds,
                                              uint32_t ram, uint32_t tia, uint64_t log, uint64_t xram) {
     static_assert(kSnapArea == 1696 * 4 && kCountMask == 31 && kFrameEntries == 5280 && kRows == 210 &&
                       kFirstRow == 34 && kSnapBytes == 32,
@@ -823,8 +857,9 @@ __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uin
         "v_or_b32 %[p], %[p], v122\n"
         : "+{s[48:49]}"(lanes), "+{s57}"(passes), "+{s58}"(rounds), [po] "+v"(H.po), [acc] "+v"(H.acc),
           [lines] "+v"(H.lines), [orow] "+v"(H.orow), "+{v[100:101]}"(H.lp), [obase] "+v"(H.obase), [a] "+v"(a),
-          [x] "+v"(x), [y] "+v"(y), [p] "+v"(p), [nz] "+v"(nz), [c] "+v"(c), [v] "+v"(v), [ic] "+v"(ic)
-        : "{s[70:71]}"(table), "{s[40:41]}"(rom), [key] "v"(H.key), [ram] "v"(ram), [tia] "v"(tia), [log] "v"(log),
+          [x] "+v"(x), [y] "+v"(y), [p] "+v"(p), [nz] "+v"(nz), [c] "+v"(c), [v] "+v"(v), [hmp0] "+v"(hmp0),
+          [hmp1] "+v"(hmp1), [vsync] "+v"(vsync), [ic] "+v"(ic)
+        : "{s[70:71]}"(table), "{s[40:41]}"(rom), [key] "v"(H.key), [inpt4] "v"(inpt4), [swcha] "v"(swcha), [ram] "v"(ram), [tia] "v"(tia), [log] "v"(log),
           [log0] "v"((uint32_t)log), [xram] "v"(xram)
         : "memory", "scc", "vcc", "s43", "s44", "s45", "s46", "s47", "s50", "s51", "s52", "s53", "s54", "s55", "s56",
           "s59", "s60", "s61", "s62", "s63", "s64", "s65", "s66", "s67", "s68", "s69", "s72", "s73", "s74", "s75",

@@ -1753,7 +1753,8 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
             uint32_t nzv = ((c.p & FN) << 1) | (((c.p >> 1) & 1) ^ 1), cf = c.p & FC, vf = c.p << 1;
             uint32_t ic = 0, hot_passes = 0, hot_rounds = 0;
             const uint64_t group =
-                hot_wave(__builtin_amdgcn_ballot_w64(active), table, rom_hbm, H, c.a, c.x, c.y, c.p, nzv, cf, vf, ic,
+                hot_wave(__builtin_amdgcn_ballot_w64(active), table, rom_hbm, H, c.a, c.x, c.y, c.p, nzv, cf, vf, c.hmp0, c.hmp1, c.vsync, c.inpt4,
+                         c.swcha, ic,
                          hot_passes, hot_rounds, W.ram_lds + c.ram_off, W.tia_lds + c.tia_off, (uint64_t)c.log,
                          (uint64_t)c.xram);
             passes += hot_passes;
@@ -1989,6 +1990,9 @@ __global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre) {
             else if (cls == SC_IGNORE) slot = HOT_ST_NOP;
             else if (cls >= SC_TIA && cls < SC_TIAS) slot = k ? k : hot_tia_slot(cls & 0x1F);
             else if (op == 0x85 && cls >= (SC_TIAS | kScFlag0) && cls < SC_TIAG) slot = HOT_FLAG + 2 * ((cls & 0x1F) - kScFlag0);
+            else if (cls == SC_EXIT && ((b1 & 0x3E) == 0x20 || ((b1 & 0x3F) == 0 && op == 0x85)) &&
+                     !(R.kind == CART_3F && b1 <= 0x3F))   // HMP0, HMP1, VSYNC
+                slot = (b1 & 0x3F) == 0 ? HOT_VSYNC : HOT_HMP + (op == 0x85 ? 0 : op == 0x86 ? 2 : 4) + (b1 & 1);
             else if (cls == (SC_TIAG | R_GRP0)) slot = k ? k + 1 : HOT_STA_GRP0;
             else if (cls == (SC_TIAG | R_GRP1)) slot = k ? k + 2 : HOT_STA_GRP1;
         } else if ((op & 0x1F) == 0x10) {              // conditional branch
@@ -2011,7 +2015,11 @@ __global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre) {
                 const uint32_t to = cart_hotspot(R.kind, R.hs_first, R.hs_n, 8, a);
                 slot = to < 8 ? HOT_HS : HOT_ABS;
                 cls = to & 7;
+            } else if ((a & 0x1287) == 0x0280 && (op == 0xAD || op == 0x4D)) {
+                slot = op == 0xAD ? HOT_SWCHA_LDA : HOT_SWCHA_EOR;
             }
+        } else if (op == 0xA5 && b1 < 0x80 && (b1 & 0xF) == 0xC) {
+            slot = HOT_INPT4;
         } else if (md != ZP || b1 >= 0x80) {
             slot = kHotSlot.s[op];
         }
