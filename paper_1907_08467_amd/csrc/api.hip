@@ -1065,10 +1065,10 @@ int vcs_reset(vcs_ctx* c, const int32_t* ids, uint32_t n, uint8_t* obs, void* st
     } else if (c->cfg.noop_after_copy) {
         launch_step_begin(P.d_stepw + c->instr_off, c->stepw_words - c->instr_off, nullptr, 0, s);
     } else if (ids) {
-        launch_step_begin(P.d_counts, c->n_roms, P.d_tag, P.residue, s);
-        launch_validate(ids, n, c->cfg.num_envs, c->d_env_rom, c->d_claim, P.d_tag, P.d_counts, P.d_valid,
-                        nullptr, nullptr, nullptr, c->d_err, s);
-        rs.valid = P.d_valid;
+        launch_step_begin(nullptr, 0, P.d_tag, P.residue, s);
+        rs.claim = c->d_claim;
+        rs.tag = P.d_tag;
+        rs.err_word = c->d_err;
     }
     rs.cache_state = c->d_cache_state;
     rs.cache_obs = c->d_cache_obs;

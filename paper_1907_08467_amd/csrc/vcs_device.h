@@ -228,6 +228,9 @@ struct ResetArgs {
     uint32_t num_envs;
     const StepInfo* info;        // NULL: reset every listed env; else only done ones
     const uint8_t* valid;        // NULL or per-position validity
+    uint32_t* claim;             // NULL, or validate the ids here: the call's tag is claimed in it
+    const uint32_t* tag;         //   (with err_word)
+    uint32_t* err_word;
     const DevEnv* cache_state;   // [n_roms][K]
     const uint8_t* cache_obs;    // [n_roms][K][84*84]
     uint32_t K;
