@@ -1656,10 +1656,10 @@ int vcs_policy_act(vcs_policy* P, const uint8_t* stack, uint32_t n, float* logit
         a.bias = P->b[l];
         a.out = l < 4 ? static_cast<void*>(P->act[l]) : static_cast<void*>(lg);
         a.M = n * L.OH * L.OH;
+        a.actions = l == 4 ? actions : nullptr;
         launch_policy_layer(l, a, s);
         in = a.out;
     }
-    if (actions) launch_argmax(lg, n, actions, s);
     HIP_OK(hipGetLastError());
     return VCS_OK;
 }

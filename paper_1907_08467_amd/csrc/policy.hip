@@ -27,9 +27,10 @@
 // Weights arrive pre-arranged in operand order (see policy_swizzle_index):
 // fragment (k-step s, channel tile j) is 64 x 16 contiguous bytes, lane l's
 // 8 values at l * 16, so a wave reads it as one linear 1 KB access, from LDS
-// for the three convolutions (whole layer staged once per block, at most
-// 72 KB) and from L2 for the two dense layers.  Layer shapes are template
-// constants: every gather offset folds at compile time.
+// for the three convolutions over many envs (whole layer staged once per
+// block, at most 72 KB), from L2 for the dense layers and for the convolutions
+// over few (see launch_policy_layer).  Layer shapes are template constants:
+// every gather offset folds at compile time.
 #include "vcs_device.h"
 
 namespace vcs {
@@ -45,23 +46,29 @@ __device__ __forceinline__ uint32_t f2bf(float f) {   // round to nearest even
 // One layer's shape and blocking.  H: input side, CIN: input channels,
 // KW: kernel side, S: stride, OH: output side, N: outputs, NT: 16-channel
 // tiles (N padded), NBW: channel tiles per wave (grid.y = NT / NBW), MR:
-// 16-position tiles per wave, TPB: block tiles per block.
+// 16-position tiles per wave, TPB: block tiles per block, LDSW: weights staged
+// in LDS, W: waves per block.  The blocking decides only which wave computes an
+// output, never the order of its sum: all blockings of a layer agree bit for bit.
 template <uint32_t H_, uint32_t CIN_, uint32_t KW_, uint32_t S_, uint32_t OH_, uint32_t N_, uint32_t NT_,
-          uint32_t NBW_, uint32_t MR_, uint32_t TPB_, bool FIRST_, bool HEAD_, bool LDSW_>
+          uint32_t NBW_, uint32_t MR_, uint32_t TPB_, bool FIRST_, bool HEAD_, bool LDSW_, uint32_t W_ = 4>
 struct Layer {
     static constexpr uint32_t H = H_, CIN = CIN_, KW = KW_, S = S_, OH = OH_, N = N_, NT = NT_, NBW = NBW_,
-                              MR = MR_, TPB = TPB_;
+                              MR = MR_, TPB = TPB_, W = W_;
     static constexpr bool FIRST = FIRST_, HEAD = HEAD_, LDSW = LDSW_;
-    static constexpr uint32_t K = KW * KW * CIN, KS = K / 32, OHW = OH * OH, ROWS = 64 * MR;
+    static constexpr uint32_t K = KW * KW * CIN, KS = K / 32, OHW = OH * OH, ROWS = 16 * MR * W;
     static_assert(K % 32 == 0 && (FIRST ? KW == 8 : CIN % 32 == 0), "reduction blocking");
     static_assert(NT % NBW == 0, "channel tiles per wave");
 };
 
-using L1 = Layer<84, 4, 8, 4, 20, 32, 2, 2, 4, 4, true, false, true>;
-using L2 = Layer<20, 32, 4, 2, 9, 64, 4, 4, 4, 2, false, false, true>;
-using L3 = Layer<9, 64, 3, 1, 7, 64, 4, 4, 2, 1, false, false, true>;
-using L4 = Layer<7, 64, 7, 1, 1, 512, 32, 4, 1, 1, false, false, false>;
-using L5 = Layer<1, 512, 1, 1, 1, 19, 2, 2, 1, 1, false, true, false>;
+// The blockings that launch_policy_layer chooses from (measured there).
+using L1 = Layer<84, 4, 8, 4, 20, 32, 2, 2, 2, 1, true, false, true, 4>;
+using L2 = Layer<20, 32, 4, 2, 9, 64, 4, 4, 1, 2, false, false, true, 8>;
+using L2Few = Layer<20, 32, 4, 2, 9, 64, 4, 2, 1, 1, false, false, false, 1>;
+using L3 = Layer<9, 64, 3, 1, 7, 64, 4, 4, 1, 2, false, false, true, 8>;
+using L3Few = Layer<9, 64, 3, 1, 7, 64, 4, 2, 1, 1, false, false, false, 1>;
+using L4 = Layer<7, 64, 7, 1, 1, 512, 32, 8, 1, 1, false, false, false, 4>;
+using L4Few = Layer<7, 64, 7, 1, 1, 512, 32, 1, 1, 1, false, false, false, 1>;
+using L5 = Layer<1, 512, 1, 1, 1, 19, 2, 2, 1, 1, false, true, false, 1>;
 
 // the second MFMA operand for k-step s: 8 reduction indices of one position
 template <class L, uint32_t s>
@@ -105,14 +112,14 @@ __device__ __forceinline__ void ksteps(const void* in, const uint64_t (&base)[L:
 }
 
 template <class L>
-__global__ void __launch_bounds__(256) k_policy_layer(PolicyLayerArgs A) {
+__global__ void __launch_bounds__(64 * L::W) k_policy_layer(PolicyLayerArgs A) {
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, q = lane >> 4, p = lane & 15;
     const uint32_t jt0 = blockIdx.y * L::NBW;
     __shared__ bf16x8 sw[L::LDSW ? L::KS * L::NT * 64 : 1];
     const bf16x8* wsrc;
     if constexpr (L::LDSW) {
         const bf16x8* g = reinterpret_cast<const bf16x8*>(A.w);
-        for (uint32_t i = threadIdx.x; i < L::KS * L::NT * 64; i += 256) sw[i] = g[i];
+        for (uint32_t i = threadIdx.x; i < L::KS * L::NT * 64; i += 64 * L::W) sw[i] = g[i];
         __syncthreads();
         wsrc = sw + jt0 * 64 + lane;
     } else {
@@ -161,6 +168,8 @@ __global__ void __launch_bounds__(256) k_policy_layer(PolicyLayerArgs A) {
         for (uint32_t r = 0; r < L::MR; ++r) {
             const uint32_t m = mbase + r * 16 + p;
             if (m >= A.M) continue;
+            float best = 0.f;                              // of the head: the lane's greatest logit
+            uint32_t arg = 0;
 #pragma unroll
             for (uint32_t j = 0; j < L::NBW; ++j) {
                 const uint32_t c0 = (jt0 + j) * 16 + 4 * q;
@@ -169,11 +178,37 @@ __global__ void __launch_bounds__(256) k_policy_layer(PolicyLayerArgs A) {
                 v = v + bias[j];
                 if constexpr (L::HEAD) {
                     *reinterpret_cast<f32x4*>(static_cast<float*>(A.out) + (size_t)m * 32 + c0) = v;
+                    // a scan over the actions never takes a NaN after the first and never leaves one there
+#pragma unroll
+                    for (uint32_t t = 0; t < 4; ++t) {
+                        const uint32_t c = c0 + t;
+                        float l = v[t];
+                        if (l != l) l = c ? -INFINITY : INFINITY;
+                        if (c >= 18) l = -INFINITY;
+                        if ((j == 0 && t == 0) || l > best) {
+                            best = l;
+                            arg = c;
+                        }
+                    }
                 } else {
                     const uint32_t lo = f2bf(v[0] > 0.f ? v[0] : 0.f) | (f2bf(v[1] > 0.f ? v[1] : 0.f) << 16);
                     const uint32_t hi = f2bf(v[2] > 0.f ? v[2] : 0.f) | (f2bf(v[3] > 0.f ? v[3] : 0.f) << 16);
                     *reinterpret_cast<uint2*>(static_cast<uint16_t*>(A.out) + (size_t)m * L::N + c0) = uint2{lo, hi};
                 }
+            }
+            if constexpr (L::HEAD) {
+                // the position's four lanes: the first greatest of their logits
+                static_assert(!L::HEAD || L::NBW == L::NT, "one wave has all logits");
+#pragma unroll
+                for (int x = 16; x < 64; x *= 2) {
+                    const float ob = __shfl_xor(best, x);
+                    const uint32_t oa = __shfl_xor(arg, x);
+                    if (ob > best || (ob == best && oa < arg)) {
+                        best = ob;
+                        arg = oa;
+                    }
+                }
+                if (A.actions && q == 0) A.actions[m] = (uint8_t)arg;
             }
         }
     }
@@ -183,36 +218,33 @@ template <class L>
 static void launch_layer(const PolicyLayerArgs& a, hipStream_t s) {
     const uint32_t per_block = L::ROWS * L::TPB;
     const dim3 grid((a.M + per_block - 1) / per_block, L::NT / L::NBW);
-    hipLaunchKernelGGL(k_policy_layer<L>, grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_policy_layer<L>, grid, dim3(64 * L::W), 0, s, a);
 }
 
-// first maximal logit among the 18 actions; one thread per env
-__global__ void k_argmax(const float* logits, uint32_t n, uint8_t* actions) {
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float* l = logits + (size_t)i * 32;
-    uint32_t best = 0;
-    float bv = l[0];
-    for (uint32_t a = 1; a < 18; ++a)
-        if (l[a] > bv) {
-            bv = l[a];
-            best = a;
-        }
-    actions[i] = (uint8_t)best;
+// Few envs are a matter of latency: one wave per block, with the least work a
+// wave can have and weights from L2, is the faster as long as its waves are no
+// more than about 10 per CU; many envs want each weight and each gathered
+// operand used by more.  Microseconds at n envs, Few against the other blocking:
+//   layer 2:  n = 33: 3.6 / 9.9   256: 10.0 / 10.3   512: 18.0 / 10.9   4096: 124 / 58
+//   layer 3:  n = 33: 4.1 / 11.3  256: 7.5 / 11.6    512: 12.6 / 11.7   4096: 85 / 43
+//   layer 4:  n = 33: 5.4 / 24    256: 8.8 / 34      1024: 29.6 / 38.5  2048: 56 / 40
+// Layers 1 and 5 have one blocking that is within 1 us of the best everywhere
+// (3.5 and 2.7 us at 33, 57 and 3 us at 4096).
+template <class Few, class Many>
+static void launch_few_or_many(const PolicyLayerArgs& a, hipStream_t s) {
+    const uint64_t waves = (uint64_t)((a.M + Few::ROWS - 1) / Few::ROWS) * (Few::NT / Few::NBW);
+    if (waves <= 2560) launch_layer<Few>(a, s);
+    else launch_layer<Many>(a, s);
 }
 
 void launch_policy_layer(int layer, const PolicyLayerArgs& a, hipStream_t s) {
     switch (layer) {
         case 0: launch_layer<L1>(a, s); break;
-        case 1: launch_layer<L2>(a, s); break;
-        case 2: launch_layer<L3>(a, s); break;
-        case 3: launch_layer<L4>(a, s); break;
+        case 1: launch_few_or_many<L2Few, L2>(a, s); break;
+        case 2: launch_few_or_many<L3Few, L3>(a, s); break;
+        case 3: launch_few_or_many<L4Few, L4>(a, s); break;
         default: launch_layer<L5>(a, s); break;
     }
-}
-
-void launch_argmax(const float* logits, uint32_t n, uint8_t* actions, hipStream_t s) {
-    hipLaunchKernelGGL(k_argmax, dim3((n + 255) / 256), dim3(256), 0, s, logits, n, actions);
 }
 
 }  // namespace vcs

@@ -259,6 +259,7 @@ struct PolicyLayerArgs {
     const float* bias;     // [Npad]
     void* out;             // bf16 NHWC [n][OH][OH][N] (hidden) or f32 [n][32] (head)
     uint32_t M;            // n * OH * OH output positions, > 0
+    uint8_t* actions;      // head: NULL or the first maximal action logit of each env
 };
 void launch_policy_layer(int layer, const PolicyLayerArgs& a, hipStream_t s);
 // Where weight (channel c, reduction index k) of a layer with K = 32 KS
@@ -269,7 +270,6 @@ inline size_t policy_swizzle_index(uint32_t c, uint32_t k, uint32_t NT) {
     const uint32_t s = k / 32, j = c / 16, lane = (c % 16) + 16 * ((k % 32) / 8), t = k % 8;
     return (((size_t)s * NT + j) * 64 + lane) * 8 + t;
 }
-void launch_argmax(const float* logits, uint32_t n, uint8_t* actions, hipStream_t s);
 void launch_stack(uint8_t* ring, uint8_t* head, const int32_t* ids, uint32_t n, uint32_t num_envs, uint32_t depth,
                   uint32_t bits, const uint8_t* obs, const uint8_t* done, uint8_t* out, hipStream_t s);
 void launch_step_begin(uint32_t* zero, uint32_t n_zero, uint32_t* tag, uint32_t residue, hipStream_t s);
