@@ -749,90 +749,163 @@ __device__ __forceinline__ void log_close(Cpu& c, const Wave& W, uint32_t t) {
 
 // ------------------------------------------------------------ collisions
 
-// Latches of the pixels of the frame's rows from the scan position
-// (c.cx_row, c.cx_x) up to row_end (pixels of row_end before x_end), from
-// the row log: each row's snapshot and logged writes, 16 pixels at a time.
-__device__ __forceinline__ void cx_scan(Cpu& c, const Wave& W, int32_t row_end, int32_t x_end) {
-    if (row_end > kRows) {
-        row_end = kRows;
-        x_end = 0;
-    }
-    // the last whole row this call scanned: a whole row with the same snapshot
-    // and the same writes draws the same pixels (unless an HMOVE blank falls
-    // on one of the two), so its latch bits are already in c.cx
-    uint4 pa = make_uint4(0, 0, 0, 0), pb = make_uint4(0, 0, 0, 0);
-    uint32_t pcnt = ~0u;
-    const uint32_t* pents = nullptr;
-    while (c.cx_row < row_end || (c.cx_row == row_end && c.cx_x < x_end && row_end < kRows)) {
-        const int32_t r = c.cx_row;
-        const uint32_t xe = r < row_end ? 160u : (uint32_t)x_end;
-        const uint8_t* rec = c.log + r * kSnapBytes;
-        const uint4 sa = reinterpret_cast<const uint4*>(rec)[0], sb = reinterpret_cast<const uint4*>(rec)[1];
-        const uint32_t cnt = r == c.open_row ? c.open_cnt : ((sa.w >> 24) & kCountMask);
-        const uint32_t* ents = reinterpret_cast<const uint32_t*>(c.log + kSnapArea) + (sb.w & 0xFFFF);
-        const bool whole = c.cx_x == 0 && xe == 160;
-        if (whole && cnt == pcnt) {
+// The latches are found by scanning pixels out of the row log, only when a
+// latch is read, when an instruction is fetched from a latch, and at the end of
+// a frame.  Every row's record holds its whole starting state, so the rows of a
+// scan are independent: the lanes that need one post a job each, and all
+// threads of the block (the wave that emulates and the helper waves that wait
+// for it at a barrier) share the jobs' rows.  A wave scanning its own envs' rows,
+// one lane per env, took 6.2 M of the 8.7 M cycles of a 4-frame step of a tile
+// of 64 envs with all objects in motion, on a chip of whose SIMDs 4,096 such
+// envs use 1 in 16; shared by 8 waves, 0.8 M of 3.6 M.
+struct CxJob {
+    uint64_t log;             // the env's row log
+    int32_t row, x;           // scanned so far: the frame's pixels before (row, x)
+    int32_t row_end, x_end;   // to scan: up to there
+    int32_t open_row;         // the row still being logged, and its entries so far
+    uint32_t open_cnt;
+    uint32_t cx;              // the latch bits found
+    uint32_t pad;
+};
+
+constexpr uint32_t kCxPre = 8;
+
+// The share of thread tid, of n_threads, of m jobs (1 <= m <= 64 <= n_threads):
+// each job's rows are cut into as many runs as leave every thread at most one.
+// Neighbouring threads take the same run of different jobs: envs of one ROM
+// mostly log the same registers at the same pixels of a row, so a wave's lanes
+// draw the same objects anew at the same time (lanes on different rows of one
+// env took 3 times as long).
+__device__ __attribute__((noinline)) void cx_scan_share(CxJob* jobs, uint32_t m, uint32_t tid, uint32_t n_threads) {
+    const uint32_t runs = n_threads / m, run = tid / m;
+    if (run >= runs) return;
+    CxJob& J = jobs[tid - run * m];
+    const uint8_t* log = (const uint8_t*)J.log;
+    const int32_t first = J.row, row_end = J.row_end;
+    const int32_t stop = row_end + (J.x_end > 0 ? 1 : 0);
+    const int32_t per = (int32_t)(((uint32_t)(stop - first) + runs - 1) / runs);
+    int32_t r = first + (int32_t)run * per;
+    const int32_t end = min(r + per, stop);
+    if (r >= end) return;
+    // Rows are read ahead, the record two rows and the first kCxPre entries one
+    // row before they are needed: 8 waves on a compute unit do not hide one
+    // round trip to memory per entry (a tenth of a scan's time).  As in the
+    // renderer, the words past a row's last entry are inside the log.
+    const uint32_t* stream = reinterpret_cast<const uint32_t*>(log + kSnapArea);
+    auto record = [&](int32_t row, uint4& a, uint4& b) {
+        const uint4* rec = reinterpret_cast<const uint4*>(log + row * kSnapBytes);
+        a = rec[0];
+        b = rec[1];
+    };
+    auto entries = [&](const uint4& b, uint32_t (&q)[kCxPre]) {
+#pragma unroll
+        for (uint32_t i = 0; i < kCxPre; ++i) q[i] = stream[(b.w & 0xFFFF) + i];
+    };
+    uint4 na, nb, na2 = make_uint4(0, 0, 0, 0), nb2 = na2;
+    uint32_t nq[kCxPre];
+    record(r, na, nb);
+    if (r + 1 < end) record(r + 1, na2, nb2);
+    entries(nb, nq);
+    // the last whole row scanned: a whole row with the same snapshot and the
+    // same writes draws the same pixels (unless an HMOVE blank falls on one of
+    // the two), so its latch bits are already found
+    uint4 pa = make_uint4(0, 0, 0, 0), pb = pa;
+    uint32_t pq[kCxPre] = {};
+    uint32_t pcnt = ~0u, cx = 0;
+    RowObjects O;
+    row_objects_none(O);
+    for (; r < end; ++r) {
+        const uint32_t xs = r == first ? (uint32_t)J.x : 0u, xe = r < row_end ? 160u : (uint32_t)J.x_end;
+        const uint4 sa = na, sb = nb;
+        uint32_t q[kCxPre];
+#pragma unroll
+        for (uint32_t i = 0; i < kCxPre; ++i) q[i] = nq[i];
+        const uint32_t cnt = r == J.open_row ? J.open_cnt : ((sa.w >> 24) & kCountMask);
+        const uint32_t* ents = stream + (sb.w & 0xFFFF);
+        if (r + 1 < end) {
+            na = na2;
+            nb = nb2;
+            entries(nb, nq);
+            if (r + 2 < end) record(r + 2, na2, nb2);
+        }
+        const bool whole = xs == 0 && xe == 160;
+        if (whole && cnt == pcnt && cnt <= kCxPre) {
             const uint32_t hmb = (sb.z >> 8) & 0xFF;
             bool same = sa.x == pa.x && sa.y == pa.y && sa.z == pa.z && ((sa.w ^ pa.w) & 0x80FFFFFFu) == 0 &&
                         sb.x == pb.x && sb.y == pb.y && sb.z == pb.z && ((sb.w ^ pb.w) & 0xFFFF0000u) == 0 &&
                         hmb != (uint32_t)r && hmb != (uint32_t)r + 1;
-            for (uint32_t i = 0; same && i < cnt; ++i) same = ents[i] == pents[i];
-            if (same) {
-                c.cx_row = r + 1;
-                continue;
-            }
+#pragma unroll
+            for (uint32_t i = 0; i < kCxPre; ++i) same = same && (i >= cnt || q[i] == pq[i]);
+            if (same) continue;
         }
+        pcnt = whole ? cnt : ~0u;
+        pa = sa;
+        pb = sb;
+#pragma unroll
+        for (uint32_t i = 0; i < kCxPre; ++i) pq[i] = q[i];
         Regs R;
         unpack(R, sa, sb);
-        uint32_t ei = 0, cur = (uint32_t)c.cx_x;
+        uint32_t ei = 0, cur = xs;           // q[0]: the next write, if ei < cnt
         while (cur < xe) {
-            while (ei < cnt && (ents[ei] & 0xFF) <= cur) apply(R, ents[ei++]);
-            const uint32_t nx = ei < cnt ? min((uint32_t)(ents[ei] & 0xFF), xe) : xe;
-            // only drawn runs, and in them only the segments where two objects can meet
-            uint32_t segs = (R.outside || (rb<R_VBLANK>(R) & 2)) ? 0u : collision_segs(R);
-            segs &= ((2u << ((nx - 1) >> 4)) - 1) & ~((1u << (cur >> 4)) - 1);
-            while (segs) {
-                const uint32_t x0 = 16u * (uint32_t)__builtin_ctz(segs);
-                segs &= segs - 1;
-                uint32_t o[6], shown;
-                objects16(R, x0, (uint32_t)r, o, shown);
-                const uint32_t lo = cur > x0 ? cur - x0 : 0u, hi = nx < x0 + 16 ? nx - x0 : 16u;
-                const uint32_t run = ((1u << hi) - 1) & ~((1u << lo) - 1);
-                c.cx |= collide16(o, shown & run);
+            // writes in effect here; colours, wherever they are, move no object
+            while (ei < cnt && ((q[0] & 0xFF) <= cur || ((q[0] >> 8) & 0xFF) <= R_COLUBK)) {
+                apply(R, q[0]);
+                ++ei;
+#pragma unroll
+                for (uint32_t i = 0; i + 1 < kCxPre; ++i) q[i] = q[i + 1];
+                q[kCxPre - 1] = ei + (kCxPre - 1) < cnt ? ents[ei + (kCxPre - 1)] : 0u;
+            }
+            const uint32_t nx = ei < cnt ? min(q[0] & 0xFF, xe) : xe;
+            if (!(R.outside || (rb<R_VBLANK>(R) & 2))) {
+                row_objects(O, R);
+                cx |= row_collisions(O, rb<R_HMB>(R) == (uint32_t)r + 1 ? max(cur, 8u) : cur, nx);
             }
             cur = nx;
         }
-        if (whole) {
-            pa = sa;
-            pb = sb;
-            pcnt = cnt;
-            pents = ents;
-        } else {
-            pcnt = ~0u;
-        }
-        if (xe == 160) {
-            c.cx_row = r + 1;
-            c.cx_x = 0;
-        } else {
-            c.cx_x = (int32_t)xe;
-        }
+    }
+    if (cx) atomicOr(&J.cx, cx);
+}
+
+// Scan for the lanes with `scan` up to (row_end, x_end).  Called by the whole
+// emulating wave; `jobs` has a place per lane, *n_jobs is the helpers' word.
+__device__ __forceinline__ void cx_scan(Cpu& c, CxJob* jobs, uint32_t* n_jobs, bool scan, int32_t row_end,
+                                        int32_t x_end) {
+    if (row_end >= kRows) {
+        row_end = kRows;
+        x_end = 0;
+    }
+    if (x_end >= 160) {
+        ++row_end;
+        x_end = 0;
+    }
+    const bool work = scan && (c.cx_row < row_end || (c.cx_row == row_end && c.cx_x < x_end));
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(work);
+    if (mask == 0) return;
+    const uint32_t m = (uint32_t)__builtin_popcountll(mask);
+    const uint32_t place = (uint32_t)__builtin_popcountll(mask & ((1ull << (threadIdx.x & 63)) - 1));
+    if (work) jobs[place] = CxJob{(uint64_t)c.log, c.cx_row, c.cx_x, row_end, x_end, c.open_row, c.open_cnt, 0u, 0u};
+    *n_jobs = m;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the log's stores, the hot loop's too
+    __syncthreads();
+    cx_scan_share(jobs, m, threadIdx.x, blockDim.x);
+    __syncthreads();
+    if (work) {
+        c.cx |= jobs[place].cx;
+        c.cx_row = row_end;
+        c.cx_x = x_end;
     }
 }
 
 // Scan the pixels through colour clock `through` (relative to the base line)
-// into the latches; the rows the beam has reached get their snapshots first
-// (as the next logged write would take them).  through < 0: the whole frame
-// (its log is complete).
-__device__ __forceinline__ void cx_catch_up(Cpu& c, const Wave& W, int32_t through) {
-    if (through < 0) {
-        cx_scan(c, W, kRows, 0);
-        return;
-    }
+// into the latches, for the lanes with `scan`; the rows the beam has reached
+// get their snapshots first (as the next logged write would take them).
+__device__ __forceinline__ void cx_catch_up(Cpu& c, const Wave& W, CxJob* jobs, uint32_t* n_jobs, bool scan,
+                                            int32_t through) {
     const int32_t line = through / 228, h = through % 228;
     const int32_t row = line - c.fl - kFirstRow;
-    if (row < 0) return;
-    log_advance(c, W, h >= 68 ? row : row - 1);
-    cx_scan(c, W, row, h >= 68 ? h - 68 + 1 : 0);
+    scan = scan && row >= 0;
+    if (scan) log_advance(c, W, h >= 68 ? row : row - 1);
+    cx_scan(c, jobs, n_jobs, scan, row, h >= 68 ? h - 68 + 1 : 0);
 }
 
 // Position a RESPx (players, +5) or RESMx / RESBL (+4) write at cycle t sets.
@@ -1579,6 +1652,17 @@ __device__ __forceinline__ uint32_t take_tile(uint32_t* queue) {
     return __builtin_amdgcn_readfirstlane(t);
 }
 
+// Orders LDS accesses between the lanes of the emulating wave (its helpers, if
+// any, wait at the block's barrier meanwhile).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Waves of a block that tracks collisions, at most: one emulates, the others
+// share its scans.
+constexpr int kScanWaves = 8;
+
 // LL = envs a tile may hold (64 or 32): RAM and TIA registers get LL + 1
 // slots in LDS (lanes at LL and above, always idle, share the last one), so
 // narrow tiles take less LDS and more waves fit on a compute unit.
@@ -1592,10 +1676,23 @@ __device__ __forceinline__ uint32_t take_tile(uint32_t* queue) {
 // step counter stays); a separate instantiation, so the step's kernel keeps
 // its code.
 template <int LL, int RC, bool TRACK, bool NOOPS>
-__global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t* __restrict__ pre_all) {
+__global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes) k_interp(InterpArgs A, const uint32_t* __restrict__ pre_all) {
     __shared__ uint32_t s_rom[RC ? RC / 4 + 4 : 1];
     __shared__ uint32_t s_ram[(LL + 1) * kRamStride / 4];
     __shared__ uint32_t s_tia[(LL + 1) * kTiaStride / 4];
+    __shared__ CxJob s_jobs[TRACK ? kLanes : 1];
+    __shared__ uint32_t s_njobs;              // jobs to scan, or 0: the block is done
+    if constexpr (TRACK) {
+        if (threadIdx.x >= (uint32_t)kLanes) {     // a helper wave: scans until the emulating wave is done
+            for (;;) {
+                __syncthreads();
+                const uint32_t m = __builtin_amdgcn_readfirstlane(s_njobs);
+                if (m == 0) return;
+                cx_scan_share(s_jobs, m, threadIdx.x, blockDim.x);
+                __syncthreads();
+            }
+        }
+    }
 
     const uint32_t n_tiles = *A.n_tiles;
     uint32_t tile_id = A.queue ? take_tile(A.queue) : blockIdx.x;
@@ -1669,7 +1766,7 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
             if (A.nframes_per_out) nfr = A.nframes_per_out[out];
             sticky_prefix = rng_prefix(A.seed, (uint64_t)env, kStickyPurpose);
         }
-        __syncthreads();
+        wave_sync();
         score0 = active ? W.ram[c.ram_off + 0x50] : 0;
         c.base = base_line * 76;
         c.icount = 0;
@@ -1784,6 +1881,13 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
                 continue;
             }
             const bool go = in;
+            const bool away = !((c.pc & 0x1000) && (c.pc & 0xFFF) <= 0xFFD);   // not fetched from one bank
+            if constexpr (TRACK) {
+                // bytes fetched from the TIA read registers show the latches
+                // through the fetch cycle's pixels, 3t+2
+                const bool scan = go && away && c.cyc < c.cap;
+                if (__any(scan)) cx_catch_up(c, W, s_jobs, &s_njobs, scan, 3 * (int32_t)c.cyc + 2);
+            }
             if (go) {
                 if (c.cyc >= c.cap) {
                     c.err |= ERR_FRAME_CAP;
@@ -1792,7 +1896,7 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
                 } else {
                     const uint32_t pc = c.pc;
                     const uint32_t off = pc & 0xFFF;
-                    if ((pc & 0x1000) && off <= 0xFFD) {
+                    if (!away) {
                         uint32_t v;
                         if (cm_kind(W) == CART_LINEAR) {   // the 4 KB bank is contiguous in LDS
                             const uint32_t boff = (c.bank << 12) | off;
@@ -1807,9 +1911,6 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
                         b1 = (v >> 8) & 0xFF;
                         b2 = (v >> 16) & 0xFF;
                     } else {
-                        // bytes fetched from the TIA read registers show the
-                        // latches through the fetch cycle's pixels, 3t+2
-                        if constexpr (TRACK) cx_catch_up(c, W, 3 * (int32_t)c.cyc + 2);
                         op = peek(c, W, pc, c.cyc);
                         b1 = peek(c, W, pc + 1, c.cyc);
                         b2 = peek(c, W, pc + 2, c.cyc);
@@ -1828,6 +1929,13 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
             uint32_t ran_lane = 0;
             while (__any(todo)) {
                 ++passes;
+                if constexpr (TRACK) {
+                    const bool again = todo && c.cx_need >= 0;   // an instruction that read the latches runs again
+                    if (__any(again)) {
+                        cx_catch_up(c, W, s_jobs, &s_njobs, again, c.cx_need);
+                        if (again) c.cx_need = -1;
+                    }
+                }
                 if (todo) {
                     const uint32_t sop = __builtin_amdgcn_readfirstlane(op);
                     // an opaque scalar copy: inside the branch below the compiler
@@ -1837,12 +1945,6 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
                     uint32_t d = kDecode.w[sw];
                     asm volatile("" : "+s"(d));
                     if (op == sop) {
-                        if constexpr (TRACK) {
-                            if (c.cx_need >= 0) {   // the second run of an instruction that read the latches
-                                cx_catch_up(c, W, c.cx_need);
-                                c.cx_need = -1;
-                            }
-                        }
                         const uint32_t sa = c.a, sx = c.x, sy = c.y, ssp = c.sp, sp_ = c.p, spc = c.pc,
                                        scy = c.cyc, sbk = c.bank;
                         exec_generic(d, c, W, b1, b2);
@@ -1882,15 +1984,21 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
                 ended = true;
                 end_t = c.cyc;
             }
-            if (ended) {
-                if (c.log) {
+            if constexpr (TRACK) {
+                if (__any(ended)) {                // the latches take the frame's remaining rows
                     uint8_t* lg = c.log;
-                    log_close(c, W, end_t);
-                    if constexpr (TRACK) {         // the latches take the frame's remaining rows
+                    const bool close = ended && c.log;
+                    if (close) {
+                        log_close(c, W, end_t);
                         c.log = lg;
-                        cx_catch_up(c, W, -1);
-                        c.log = nullptr;
                     }
+                    cx_scan(c, s_jobs, &s_njobs, close, kRows, 0);
+                    if (close) c.log = nullptr;
+                }
+            }
+            if (ended) {
+                if constexpr (!TRACK) {
+                    if (c.log) log_close(c, W, end_t);
                 }
                 c.fl = (int32_t)(end_t / 76);
                 ++k;
@@ -1955,8 +2063,12 @@ __global__ void __launch_bounds__(kLanes) k_interp(InterpArgs A, const uint32_t*
             atomicAdd(&A.instr_total[3], (unsigned long long)rounds);
         }
         if (!A.queue) break;
-        __syncthreads();   // every lane is done with the LDS of this tile
+        wave_sync();   // every lane is done with the LDS of this tile
         tile_id = take_tile(A.queue);
+    }
+    if constexpr (TRACK) {                    // the helpers leave
+        s_njobs = 0;
+        __syncthreads();
     }
 }
 
@@ -2033,17 +2145,24 @@ void launch_predecode(const uint8_t* rom, const RomInfo& info, uint32_t* pre, hi
     hipLaunchKernelGGL(k_predecode, dim3((n + 255) / 256), dim3(256), 0, s, rom, info, pre);
 }
 
+// Waves per block of a launch that tracks collisions: as many as the chip can
+// hold at once for that many tiles.
+static int scan_waves(uint32_t tiles) {
+    return tiles <= 256 ? 8 : (tiles <= 512 ? 4 : (tiles <= 1024 ? 2 : 1));
+}
+
 template <bool TRACK, bool NOOPS>
 static void launch_interp_t(const InterpArgs& a, uint32_t grid, uint32_t tile_envs, uint32_t rom_lds, hipStream_t s) {
+    const dim3 block(TRACK ? kLanes * scan_waves(grid) : kLanes);
     if (rom_lds == 0) {
         if (tile_envs <= 32)
-            hipLaunchKernelGGL((k_interp<32, 0, TRACK, NOOPS>), dim3(grid), dim3(kLanes), 0, s, a, a.pre);
+            hipLaunchKernelGGL((k_interp<32, 0, TRACK, NOOPS>), dim3(grid), block, 0, s, a, a.pre);
         else
-            hipLaunchKernelGGL((k_interp<64, 0, TRACK, NOOPS>), dim3(grid), dim3(kLanes), 0, s, a, a.pre);
+            hipLaunchKernelGGL((k_interp<64, 0, TRACK, NOOPS>), dim3(grid), block, 0, s, a, a.pre);
     } else if (tile_envs <= 32) {
-        hipLaunchKernelGGL((k_interp<32, 8192, TRACK, NOOPS>), dim3(grid), dim3(kLanes), 0, s, a, a.pre);
+        hipLaunchKernelGGL((k_interp<32, 8192, TRACK, NOOPS>), dim3(grid), block, 0, s, a, a.pre);
     } else {
-        hipLaunchKernelGGL((k_interp<64, 8192, TRACK, NOOPS>), dim3(grid), dim3(kLanes), 0, s, a, a.pre);
+        hipLaunchKernelGGL((k_interp<64, 8192, TRACK, NOOPS>), dim3(grid), block, 0, s, a, a.pre);
     }
 }
 

@@ -1,7 +1,7 @@
-// The TIA's objects over 16-pixel segments of a row, from a row snapshot
-// (R[0..31]) and the register writes logged inside the row.  Used by the
-// render kernels (colours) and by the interpreter's collision scan (which
-// objects meet).
+// The TIA's objects over a row's pixels, from a row snapshot (R[0..31]) and
+// the register writes logged inside the row: over 16-pixel segments for the
+// render kernels (colours), over the whole row for the interpreter's collision
+// scan (which objects meet).
 //
 // Objects (TIA register definitions, with the conventions of this library):
 // the playfield (20 bits PF0 D4..D7, PF1 D7..D0, PF2 D0..D7 over 4-pixel
@@ -214,84 +214,148 @@ __device__ __forceinline__ void objects16(const Regs& r, uint32_t x0, uint32_t r
     o[5] = missile16(rb<R_M1X>(r), ((flags >> 1) & 1) && !(rb<R_FLAGS2>(r) & 1), rb<R_NUSIZ1>(r), x0);
 }
 
-// 10-bit mask of the 16-pixel segments that pixels [start, start + width)
-// (mod 160, width <= 32) touch
-__device__ __forceinline__ uint32_t span_segs(uint32_t start, uint32_t width) {
-    const uint32_t end = start + width - 1;
-    const uint32_t from = ~((1u << (start >> 4)) - 1);
-    if (end < 160) return ((2u << (end >> 4)) - 1) & from;
-    return (0x3FFu & from) | ((2u << ((end - 160) >> 4)) - 1);
+// A row's objects as masks of its 160 pixels (five words each): o[0] PF, o[1]
+// BL, o[2] P0, o[3] P1, o[4] M0, o[5] M1, and for each the registers it was
+// drawn from (a register write changes one or two objects; the others' masks
+// stay).  Segment by segment, with the players drawn anew in each, a scanned
+// row with all objects on took 20,000 cycles of a wave, of which these take
+// a quarter.
+struct RowObjects {
+    uint32_t o[6][5];
+    uint32_t key[6];
+};
+
+__device__ __forceinline__ void row_objects_none(RowObjects& O) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        O.key[k] = 0;
+#pragma unroll
+        for (int i = 0; i < 5; ++i) O.o[k][i] = 0;
+    }
 }
 
-__device__ __forceinline__ uint32_t copies_segs(uint32_t pos, uint32_t mode, uint32_t n, uint32_t width) {
+// pattern `pat` (bit i = pixel start + i) into the row mask m; the row is five
+// whole words, so what passes its end wraps into word 0
+__device__ __forceinline__ void place_row(uint32_t (&m)[5], uint32_t pat, uint32_t start) {
+    const uint64_t t = (uint64_t)pat << (start & 31);
+    const uint32_t k = start >> 5, lo = (uint32_t)t, hi = (uint32_t)(t >> 32);
+#pragma unroll
+    for (uint32_t i = 0; i < 5; ++i) m[i] |= (k == i ? lo : 0u) | (k == (i + 4) % 5 ? hi : 0u);
+}
+
+// the copies of NUSIZ mode (n of them) of a pattern at pos
+__device__ __forceinline__ void place_copies(uint32_t (&m)[5], uint32_t pat, uint32_t pos, uint32_t mode, uint32_t n) {
     const uint32_t offs = copy_offsets(mode);
-    uint32_t m = 0;
-    for (uint32_t k = 0; k < n; ++k) {
+#pragma unroll
+    for (uint32_t i = 0; i < 5; ++i) m[i] = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 3; ++k) {
         uint32_t st = pos + ((offs >> (8 * k)) & 0xFF);
         st = st >= 160 ? st - 160 : st;
-        m |= span_segs(st, width);
+        place_row(m, k < n ? pat : 0u, st);
     }
-    return m;
 }
 
-// The segments of a row where two objects can meet under registers r: where
-// the extents of two of the players, missiles and ball overlap, or one of
-// them overlaps a playfield block that is set.  Every collision pair has a
-// player, missile or ball in it, so no latch can be set elsewhere.
-__device__ __forceinline__ uint32_t collision_segs(const Regs& r) {
+// every bit of an 8-bit pattern over two / four pixels
+__device__ __forceinline__ uint32_t widen2(uint32_t x) {
+    x = (x | (x << 4)) & 0x0F0Fu;
+    x = (x | (x << 2)) & 0x3333u;
+    x = (x | (x << 1)) & 0x5555u;
+    return x | (x << 1);
+}
+__device__ __forceinline__ uint32_t widen4(uint32_t x) {
+    x = (x | (x << 12)) & 0x000F000Fu;
+    x = (x | (x << 6)) & 0x03030303u;
+    x = (x | (x << 3)) & 0x11111111u;
+    return (x << 4) - x;
+}
+
+// Bring the masks up to registers r.  A mask is redrawn when any lane's
+// registers for it changed (for the other lanes that draws it as it is).
+__device__ __forceinline__ void row_objects(RowObjects& O, const Regs& r) {
     const uint32_t ctrlpf = rb<R_CTRLPF>(r), flags = rb<R_FLAGS>(r);
-    uint32_t m[5];
+    const uint32_t kpf = r.pfm | ((ctrlpf & 1) << 20);
+    if (__any(kpf != O.key[0])) {
+        O.key[0] = kpf;
+        const uint64_t right = (ctrlpf & 1) ? __builtin_bitreverse32(r.pfm) >> 12 : r.pfm;
+        const uint64_t blocks = r.pfm | (right << 20);
+#pragma unroll
+        for (int i = 0; i < 5; ++i) O.o[0][i] = widen4((uint32_t)(blocks >> (8 * i)) & 0xFF);
+    }
+    const bool bl_on = (((flags >> 6) & 1) ? (flags >> 3) : (flags >> 2)) & 1;
+    const uint32_t kbl = bl_on ? 1u | (ctrlpf & 0x30) | ((uint32_t)rb<R_BLX>(r) << 8) : 0u;
+    if (__any(kbl != O.key[1])) {
+        O.key[1] = kbl;
+        const uint32_t size = 1u << ((ctrlpf >> 4) & 3);
+        place_copies(O.o[1], kbl ? (1u << size) - 1 : 0u, rb<R_BLX>(r), 0, 1);
+    }
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const uint32_t nus = i ? rb<R_NUSIZ1>(r) : rb<R_NUSIZ0>(r), mode = nus & 7;
         const uint32_t grp = ((flags >> (4 + i)) & 1) ? (i ? rb<R_GRP1_OLD>(r) : rb<R_GRP0_OLD>(r))
                                                      : (i ? rb<R_GRP1>(r) : rb<R_GRP0>(r));
-        const uint32_t pw = mode == 5 ? 16u : (mode == 7 ? 32u : 8u);
-        m[i] = grp ? copies_segs(i ? rb<R_P1X>(r) : rb<R_P0X>(r), mode, copy_count(mode), pw) : 0u;
+        const uint32_t refp = (i ? rb<R_REFP1>(r) : rb<R_REFP0>(r)) & 8, px = i ? rb<R_P1X>(r) : rb<R_P0X>(r);
+        const uint32_t kp = grp ? grp | (px << 8) | (mode << 16) | (refp << 20) : 0u;
+        if (__any(kp != O.key[2 + i])) {
+            O.key[2 + i] = kp;
+            const uint32_t spr = refp ? grp : (__builtin_bitreverse32(grp) >> 24);   // bit d = sprite pixel d
+            const uint32_t pat = mode == 5 ? widen2(spr) : (mode == 7 ? widen4(spr) : spr);
+            place_copies(O.o[2 + i], pat, px, mode, copy_count(mode));
+        }
         const bool mon = ((flags >> i) & 1) && !(i ? (rb<R_FLAGS2>(r) & 1) : ((flags >> 7) & 1));
-        m[2 + i] = mon ? copies_segs(i ? rb<R_M1X>(r) : rb<R_M0X>(r), mode,
-                                     (mode == 5 || mode == 7) ? 1u : copy_count(mode), 1u << ((nus >> 4) & 3))
-                       : 0u;
+        const uint32_t mx = i ? rb<R_M1X>(r) : rb<R_M0X>(r);
+        const uint32_t km = mon ? 0x100u | (nus & 0x37) | (mx << 16) : 0u;
+        if (__any(km != O.key[4 + i])) {
+            O.key[4 + i] = km;
+            const uint32_t size = 1u << ((nus >> 4) & 3);
+            place_copies(O.o[4 + i], km ? (1u << size) - 1 : 0u, mx, mode,
+                         (mode == 5 || mode == 7) ? 1u : copy_count(mode));
+        }
     }
-    const bool bl_on = (((flags >> 6) & 1) ? (flags >> 3) : (flags >> 2)) & 1;
-    m[4] = bl_on ? span_segs(rb<R_BLX>(r), 1u << ((ctrlpf >> 4) & 3)) : 0u;
-    uint32_t one = 0, two = 0;
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-        two |= one & m[i];
-        one |= m[i];
-    }
-    uint32_t pf = 0;                               // segments with a playfield block set
-#pragma unroll
-    for (int k = 0; k < 5; ++k) pf |= (((r.pfm >> (4 * k)) & 0xF) != 0 ? 1u : 0u) << k;
-    if (!(ctrlpf & 1)) {
-        pf |= pf << 5;
-    } else {
-#pragma unroll
-        for (int j = 0; j < 5; ++j) pf |= ((pf >> (4 - j)) & 1) << (5 + j);
-    }
-    return two | (one & pf);
 }
 
-// collision latch bits for the pixels in `px` (a 16-bit mask)
-__device__ __forceinline__ uint32_t collide16(const uint32_t (&o)[6], uint32_t px) {
-    const uint32_t pf = o[0] & px, bl = o[1] & px, p0 = o[2] & px, p1 = o[3] & px, m0 = o[4] & px, m1 = o[5] & px;
+// collision latch bits of the pixels [from, to) of the row (to <= 160)
+__device__ __forceinline__ uint32_t row_collisions(const RowObjects& O, uint32_t from, uint32_t to) {
+    uint32_t mp0p = 0, mp0q = 0, mp1q = 0, mp1p = 0, p0f = 0, p0b = 0, p1f = 0, p1b = 0, m0f = 0, m0b = 0, m1f = 0,
+             m1b = 0, bf = 0, pp = 0, mm = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < 5; ++i) {
+        const uint32_t a = from > 32 * i ? from - 32 * i : 0u, b = to > 32 * i ? to - 32 * i : 0u;
+        const uint32_t px = (b >= 32 ? ~0u : (1u << b) - 1) & ~(a >= 32 ? ~0u : (1u << a) - 1);
+        const uint32_t pf = O.o[0][i], bl = O.o[1][i] & px, p0 = O.o[2][i] & px, p1 = O.o[3][i] & px;
+        const uint32_t m0 = O.o[4][i] & px, m1 = O.o[5][i] & px;
+        mp0p |= m0 & p1;
+        mp0q |= m0 & p0;
+        mp1q |= m1 & p0;
+        mp1p |= m1 & p1;
+        p0f |= p0 & pf;
+        p0b |= p0 & bl;
+        p1f |= p1 & pf;
+        p1b |= p1 & bl;
+        m0f |= m0 & pf;
+        m0b |= m0 & bl;
+        m1f |= m1 & pf;
+        m1b |= m1 & bl;
+        bf |= bl & pf;
+        pp |= p0 & p1;
+        mm |= m0 & m1;
+    }
     uint32_t cx = 0;
-    cx |= (m0 & p1) ? 1u << 1 : 0u;      // CXM0P
-    cx |= (m0 & p0) ? 1u << 0 : 0u;
-    cx |= (m1 & p0) ? 1u << 3 : 0u;      // CXM1P
-    cx |= (m1 & p1) ? 1u << 2 : 0u;
-    cx |= (p0 & pf) ? 1u << 5 : 0u;      // CXP0FB
-    cx |= (p0 & bl) ? 1u << 4 : 0u;
-    cx |= (p1 & pf) ? 1u << 7 : 0u;      // CXP1FB
-    cx |= (p1 & bl) ? 1u << 6 : 0u;
-    cx |= (m0 & pf) ? 1u << 9 : 0u;      // CXM0FB
-    cx |= (m0 & bl) ? 1u << 8 : 0u;
-    cx |= (m1 & pf) ? 1u << 11 : 0u;     // CXM1FB
-    cx |= (m1 & bl) ? 1u << 10 : 0u;
-    cx |= (bl & pf) ? 1u << 13 : 0u;     // CXBLPF
-    cx |= (p0 & p1) ? 1u << 15 : 0u;     // CXPPMM
-    cx |= (m0 & m1) ? 1u << 14 : 0u;
+    cx |= mp0p ? 1u << 1 : 0u;       // CXM0P
+    cx |= mp0q ? 1u << 0 : 0u;
+    cx |= mp1q ? 1u << 3 : 0u;       // CXM1P
+    cx |= mp1p ? 1u << 2 : 0u;
+    cx |= p0f ? 1u << 5 : 0u;        // CXP0FB
+    cx |= p0b ? 1u << 4 : 0u;
+    cx |= p1f ? 1u << 7 : 0u;        // CXP1FB
+    cx |= p1b ? 1u << 6 : 0u;
+    cx |= m0f ? 1u << 9 : 0u;        // CXM0FB
+    cx |= m0b ? 1u << 8 : 0u;
+    cx |= m1f ? 1u << 11 : 0u;       // CXM1FB
+    cx |= m1b ? 1u << 10 : 0u;
+    cx |= bf ? 1u << 13 : 0u;        // CXBLPF
+    cx |= pp ? 1u << 15 : 0u;        // CXPPMM
+    cx |= mm ? 1u << 14 : 0u;
     return cx;
 }
 
