@@ -270,12 +270,11 @@ __device__ __forceinline__ uint32_t widen4(uint32_t x) {
     return (x << 4) - x;
 }
 
-// Bring the masks up to registers r.  A mask is redrawn when any lane's
-// registers for it changed (for the other lanes that draws it as it is).
+// Bring the masks up to registers r: those whose registers changed.
 __device__ __forceinline__ void row_objects(RowObjects& O, const Regs& r) {
     const uint32_t ctrlpf = rb<R_CTRLPF>(r), flags = rb<R_FLAGS>(r);
     const uint32_t kpf = r.pfm | ((ctrlpf & 1) << 20);
-    if (__any(kpf != O.key[0])) {
+    if (kpf != O.key[0]) {
         O.key[0] = kpf;
         const uint64_t right = (ctrlpf & 1) ? __builtin_bitreverse32(r.pfm) >> 12 : r.pfm;
         const uint64_t blocks = r.pfm | (right << 20);
@@ -284,7 +283,7 @@ __device__ __forceinline__ void row_objects(RowObjects& O, const Regs& r) {
     }
     const bool bl_on = (((flags >> 6) & 1) ? (flags >> 3) : (flags >> 2)) & 1;
     const uint32_t kbl = bl_on ? 1u | (ctrlpf & 0x30) | ((uint32_t)rb<R_BLX>(r) << 8) : 0u;
-    if (__any(kbl != O.key[1])) {
+    if (kbl != O.key[1]) {
         O.key[1] = kbl;
         const uint32_t size = 1u << ((ctrlpf >> 4) & 3);
         place_copies(O.o[1], kbl ? (1u << size) - 1 : 0u, rb<R_BLX>(r), 0, 1);
@@ -296,7 +295,7 @@ __device__ __forceinline__ void row_objects(RowObjects& O, const Regs& r) {
                                                      : (i ? rb<R_GRP1>(r) : rb<R_GRP0>(r));
         const uint32_t refp = (i ? rb<R_REFP1>(r) : rb<R_REFP0>(r)) & 8, px = i ? rb<R_P1X>(r) : rb<R_P0X>(r);
         const uint32_t kp = grp ? grp | (px << 8) | (mode << 16) | (refp << 20) : 0u;
-        if (__any(kp != O.key[2 + i])) {
+        if (kp != O.key[2 + i]) {
             O.key[2 + i] = kp;
             const uint32_t spr = refp ? grp : (__builtin_bitreverse32(grp) >> 24);   // bit d = sprite pixel d
             const uint32_t pat = mode == 5 ? widen2(spr) : (mode == 7 ? widen4(spr) : spr);
@@ -305,7 +304,7 @@ __device__ __forceinline__ void row_objects(RowObjects& O, const Regs& r) {
         const bool mon = ((flags >> i) & 1) && !(i ? (rb<R_FLAGS2>(r) & 1) : ((flags >> 7) & 1));
         const uint32_t mx = i ? rb<R_M1X>(r) : rb<R_M0X>(r);
         const uint32_t km = mon ? 0x100u | (nus & 0x37) | (mx << 16) : 0u;
-        if (__any(km != O.key[4 + i])) {
+        if (km != O.key[4 + i]) {
             O.key[4 + i] = km;
             const uint32_t size = 1u << ((nus >> 4) & 3);
             place_copies(O.o[4 + i], km ? (1u << size) - 1 : 0u, mx, mode,
