@@ -23,13 +23,18 @@
 //  * decimal ADC/SBC follow the NMOS behaviour described by B. Clark
 //    ("Decimal Mode", 6502.org, Appendix A).
 //
-// Dispatch: each loop iteration every running lane fetches its next opcode;
-// the wave then executes one opcode at a time for all lanes that share it
-// (readfirstlane + compare), so the opcode's decode word is a scalar and the
-// addressing-mode and operation switches of the one generic executor are
-// scalar branches.  In lockstep (the common case for envs of one ROM) that is
-// a single pass.  TIA writes are queued during the pass and applied in one
-// shared block afterwards.
+// Dispatch: the running lanes at one place (bank, pc, cycle, frame line) form a
+// group, which the hot loop (hotloop.h) runs as threaded code with its control
+// state in scalars, one group after the other in order of emulated time; groups
+// part at data-dependent branches and meet again there.  An instruction the hot
+// loop does not cover goes once through the full scalar dispatch (run_cold).
+// What that refuses -- undocumented opcodes, latch reads, lanes that disagree
+// about a bank or the decimal mode, code outside the cartridge window -- goes
+// through the per-lane path: the wave executes one opcode at a time for all
+// lanes that share it (readfirstlane + compare), so the opcode's decode word is
+// a scalar and the addressing-mode and operation switches of the one generic
+// executor are scalar branches; TIA writes are queued during the pass and
+// applied in one shared block afterwards.
 #include "tia_draw.h"
 #include "hotloop.h"
 
