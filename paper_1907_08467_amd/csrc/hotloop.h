@@ -621,6 +621,7 @@ __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uin
         "s_movk_i32 s69, 1696+5280-31\n"
         "s_mov_b32 s98, (3<<25)+1\n"
         "s_mov_b32 s99, (4<<25)+1\n"
+        "s_mov_b32 s56, 0x7fffffff\n"             // no group picked yet
         // --- groups of the lanes in s[48:49]
         ".Lform%=:\n"
         "s_ff1_i32_b64 s93, s[48:49]\n"
@@ -638,7 +639,6 @@ __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uin
         "s_cbranch_scc0 .Lrun%=\n"                 // one group, none waiting
         ".Lforw%=:\n"
         HL_PUT
-        "s_mov_b32 s56, 0x7fffffff\n"
         "s_cmp_lg_u64 s[48:49], 0\n"
         "s_cbranch_scc1 .Lform%=\n"
         // --- the next group: the earliest (s56: the last one's time)
