@@ -10,13 +10,12 @@ SRC = os.path.join(HERE, "csrc")
 OUT_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libvcs355.so")
 SOURCES = ["interp.hip", "render.hip", "envops.hip", "stack.hip", "policy.hip", "api.hip"]
-# Control flow that the compiler can prove wave-uniform (the interpreter's
-# scalar loop) is left as plain scalar branches instead of being rewritten into
-# the structured form divergent code needs, which would add a copy of every
-# live value at each merge point.
+# No -mllvm options: with -structurizecfg-skip-uniform-regions=true a
+# wave-uniform branch around per-lane work gave wrong frames, and which forms
+# are safe under it is nowhere stated.  It is worth 1-2 % of a step (4,096 envs:
+# 1,361 us with it, 1,382 without).
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-         "-mllvm", "-structurizecfg-skip-uniform-regions=true",
          "-I", os.path.join(ROOT, "include")]
 
 
