@@ -776,7 +776,8 @@ int vcs_load_roms(vcs_ctx* c, uint32_t n_roms, const uint8_t* const* rom_host, c
     HIP_OK(hipMemcpy(c->d_cmap, cmap.data(), n_roms * sizeof(CartMap), hipMemcpyHostToDevice));
     HIP_OK(hipMemcpy(c->d_pre_off, pre_off.data(), n_roms * 4, hipMemcpyHostToDevice));
     for (uint32_t r = 0; r < n_roms; ++r)
-        launch_predecode(c->d_roms + (size_t)r * kRomSlot, c->h_rinfo[r], c->d_pre + c->h_rinfo[r].pre_off, nullptr);
+        launch_predecode(c->d_roms + (size_t)r * kRomSlot, c->h_rinfo[r], c->d_pre + c->h_rinfo[r].pre_off,
+                         c->cfg.collisions ? 1u : 0u, nullptr);
     HIP_OK(hipGetLastError());
     HIP_OK(hipDeviceSynchronize());
     return VCS_OK;

@@ -62,8 +62,21 @@ constexpr uint32_t HOT_REAL = 0, HOT_STA_TIA = 1,
                    HOT_XR_ADC = 54, HOT_XR_AND = 55, HOT_XR_EOR = 56, HOT_XR_ORA = 57, HOT_XW = 58,
                    HOT_ABS = 59, HOT_HS = 60, HOT_HMP = 61, HOT_VSYNC = 67, HOT_INPT4 = 68,
                    HOT_SWCHA_LDA = 69, HOT_SWCHA_EOR = 70, HOT_WSYNC = 71, HOT_ST_NOP = 72, HOT_BPL_X = 73,
-                   kHotPlain = 81;
-constexpr uint32_t kHotSlots = 140;
+                   kHotPlain = 81,
+                   HOT_JSR = 147, HOT_RESP = 149, HOT_RESM = 150, HOT_FLAG_X = 151, HOT_FLAG_Y = 157, HOT_3F = 163,
+                   HOT_E0 = 166, HOT_HS_ST = 168, HOT_Z_CONST = 169, HOT_Z_INPT4 = 170, HOT_A_CONST = 171,
+                   HOT_A_SWCHA = 172, HOT_A_INTIM = 173, HOT_A_ROM = 175, HOT_A_RAM = 177, HOT_ZX = 178,
+                   HOT_ZY = 179, HOT_ZX_RMW = 180, HOT_AX_ROM = 181, HOT_AY_ROM = 183, HOT_AX_RAM = 185,
+                   HOT_AY_RAM = 186, HOT_IY_ROM = 187, HOT_A_RMW = 189, HOT_SEG = 190, HOT_SEG_X = 191, HOT_SEG_Y = 192,
+                   HOT_STA_ZX = 193, HOT_STY_ZX = 194, HOT_STX_ZY = 195, HOT_STA_AX = 196, HOT_STA_AY = 197,
+                   HOT_STA_A = 198, HOT_STX_A = 199, HOT_STY_A = 200, HOT_A_TIA = 201, HOT_PHP = 210, HOT_PLP = 212;
+// The two-step reads: HOT_Z_CONST .. HOT_SEG_Y fetch the operand (the word's
+// class: the operation's number, and for the constants which one << 5) and go
+// on to the operation, slot kHotWork + its number.
+constexpr uint32_t kHotWork = 214, kHotWorks = 18;
+enum : uint32_t { HW_LDA, HW_LDX, HW_LDY, HW_AND, HW_ORA, HW_EOR, HW_CMP, HW_CPX, HW_CPY, HW_BIT, HW_ADC, HW_SBC,
+                  HW_ASL, HW_ROL, HW_LSR, HW_ROR, HW_DEC, HW_INC, HW_NONE };
+constexpr uint32_t kHotSlots = kHotWork + kHotWorks;
 constexpr uint8_t kHotSlotOp[kHotSlots] = {
     0x00, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85,
     0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85, 0x85,
@@ -73,12 +86,18 @@ constexpr uint8_t kHotSlotOp[kHotSlots] = {
     0xF0, 0x05, 0x06, 0x09, 0x0A, 0x10, 0x18, 0x24, 0x25, 0x26, 0x29, 0x2A, 0x30, 0x38, 0x45, 0x46,
     0x49, 0x4A, 0x4C, 0x50, 0x65, 0x66, 0x69, 0x6A, 0x70, 0x84, 0x85, 0x86, 0x88, 0x8A, 0x90, 0x98,
     0xA0, 0xA2, 0xA4, 0xA5, 0xA6, 0xA8, 0xA9, 0xAA, 0xB0, 0xB8, 0xC0, 0xC4, 0xC5, 0xC6, 0xC8, 0xC9,
-    0xCA, 0xD0, 0xD8, 0xE0, 0xE4, 0xE5, 0xE6, 0xE8, 0xE9, 0xEA, 0xF0, 0xF8,
+    0xCA, 0xD0, 0xD8, 0xE0, 0xE4, 0xE5, 0xE6, 0xE8, 0xE9, 0xEA, 0xF0, 0xF8, 0x48, 0x68, 0xBA, 0x9A,
+    0x60, 0x00, 0x00, 0x20, 0x00, 0x85, 0x85, 0x86, 0x86, 0x86, 0x86, 0x86, 0x86, 0x84, 0x84, 0x84,
+    0x84, 0x84, 0x84, 0x85, 0x86, 0x84, 0xAD, 0x00, 0x8D, 0xA5, 0xA5, 0xAD, 0xAD, 0xAD, 0x00, 0xAD,
+    0x00, 0xAD, 0xB5, 0xB6, 0x16, 0xBD, 0x00, 0xB9, 0x00, 0xBD, 0xB9, 0xB1, 0x00, 0x0E, 0xAD, 0xBD,
+    0xB9, 0x95, 0x94, 0x96, 0x9D, 0x99, 0x8D, 0x8E, 0x8C, 0x8D, 0x8D, 0x8D, 0x8E, 0x8E, 0x8E, 0x8C,
+    0x8C, 0x8C, 0x08, 0x00, 0x28, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00,
+    0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00,
 };
 // The slot that runs opcode `op` without a page-crossing branch or a TIA store
 // (HOT_REAL: none).
 constexpr uint32_t hot_slot(uint32_t op) {
-    for (uint32_t s = kHotPlain; s < kHotSlots; ++s)
+    for (uint32_t s = kHotPlain; op && s < HOT_JSR; ++s)
         if (kHotSlotOp[s] == op) return s;
     return HOT_REAL;
 }
@@ -116,12 +135,11 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
 // immediate: operand in s86
 #define HL_IMM_(work) HL_B1_8 HL_TGT("s78") HL_FETCH(2) work HL_GO(2)
 #define HL_IMM(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_IMM_(work)
-#define HL_IMMD(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_BIN HL_IMM_(work)
+#define HL_IMMD(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_B1_8 HL_TGT("s78") HL_FETCH(2) HL_ACC(2) work HL_JUMP
 // zero-page read whose result the handler needs: operand in v123
 #define HL_ZPR_(work)                                                                              \
     HL_B1_7 HL_RAMADDR "ds_read_u8 v123, v122\n" HL_TGT("s78") HL_FETCH(2) HL_ACC(3) HL_WAIT work HL_JUMP
 #define HL_ZPR(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_ZPR_(work)
-#define HL_ZPRD(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_BIN HL_ZPR_(work)
 // zero-page load: lands in the register and nz before the next handler's wait ends
 #define HL_ZPL(B, slot, reg)                                                                       \
     HL_ORG(B, slot) HL_WAIT HL_B1_7 HL_RAMADDR "ds_read_u8 " reg ", v122\n"                        \
@@ -136,10 +154,10 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
 #define HL_NZ(reg) "v_mov_b32 %[nz], " reg "\n"
 #define HL_LDV "v_mov_b32 %[a], v123\nv_mov_b32 %[nz], v123\n"
 #define HL_LDI(reg) "v_mov_b32 " reg ", s86\nv_mov_b32 %[nz], s86\n"
-// ADC and SBC leave groups with a lane in decimal mode (s[50:51]) to the full dispatch
-#define HL_BIN                                             \
+// ADC and SBC of a group with a lane in decimal mode (s[50:51]) go on at `to`
+#define HL_BIN(to)                                         \
     "s_and_b64 s[96:97], s[50:51], exec\n"                 \
-    "s_cbranch_scc1 .Lout%=\n"
+    "s_cbranch_scc1 " to "%=\n"
 // arithmetic on A and operand `m` (a register or s86)
 #define HL_AND(m) "v_and_b32 %[a], " m ", %[a]\n" HL_NZ("%[a]")
 #define HL_ORA(m) "v_or_b32 %[a], " m ", %[a]\n" HL_NZ("%[a]")
@@ -150,6 +168,10 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     "v_bitop3_b32 %[v], %[a], " m ", v124 bitop3:0x42\n"   \
     "v_lshrrev_b32 %[c], 8, v124\n"                        \
     "v_and_b32 %[a], 0xff, v124\n" HL_NZ("%[a]")
+#define HL_ADCV HL_BIN(".Ldadc") HL_ADC("v123")
+#define HL_ADCI HL_BIN(".Ldadci") HL_ADC("s86")
+#define HL_SBCV HL_BIN(".Ldsbc") "v_xor_b32 v123, 0xff, v123\n" HL_ADC("v123")
+#define HL_SBCI HL_BIN(".Ldsbci") "s_xor_b32 s86, s86, 0xff\n" HL_ADC("s86")
 // r - m: carry is no borrow
 #define HL_CMP(r, m)                                       \
     "v_sub_u32 v124, " r ", " m "\n"                       \
@@ -269,7 +291,6 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     HL_XADDR "global_load_ubyte v123, v[120:121], off\n" HL_TGT("s79") HL_FETCH(3) HL_ACC(4)        \
     "s_waitcnt vmcnt(0)\n" work HL_JUMP
 #define HL_XR(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_XR_(work)
-#define HL_XRD(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_BIN HL_XR_(work)
 #define HL_XW(B, slot)                                     \
     HL_ORG(B, slot) HL_WAIT HL_XADDR                       \
     "global_store_byte v[120:121], %[a], off\n" HL_TGT("s79") HL_FETCH(3) HL_GO(4)
@@ -376,24 +397,341 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     ".Lbhu%=:\n" HL_GRP1_READ HL_TGT("s78") HL_FETCH(2)     \
     HL_ACC(3) HL_GRP1_WRITE HL_JUMP
 // ENAMx, ENABL (bit 1), VDELx (bit 0): bit k of the flags byte and the full byte 32 + k
-#define HL_FLAG_(slot, B, k, bit)                          \
-    HL_ORG(B, slot) HL_WAIT                                \
+#define HL_FLAG_(slot, B, k, bit, body)                    \
+    HL_ORG(B, slot) HL_WAIT "v_mov_b32 v126, %[a]\n"       \
+    ".Lbf" #k body "%=:\n"                                 \
     "ds_read_u8 v124, %[tia] offset:23\n"                  \
-    "v_bfe_u32 v122, %[a], " #bit ", 1\n" HL_TGT("s78") HL_FETCH(2) HL_WAIT \
+    "v_bfe_u32 v122, v126, " #bit ", 1\n" HL_TGT("s78") HL_FETCH(2) HL_WAIT \
     "v_and_b32 v124, ~(1<<" #k "), v124\n"                 \
     "v_lshl_or_b32 v125, v122, " #k ", v124\n"
 #define HL_FLAG_WRITE(k)                                   \
     "ds_write_b8 %[tia], v125 offset:23\n"                 \
-    "ds_write_b8 %[tia], %[a] offset:32+" #k "\n"
+    "ds_write_b8 %[tia], v126 offset:32+" #k "\n"
 #define HL_FLAG_LOG(B, slot, k, bit)                       \
-    HL_FLAG_(slot, B, k, bit) HL_LOGGED("f" #k, "v125", "23*256-224", HL_FLAG_WRITE(k))
-#define HL_FLAG_NOLOG(B, slot, k, bit) HL_FLAG_(slot, B, k, bit) HL_FLAG_WRITE(k) HL_GO(3)
+    HL_FLAG_(slot, B, k, bit, "l") HL_LOGGED("f" #k, "v125", "23*256-224", HL_FLAG_WRITE(k))
+#define HL_FLAG_NOLOG(B, slot, k, bit) HL_FLAG_(slot, B, k, bit, "u") HL_FLAG_WRITE(k) HL_GO(3)
+// the same of X or Y
+#define HL_FLAG_XY(B, slot, reg, k, body) HL_ORG(B, slot) HL_WAIT "v_mov_b32 v126, " reg "\ns_branch .Lbf" #k body "%=\n"
+#define HL_FLAGS_XY(B, body)                                                                                   \
+    HL_FLAG_XY(B, 151, "%[x]", 0, body) HL_FLAG_XY(B, 152, "%[x]", 1, body) HL_FLAG_XY(B, 153, "%[x]", 2, body) \
+    HL_FLAG_XY(B, 154, "%[x]", 4, body) HL_FLAG_XY(B, 155, "%[x]", 5, body) HL_FLAG_XY(B, 156, "%[x]", 6, body) \
+    HL_FLAG_XY(B, 157, "%[y]", 0, body) HL_FLAG_XY(B, 158, "%[y]", 1, body) HL_FLAG_XY(B, 159, "%[y]", 2, body) \
+    HL_FLAG_XY(B, 160, "%[y]", 4, body) HL_FLAG_XY(B, 161, "%[y]", 5, body) HL_FLAG_XY(B, 162, "%[y]", 6, body)
+// RESPx, RESMx, RESBL (of any register): the position is the beam's + `delay`
+// in the visible part, delay - 2 before it; then as a register store
+#define HL_RES(B, slot, delay, body)                       \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "s_add_u32 s88, s73, 3<<25\n"                          \
+    "s_lshr_b32 s88, s88, 25\n"                            \
+    "s_mul_i32 s87, s88, 3\n"                              \
+    "s_sub_u32 s87, s87, 3*52+68-" #delay "\n"             \
+    "s_sub_u32 s86, s87, 160\n"                            \
+    "s_cselect_b32 s87, s87, s86\n"                        \
+    "s_cmp_lt_u32 s88, 75\n"                               \
+    "s_cselect_b32 s87, " #delay "-2, s87\n"               \
+    "v_mov_b32 v125, s87\n"                                \
+    "s_branch .Lbt" body "%=\n"
+#define HL_RES_LOG(B, slot, delay) HL_RES(B, slot, delay, "l")
+#define HL_RES_NOLOG(B, slot, delay) HL_RES(B, slot, delay, "u")
+#define HL_FXY_LOG(B) HL_FLAGS_XY(B, "l")
+#define HL_FXY_NOLOG(B) HL_FLAGS_XY(B, "u")
+
+// The stack, while it stays in RAM in every lane (a push at $80 or above, a
+// pull from below $FF); a return whose lanes or window part is left too.
+#define HL_PUSHADDR "v_and_b32 v122, 0x7f, %[sp]\nv_add_u32 v122, v122, %[ram]\n"
+#define HL_PHA(B, slot)                                    \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "v_cmp_gt_u32 vcc, 0x80, %[sp]\n" HL_PUSHADDR          \
+    "s_cbranch_vccnz .Lout%=\n" HL_TGT("s77") HL_FETCH(1)  \
+    "ds_write_b8 v122, %[a]\n"                             \
+    "v_add_u32 %[sp], -1, %[sp]\n" HL_GO(3)
+#define HL_PLA(B, slot)                                    \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "v_add_u32 v122, 0xffffff81, %[sp]\n"                  \
+    "v_cmp_lt_u32 vcc, 0x7f, v122\n"                       \
+    "v_add_u32 v122, v122, %[ram]\n"                       \
+    "s_cbranch_vccnz .Lout%=\n" HL_TGT("s77") HL_FETCH(1)  \
+    "ds_read_u8 %[a], v122\n"                              \
+    "ds_read_u8 %[nz], v122\n"                             \
+    "v_add_u32 %[sp], 1, %[sp]\n" HL_GO(4)
+#define HL_JSR(B, slot)                                    \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "s_xor_b32 s86, s76, s59\n"                            \
+    "s_lshr_b32 s86, s86, 28\n"                            \
+    "s_cbranch_scc1 .Lout%=\n"                             \
+    "v_cmp_gt_u32 vcc, 0x81, %[sp]\n" HL_PUSHADDR          \
+    "s_cbranch_vccnz .Lout%=\n"                            \
+    "s_lshr_b32 s87, s72, 2\n"                             \
+    "s_and_b32 s87, s87, 0xfff\n"                          \
+    "s_lshr_b32 s88, s59, 28\n"                            \
+    "s_lshl_b32 s88, s88, 12\n"                            \
+    "s_bfe_u32 s86, s76, 0xc0010\n"                        \
+    "s_and_b32 s72, s72, 0xffffc000\n"                     \
+    "s_lshl2_add_u32 s72, s86, s72\n"                      \
+    "s_load_dwordx4 s[76:79], s[70:71], s72\n"             \
+    "s_add_u32 s87, s87, 2\n"                              \
+    "s_or_b32 s87, s87, s88\n"                             \
+    "s_lshr_b32 s88, s87, 8\n"                             \
+    "v_mov_b32 v123, s88\n"                                \
+    "v_mov_b32 v124, s87\n"                                \
+    "ds_write_b8 v122, v123\n"                             \
+    "v_add_u32 v122, -1, v122\n"                           \
+    "ds_write_b8 v122, v124\n"                             \
+    "v_add_u32 %[sp], -2, %[sp]\n" HL_WAIT HL_TGT("s76") HL_GO(6)
+#define HL_RTS(B, slot)                                    \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "v_add_u32 v122, 0xffffff81, %[sp]\n"                  \
+    "v_cmp_lt_u32 vcc, 0x7e, v122\n"                       \
+    "v_add_u32 v122, v122, %[ram]\n"                       \
+    "s_cbranch_vccnz .Lout%=\n"                            \
+    "ds_read_u8 v123, v122\n"                              \
+    "ds_read_u8 v124, v122 offset:1\n" HL_WAIT             \
+    "v_lshl_or_b32 v123, v124, 8, v123\n"                  \
+    "v_add_u32 v123, 1, v123\n"                            \
+    "v_and_b32 v123, 0xffff, v123\n"                       \
+    "s_nop 1\n"                                            \
+    "v_readfirstlane_b32 s86, v123\n"                      \
+    "s_lshr_b32 s88, s59, 28\n"                            \
+    "s_lshr_b32 s87, s86, 12\n"                            \
+    "s_cmp_lg_u32 s87, s88\n"                              \
+    "v_cmp_ne_u32 vcc, s86, v123\n"                        \
+    "s_cbranch_scc1 .Lout%=\n"                             \
+    "s_and_b32 s86, s86, 0xfff\n"                          \
+    "s_cbranch_vccnz .Lout%=\n"                            \
+    "s_cmp_gt_u32 s86, 0xffc\n"                            \
+    "s_cbranch_scc1 .Lout%=\n"                             \
+    "s_and_b32 s72, s72, 0xffffc000\n"                     \
+    "s_lshl2_add_u32 s72, s86, s72\n"                      \
+    "s_load_dwordx4 s[76:79], s[70:71], s72\n"             \
+    "v_add_u32 %[sp], 2, %[sp]\n" HL_WAIT HL_TGT("s76") HL_GO(6)
+
+#define HL_PHP(B, slot)                                    \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "v_cmp_gt_u32 vcc, 0x80, %[sp]\n" HL_PUSHADDR          \
+    "s_cbranch_vccnz .Lout%=\n" HL_TGT("s77") HL_FETCH(1)  \
+    "v_and_b32 v124, 0x180, %[nz]\n"                       \
+    "v_cmp_ne_u32 vcc, 0, v124\n"                          \
+    "v_and_b32 v123, 4, %[p]\n"                            \
+    "v_or_b32 v123, 0x30, v123\n"                          \
+    "v_mov_b32 v125, 0x80\n"                               \
+    "v_cndmask_b32 v125, 0, v125, vcc\n"                   \
+    "v_and_b32 v124, 0xff, %[nz]\n"                        \
+    "v_cmp_eq_u32 vcc, 0, v124\n"                          \
+    "v_or3_b32 v123, v123, v125, %[c]\n"                   \
+    "v_mov_b32 v125, 2\n"                                  \
+    "v_mov_b32 v124, 8\n"                                  \
+    "v_cndmask_b32 v125, 0, v125, vcc\n"                   \
+    "v_cndmask_b32 v124, 0, v124, s[50:51]\n"              \
+    "v_or3_b32 v123, v123, v125, v124\n"                   \
+    "v_bfe_u32 v124, %[v], 7, 1\n"                         \
+    "v_lshl_or_b32 v123, v124, 6, v123\n"                  \
+    "ds_write_b8 v122, v123\n"                             \
+    "v_add_u32 %[sp], -1, %[sp]\n" HL_GO(3)
+#define HL_PLP(B, slot)                                    \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "v_add_u32 v122, 0xffffff81, %[sp]\n"                  \
+    "v_cmp_lt_u32 vcc, 0x7f, v122\n"                       \
+    "v_add_u32 v122, v122, %[ram]\n"                       \
+    "s_cbranch_vccnz .Lout%=\n"                            \
+    "ds_read_u8 v123, v122\n" HL_TGT("s77") HL_FETCH(1)    \
+    "v_add_u32 %[sp], 1, %[sp]\n" HL_ACC(4) HL_WAIT        \
+    "v_and_b32 v124, 0xef, v123\n"                         \
+    "v_or_b32 %[p], 0x20, v124\n"                          \
+    "v_and_b32 %[c], 1, v123\n"                            \
+    "v_lshlrev_b32 %[v], 1, v123\n"                        \
+    "v_and_b32 v124, 0x80, v123\n"                         \
+    "v_bfe_u32 v125, v123, 1, 1\n"                         \
+    "v_xor_b32 v125, 1, v125\n"                            \
+    "v_lshl_or_b32 %[nz], v124, 1, v125\n"                 \
+    "v_and_b32 v124, 8, v123\n"                            \
+    "v_cmp_ne_u32 vcc, 0, v124\n"                          \
+    "s_andn2_b64 s[50:51], s[50:51], exec\n"               \
+    "s_or_b64 s[50:51], s[50:51], vcc\n" HL_JUMP
+
+// Absolute stores: to RAM; to a TIA register that the zero-page form logs, as
+// that form a cycle and a byte later (left first when it would be: at the
+// line's end, or when a row's entries might not fit)
+#define HL_ASTO(B, slot, reg)                              \
+    HL_ORG(B, slot) HL_WAIT HL_B1_7 HL_RAMADDR "ds_write_b8 v122, " reg "\n" HL_TGT("s79") HL_FETCH(3) HL_GO(4)
+#define HL_ATIA(B, slot, reg, body)                        \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "v_sub_u32 v122, v100, %[log0]\n"                      \
+    "v_lshrrev_b32 v122, 2, v122\n"                        \
+    "v_cmp_lt_u32 vcc, s69, v122\n"                        \
+    "s_add_u32 s87, s73, 4<<25\n"                          \
+    "s_cbranch_scc1 .Lout%=\n"                             \
+    "s_bitcmp1_b32 s59, 27\n"                              \
+    "s_cselect_b64 vcc, vcc, 0\n"                          \
+    "s_cbranch_vccnz .Lout%=\n"                            \
+    "s_add_u32 s73, s73, 1<<25\n"                          \
+    "s_add_u32 s72, s72, 4\n"                              \
+    "s_mov_b32 s78, s79\n"                                 \
+    "v_mov_b32 v125, " reg "\n"                            \
+    "s_branch .Lb" body "%=\n"
+#define HL_ATIAS(B, l)                                                                                            \
+    HL_ATIA(B, 201, "%[a]", "t" l) HL_ATIA(B, 202, "%[a]", "g" l) HL_ATIA(B, 203, "%[a]", "h" l)                 \
+    HL_ATIA(B, 204, "%[x]", "t" l) HL_ATIA(B, 205, "%[x]", "g" l) HL_ATIA(B, 206, "%[x]", "h" l)                 \
+    HL_ATIA(B, 207, "%[y]", "t" l) HL_ATIA(B, 208, "%[y]", "g" l) HL_ATIA(B, 209, "%[y]", "h" l)
+#define HL_ATIA_LOG(B) HL_ATIAS(B, "l")
+#define HL_ATIA_NOLOG(B) HL_ATIAS(B, "u")
+
+// 3F: a store to $00-$3F selects a slice (mask: the class), the same in every lane
+#define HL_3F(B, slot, reg)                                \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "s_and_b32 s86, s76, 0x7f\n"                           \
+    "v_and_b32 v122, s86, " reg "\n"                       \
+    "s_branch .Lslice%=\n"
+// LDA from an E0 hotspot ($1FE0-$1FF7: slice number in bits 0-2, segment in
+// 3-4), whose byte lies in the last slice
+#define HL_E0(B, slot)                                     \
+    HL_ORG(B, slot) HL_WAIT HL_B1_8                        \
+    "s_bfe_u32 s87, s86, 0x20003\n"                        \
+    "s_mul_i32 s87, s87, 3\n"                              \
+    "s_add_u32 s87, s87, 14\n"                             \
+    "s_lshl_b32 s88, 7, s87\n"                             \
+    "s_and_b32 s89, s86, 7\n"                              \
+    "s_lshl_b32 s89, s89, s87\n"                           \
+    "s_add_u32 s72, s72, 12\n"                             \
+    "s_andn2_b32 s72, s72, s88\n"                          \
+    "s_or_b32 s72, s72, s89\n"                             \
+    "s_load_dwordx4 s[76:79], s[70:71], s72\n"             \
+    "s_or_b32 s86, s86, 0x1f00\n" HL_ABSBYTE HL_TGT("s76") HL_GO(4)
+// a store to a bank hotspot of a linear scheme (the new bank in the class)
+#define HL_HS_ST(B, slot)                                  \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "s_and_b32 s87, s76, 7\n"                              \
+    "s_lshl_b32 s87, s87, 14\n"                            \
+    "s_add_u32 s72, s72, 12\n"                             \
+    "s_and_b32 s72, s72, 0x3fff\n"                         \
+    "s_or_b32 s72, s72, s87\n"                             \
+    "s_load_dwordx4 s[76:79], s[70:71], s72\n" HL_WAIT HL_TGT("s76") HL_GO(4)
+
+// Two-step reads: the operand to v123, then on to the operation's slot (HL_OP,
+// taken from the word before the next one is loaded).
+#define HL_OP                                              \
+    "s_and_b32 s90, s76, 31\n"                             \
+    "s_lshl_b32 s90, s90, 7\n"                             \
+    "s_add_u32 s90, s90, s84\n"                            \
+    "s_add_u32 s90, s90, 128*214\n"
+#define HL_DO "s_setpc_b64 s[90:91]\n"
+#define HL_WORK(B, slot, work) HL_ORG(B, slot) work HL_JUMP
+// constants: 0, $80, $0B (SWCHB)
+#define HL_CONST                                           \
+    "s_bfe_u32 s87, s76, 0x20005\n"                        \
+    "s_lshl_b32 s87, s87, 3\n"                             \
+    "s_lshr_b32 s86, 0x0b8000, s87\n"                      \
+    "s_and_b32 s86, s86, 0xff\n"                           \
+    "v_mov_b32 v123, s86\n"
+#define HL_ZIN(B, slot, get) HL_ORG(B, slot) HL_WAIT get HL_OP HL_TGT("s78") HL_FETCH(2) HL_ACC(3) HL_DO
+#define HL_AIN(B, slot, get) HL_ORG(B, slot) HL_WAIT get HL_OP HL_TGT("s79") HL_FETCH(3) HL_ACC(4) HL_DO
+#define HL_AROM(B, slot)                                   \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "s_lshr_b32 s87, s72, 14\n"                            \
+    "s_bfe_u32 s86, s76, 0xc0010\n"                        \
+    "s_lshl_b32 s87, s87, 12\n"                            \
+    "s_or_b32 s86, s86, s87\n" HL_OP HL_TGT("s79") HL_FETCH(3) HL_ACC(4) \
+    "s_and_b32 s87, s86, -4\n"                             \
+    "s_load_dword s94, s[40:41], s87\n"                    \
+    "s_lshl_b32 s86, s86, 3\n" HL_WAIT                     \
+    "s_lshr_b32 s94, s94, s86\n"                           \
+    "s_and_b32 s86, s94, 0xff\n"                           \
+    "v_mov_b32 v123, s86\n" HL_DO
+#define HL_ARAM(B, slot)                                   \
+    HL_ORG(B, slot) HL_WAIT HL_B1_7 HL_RAMADDR "ds_read_u8 v123, v122\n"   \
+    HL_OP HL_TGT("s79") HL_FETCH(3) HL_ACC(4) HL_WAIT HL_DO
+// INTIM: cycles since the timer was written are the lane's `tm` + the access
+// cycle (76 lines + the cycle in the line, from the base line)
+#define HL_INTIM(B, slot)                                  \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "s_bfe_i32 s86, s59, 0x1b0000\n"                       \
+    "s_sub_u32 s86, s86, s80\n"                            \
+    "s_mul_i32 s86, s86, 76\n"                             \
+    "s_lshr_b32 s87, s73, 25\n"                            \
+    "s_add_u32 s86, s86, s87\n"                            \
+    "s_add_u32 s86, s86, 76*320-52+3\n"                    \
+    HL_OP HL_TGT("s79") HL_FETCH(3)                        \
+    "v_add_u32 v122, s86, %[tm]\n"                         \
+    "v_add_u32 v124, 1, %[tv]\n"                           \
+    "v_lshlrev_b32 v124, %[tsh], v124\n"                   \
+    "v_sub_u32 v124, v122, v124\n"                         \
+    "v_cmp_gt_i32 vcc, 0, v124\n"                          \
+    "v_sub_u32 v124, 0xff, v124\n"                         \
+    "v_ashrrev_i32 v123, %[tsh], v122\n"                   \
+    "v_sub_u32 v123, %[tv], v123\n"                        \
+    "v_cndmask_b32 v123, v124, v123, vcc\n"                \
+    "v_and_b32 v123, 0xff, v123\n" HL_ACC(4) HL_DO
+// indexed by a register: the address in RAM in every lane, or left.  Zero page
+// (wraps in it), and absolute with a zero-page base (does not).
+#define HL_ZIDX(idx)                                       \
+    HL_B1_8                                                \
+    "v_add_u32 v122, s86, " idx "\n"                       \
+    "v_and_b32 v122, 0xff, v122\n" HL_INRAM
+#define HL_AIDX(idx)                                       \
+    HL_B1_8                                                \
+    "v_add_u32 v122, s86, " idx "\n" HL_INRAM
+#define HL_INRAM                                           \
+    "v_add_u32 v122, 0xffffff80, v122\n"                   \
+    "v_cmp_lt_u32 vcc, 0x7f, v122\n"                       \
+    "v_add_u32 v122, v122, %[ram]\n"                       \
+    "s_cbranch_vccnz .Lout%=\n"
+#define HL_RIDX(B, slot, addr, len, next, cyc)             \
+    HL_ORG(B, slot) HL_WAIT addr "ds_read_u8 v123, v122\n" \
+    HL_OP HL_TGT(next) HL_FETCH(len) HL_ACC(cyc) HL_WAIT HL_DO
+#define HL_SIDX(B, slot, addr, reg, len, next, cyc)        \
+    HL_ORG(B, slot) HL_WAIT addr "ds_write_b8 v122, " reg "\n" HL_TGT(next) HL_FETCH(len) HL_GO(cyc)
+// ... in a linear cartridge: every lane in the bank's plain ROM (offsets s92 ..
+// s92 + s42 - 1: no hotspot, no Superchip RAM), and all or none across a page.
+// s39: the LDS copy, or -1: read from HBM (the wait includes the log stores before it)
+#define HL_AXROM(B, slot, idx)                             \
+    HL_ORG(B, slot) HL_WAIT HL_B1_8                        \
+    "s_bfe_u32 s87, s76, 0xc0010\n"                        \
+    "v_add_u32 v122, s87, " idx "\n"                       \
+    "v_add_u32 v124, s86, " idx "\n"                       \
+    HL_INROM(4, ".Lhbm") HL_ROM_GO("s79", 3) HL_WAIT HL_DO
+// (v122: the offset in the bank, v124: above $FF across a page)
+#define HL_INROM(cyc, hbm)                                 \
+    "v_subrev_u32 v123, s92, v122\n"                       \
+    "v_cmp_le_u32 s[96:97], s42, v123\n" HL_CROSS(cyc)     \
+    "s_lshr_b32 s87, s72, 14\n"                            \
+    "s_lshl_b32 s87, s87, 12\n" HL_ROMBYTE(hbm)
+#define HL_CROSS(cyc)                                      \
+    "v_cmp_lt_u32 vcc, 0xff, v124\n"                       \
+    "s_cmp_lg_u64 s[96:97], 0\n"                           \
+    "s_cbranch_scc1 .Lout%=\n"                             \
+    "s_mov_b32 s88, (" #cyc "<<25)+1\n"                    \
+    "s_cmp_eq_u64 vcc, exec\n"                             \
+    "s_cselect_b32 s88, ((" #cyc "+1)<<25)+1, s88\n"       \
+    "s_cselect_b64 s[96:97], exec, 0\n"                    \
+    "s_cmp_lg_u64 vcc, s[96:97]\n"                         \
+    "s_cbranch_scc1 .Lout%=\n"
+#define HL_ROMBYTE(hbm)                                    \
+    "v_add_u32 v122, s87, v122\n"                          \
+    "s_cmp_eq_u32 s39, -1\n"                               \
+    "s_cbranch_scc1 " hbm "%=\n"                           \
+    "v_add_u32 v122, s39, v122\n"                          \
+    "ds_read_u8 v123, v122\n"
+#define HL_ROM_GO(next, len)                               \
+    HL_OP HL_TGT(next) HL_FETCH(len)                       \
+    "s_add_u32 s73, s73, s88\n"                            \
+    "s_cselect_b32 s74, s85, s74\n"
+// ... in an E0 or 3F cartridge: v125, the index, added inside the segment or half
+#define HL_SEG(B, slot, idx) HL_ORG(B, slot) HL_WAIT "v_mov_b32 v125, " idx "\ns_branch .Lseg%=\n"
+// (zp),Y: the pointer in RAM, per lane
+#define HL_IYROM(B, slot)                                  \
+    HL_ORG(B, slot) HL_WAIT HL_B1_7 HL_RAMADDR             \
+    "ds_read_u8 v124, v122\n"                              \
+    "ds_read_u8 v123, v122 offset:1\n" HL_WAIT             \
+    "v_add_u32 v124, v124, %[y]\n"                         \
+    "v_lshl_add_u32 v122, v123, 8, v124\n"                 \
+    "v_and_b32 v122, 0x1fff, v122\n"                       \
+    "v_add_u32 v122, 0xfffff000, v122\n"                   \
+    HL_INROM(5, ".Lhbmy") HL_ROM_GO("s78", 2) HL_WAIT HL_DO
 #define HL_XY_LOG(B, slot, reg, body) HL_XY_(B, slot, reg, ".Lb" body "l")
 #define HL_XY_NOLOG(B, slot, reg, body) HL_XY_(B, slot, reg, ".Lb" body "u")
 
 // Every handler of one of the two blocks (frames whose writes are logged, and
 // the others: dispatch by block spares each TIA store the question).
-#define HL_BLOCK(B, TIA, TIAX, GRP0, GRP1, HL_XY, FLAG) \
+#define HL_BLOCK(B, TIA, TIAX, GRP0, GRP1, HL_XY, FLAG, RES, FXY, ATIA) \
     HL_ORG(B, 0) "s_branch .Lout%=\n"                                                                /* HOT_REAL */ \
     TIA(B, 1, 0)                                                                                     /* STA COLUP0 */ \
     TIA(B, 3, 1)                                                                                     /* STA COLUP1 */ \
@@ -424,7 +762,7 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     FLAG(B, 49, 5, 0)                                                                                /* STA VDELP1 */ \
     FLAG(B, 51, 6, 0)                                                                                /* STA VDELBL */ \
     HL_XR(B, 53, HL_LDV)                                                                             /* LDA from Superchip RAM */ \
-    HL_XRD(B, 54, HL_ADC("v123"))                                                                    /* ADC from Superchip RAM */ \
+    HL_XR(B, 54, HL_ADCV)                                                                             /* ADC from Superchip RAM */ \
     HL_XR(B, 55, HL_AND("v123"))                                                                     /* AND from Superchip RAM */ \
     HL_XR(B, 56, HL_EOR("v123"))                                                                     /* EOR from Superchip RAM */ \
     HL_XR(B, 57, HL_ORA("v123"))                                                                     /* ORA from Superchip RAM */ \
@@ -470,9 +808,9 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     HL_IMP(B, 97, HL_LSR("%[a]"))                                                                    /* $4A */ \
     HL_JMP(B, 98)                                                                                    /* $4C */ \
     HL_BR(B, 99, HL_T_EQ("0x80", "%[v]"), "8")                                                       /* $50 */ \
-    HL_ZPRD(B, 100, HL_ADC("v123"))                                                                  /* $65 */ \
+    HL_ZPR(B, 100, HL_ADCV)                                                                          /* $65 */ \
     HL_ZPM(B, 101, HL_ROR("v123"))                                                                   /* $66 */ \
-    HL_IMMD(B, 102, HL_ADC("s86"))                                                                   /* $69 */ \
+    HL_IMMD(B, 102, HL_ADCI)                                                                         /* $69 */ \
     HL_IMP(B, 103, HL_ROR("%[a]"))                                                                   /* $6A */ \
     HL_BR(B, 104, HL_T_NE("0x80", "%[v]"), "8")                                                      /* $70 */ \
     HL_ZPS(B, 105, "%[y]")                                                                           /* $84 */ \
@@ -503,13 +841,75 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     HL_IMP(B, 130, "s_andn2_b64 s[50:51], s[50:51], exec\n")                                         /* $D8 */ \
     HL_IMM(B, 131, HL_CMP_S("%[x]"))                                                                 /* $E0 */ \
     HL_ZPR(B, 132, HL_CMP("%[x]", "v123"))                                                           /* $E4 */ \
-    HL_ZPRD(B, 133, "v_xor_b32 v123, 0xff, v123\n" HL_ADC("v123"))                                   /* $E5 */ \
+    HL_ZPR(B, 133, HL_SBCV)                                                                          /* $E5 */ \
     HL_ZPM(B, 134, HL_INC("v123"))                                                                   /* $E6 */ \
     HL_IMP(B, 135, HL_INC("%[x]"))                                                                   /* $E8 */ \
-    HL_IMMD(B, 136, "s_xor_b32 s86, s86, 0xff\n" HL_ADC("s86"))                                      /* $E9 */ \
+    HL_IMMD(B, 136, HL_SBCI)                                                                         /* $E9 */ \
     HL_IMP(B, 137, "")                                                                               /* $EA */ \
     HL_BR(B, 138, HL_T_EQ("0xff", "%[nz]"), "8")                                                     /* $F0 */ \
-    HL_IMP(B, 139, "s_or_b64 s[50:51], s[50:51], exec\n")                                            /* $F8 */
+    HL_IMP(B, 139, "s_or_b64 s[50:51], s[50:51], exec\n")                                            /* $F8 */ \
+    HL_PHA(B, 140)                                                                                   /* $48 */ \
+    HL_PLA(B, 141)                                                                                   /* $68 */ \
+    HL_IMP(B, 142, "v_mov_b32 %[x], %[sp]\n" HL_NZ("%[sp]"))                                         /* $BA */ \
+    HL_IMP(B, 143, "v_mov_b32 %[sp], %[x]\n")                                                        /* $9A */ \
+    HL_RTS(B, 144)                                                                                   /* $60 */ \
+    HL_JSR(B, 147)                                                                                   /* $20 */ \
+    RES(B, 149, 5)                                                                                   /* RESP0, RESP1 */ \
+    RES(B, 150, 4)                                                                                   /* RESM0, RESM1, RESBL */ \
+    FXY(B)                                                                                           /* STX, STY to ENAM0 .. VDELBL */ \
+    HL_3F(B, 163, "%[a]")                                                                            /* STA selecting a 3F slice */ \
+    HL_3F(B, 164, "%[x]")                                                                            /* STX selecting one */ \
+    HL_3F(B, 165, "%[y]")                                                                            /* STY selecting one */ \
+    HL_E0(B, 166)                                                                                    /* LDA from an E0 hotspot */ \
+    HL_HS_ST(B, 168)                                                                                 /* store to a bank hotspot */ \
+    HL_ZIN(B, 169, HL_CONST)                                                                         /* a constant TIA read, zero page */ \
+    HL_ZIN(B, 170, "v_mov_b32 v123, %[inpt4]\n")                                                     /* INPT4 */ \
+    HL_AIN(B, 171, HL_CONST)                                                                         /* a constant read, absolute */ \
+    HL_AIN(B, 172, "v_mov_b32 v123, %[swcha]\n")                                                     /* SWCHA */ \
+    HL_INTIM(B, 173)                                                                                 /* INTIM */ \
+    HL_AROM(B, 175)                                                                                  /* the cartridge, absolute */ \
+    HL_ARAM(B, 177)                                                                                  /* RAM, absolute */ \
+    HL_RIDX(B, 178, HL_ZIDX("%[x]"), 2, "s78", 4)                                                    /* zero page, X */ \
+    HL_RIDX(B, 179, HL_ZIDX("%[y]"), 2, "s78", 4)                                                    /* zero page, Y */ \
+    HL_RIDX(B, 180, HL_ZIDX("%[x]"), 2, "s78", 6)                                                    /* read-modify-write of it */ \
+    HL_AXROM(B, 181, "%[x]")                                                                         /* the cartridge, absolute, X */ \
+    HL_AXROM(B, 183, "%[y]")                                                                         /* the cartridge, absolute, Y */ \
+    HL_RIDX(B, 185, HL_AIDX("%[x]"), 3, "s79", 4)                                                    /* RAM, absolute, X */ \
+    HL_RIDX(B, 186, HL_AIDX("%[y]"), 3, "s79", 4)                                                    /* RAM, absolute, Y */ \
+    HL_IYROM(B, 187)                                                                                 /* the cartridge through a pointer, Y */ \
+    HL_RIDX(B, 189, HL_B1_7 HL_RAMADDR, 3, "s79", 6)                                                 /* read-modify-write of RAM, absolute */ \
+    HL_SEG(B, 190, "0")                                                                              /* an E0 or 3F cartridge, absolute */ \
+    HL_SEG(B, 191, "%[x]")                                                                           /* absolute, X */ \
+    HL_SEG(B, 192, "%[y]")                                                                           /* absolute, Y */ \
+    HL_SIDX(B, 193, HL_ZIDX("%[x]"), "%[a]", 2, "s78", 4)                                            /* $95 */ \
+    HL_SIDX(B, 194, HL_ZIDX("%[x]"), "%[y]", 2, "s78", 4)                                            /* $94 */ \
+    HL_SIDX(B, 195, HL_ZIDX("%[y]"), "%[x]", 2, "s78", 4)                                            /* $96 */ \
+    HL_SIDX(B, 196, HL_AIDX("%[x]"), "%[a]", 3, "s79", 5)                                            /* $9D */ \
+    HL_SIDX(B, 197, HL_AIDX("%[y]"), "%[a]", 3, "s79", 5)                                            /* $99 */ \
+    HL_ASTO(B, 198, "%[a]")                                                                          /* $8D to RAM */ \
+    HL_ASTO(B, 199, "%[x]")                                                                          /* $8E */ \
+    HL_ASTO(B, 200, "%[y]")                                                                          /* $8C */ \
+    ATIA(B)                                                                                          /* absolute stores to TIA registers */ \
+    HL_PHP(B, 210)                                                                                   /* $08 */ \
+    HL_PLP(B, 212)                                                                                   /* $28 */ \
+    HL_WORK(B, 214, HL_LDV)                                                                          /* LDA */ \
+    HL_WORK(B, 215, "v_mov_b32 %[x], v123\n" HL_NZ("v123"))                                          /* LDX */ \
+    HL_WORK(B, 216, "v_mov_b32 %[y], v123\n" HL_NZ("v123"))                                          /* LDY */ \
+    HL_WORK(B, 217, HL_AND("v123"))                                                                  /* AND */ \
+    HL_WORK(B, 218, HL_ORA("v123"))                                                                  /* ORA */ \
+    HL_WORK(B, 219, HL_EOR("v123"))                                                                  /* EOR */ \
+    HL_WORK(B, 220, HL_CMP("%[a]", "v123"))                                                          /* CMP */ \
+    HL_WORK(B, 221, HL_CMP("%[x]", "v123"))                                                          /* CPX */ \
+    HL_WORK(B, 222, HL_CMP("%[y]", "v123"))                                                          /* CPY */ \
+    HL_WORK(B, 223, HL_BIT)                                                                          /* BIT */ \
+    HL_WORK(B, 224, HL_ADCV)                                                                         /* ADC */ \
+    HL_WORK(B, 225, HL_SBCV)                                                                         /* SBC */ \
+    HL_WORK(B, 226, HL_ASL("v123") "ds_write_b8 v122, v123\n")                                       /* ASL */ \
+    HL_WORK(B, 227, HL_ROL("v123") "ds_write_b8 v122, v123\n")                                       /* ROL */ \
+    HL_WORK(B, 228, HL_LSR("v123") "ds_write_b8 v122, v123\n")                                       /* LSR */ \
+    HL_WORK(B, 229, HL_ROR("v123") "ds_write_b8 v122, v123\n")                                       /* ROR */ \
+    HL_WORK(B, 230, HL_DEC("v123") "ds_write_b8 v122, v123\n")                                       /* DEC */ \
+    HL_WORK(B, 231, HL_INC("v123") "ds_write_b8 v122, v123\n")                                       /* INC */
 
 // Fold the current group's instruction count into its lanes' counts and the
 // wave's passes (exec: the group).
@@ -566,6 +966,16 @@ struct HotLane {
     uint64_t lp;         // where the next entry goes (not part of the place)
     uint32_t obase;      // the open row's first entry, in dwords from the log's start (nor this)
 };
+// The lane's timer: cycles of the base line's start after the one that the last
+// write is visible at, its value and log2 interval.
+struct HotTimer {
+    uint32_t tm, tv, tshift;
+};
+// The cartridge: its LDS copy's address or -1; linear schemes: the bank offsets
+// that are plain ROM; E0: span 0; 3F: span 1, first the fixed half's ROM offset.
+struct HotRom {
+    uint32_t lds, first, span;
+};
 constexpr uint32_t kHotNone = 0xFFFFFFFFu;
 constexpr uint32_t kHotLogged = 1u << 27;
 
@@ -591,13 +1001,16 @@ __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uin
                                              uint32_t& x, uint32_t& y, uint32_t& p, uint32_t& nz, uint32_t& c,
                                              uint32_t& v, uint32_t& hmp0, uint32_t& hmp1, uint32_t& vsync,
                                              uint32_t inpt4, uint32_t swcha, uint32_t& ic, uint32_t& passes, uint32_t& rounds,
-                                             uint32_t ram, uint32_t tia, uint64_t log, uint64_t xram) {
+                                             uint32_t ram, uint32_t tia, uint64_t log, uint64_t xram, uint32_t& sp,
+                                             const HotTimer& T, const HotRom& R) {
     static_assert(kSnapArea == 1696 * 4 && kCountMask == 31 && kFrameEntries == 5280 && kRows == 210 &&
                       kFirstRow == 34 && kSnapBytes == 32,
                   "the block's constants");
     static_assert(R_GRP0 == 10 && R_GRP1 == 11 && R_GRP0_OLD == 16 && R_GRP1_OLD == 17 && R_FLAGS == 23 &&
                       R_ENAM0 == 32 && R_ENABL == 34 && R_ENABL_OLD == 35 && R_VDELBL == 38,
                   "the block's register offsets");
+    static_assert(kHotWork == 214 && HW_INC == kHotWorks - 1 && (HW_NONE | 3 << 5) < 128 && kHotSlots * 128 < 0x8000,
+                  "the block's slots");
     asm volatile(
         // --- entry: block bases, line-change and row addresses, constants
         "s_mov_b64 s[44:45], exec\n"
@@ -616,6 +1029,7 @@ __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uin
         "s_add_u32 s85, s74, .Lline%=-.Lpc%=\n"
         "s_add_u32 s64, s74, .Lsnap%=-.Lpc%=\n"
         "s_mov_b32 s65, s75\n"
+        "s_mov_b32 s91, s75\n"
         "s_mov_b32 s67, 0\n"
         "s_movk_i32 s68, 1696\n"
         "s_movk_i32 s69, 1696+5280-31\n"
@@ -842,13 +1256,130 @@ __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uin
         "s_cbranch_vccnz .Lundo%=\n"
         "s_cmp_lg_u32 s95, 0\n"
         "s_setpc_b64 s[96:97]\n"
+        // --- an indexed cartridge read without an LDS copy
+        ".Lhbm%=:\n"
+        "global_load_ubyte v123, v122, s[40:41]\n" HL_ROM_GO("s79", 3)
+        "s_waitcnt vmcnt(0)\n" HL_DO
+        ".Lhbmy%=:\n"
+        "global_load_ubyte v123, v122, s[40:41]\n" HL_ROM_GO("s78", 2)
+        "s_waitcnt vmcnt(0)\n" HL_DO
+        // --- an E0 (s42: 0) or 3F cartridge read at the word's address + v125: in the
+        // segment of 1 KB (below E0's hotspots in the last) or half of 2 KB it begins in
+        ".Lseg%=:\n"
+        "s_bfe_u32 s86, s76, 0x80010\n"
+        "s_bfe_u32 s89, s76, 0xc0010\n"
+        "s_lshr_b32 s87, s72, 14\n"
+        "s_cmp_lg_u32 s42, 0\n"
+        "s_cbranch_scc1 .Lhalf%=\n"
+        "s_lshr_b32 s88, s89, 10\n"
+        "s_mul_i32 s60, s88, 3\n"
+        "s_lshr_b32 s87, s87, s60\n"
+        "s_and_b32 s87, s87, 7\n"
+        "s_movk_i32 s61, 0x400\n"
+        "s_cmp_eq_u32 s88, 3\n"
+        "s_cselect_b32 s87, 7, s87\n"
+        "s_cselect_b32 s61, 0x3e0, s61\n"
+        "s_lshl_b32 s87, s87, 10\n"
+        "s_and_b32 s89, s89, 0x3ff\n"
+        "s_branch .Lsegc%=\n"
+        ".Lhalf%=:\n"
+        "s_lshl_b32 s87, s87, 11\n"
+        "s_bitcmp1_b32 s89, 11\n"
+        "s_cselect_b32 s87, s92, s87\n"
+        "s_and_b32 s89, s89, 0x7ff\n"
+        "s_movk_i32 s61, 0x800\n"
+        ".Lsegc%=:\n"
+        "v_add_u32 v122, s89, v125\n"
+        "v_add_u32 v124, s86, v125\n"
+        "v_cmp_le_u32 s[96:97], s61, v122\n" HL_CROSS(4)
+        HL_ROMBYTE(".Lhbm") HL_ROM_GO("s79", 3) HL_WAIT HL_DO
+        // --- a 3F slice (v122), if the same in every lane
+        ".Lslice%=:\n"
+        "s_nop 0\n"
+        "v_readfirstlane_b32 s87, v122\n"
+        "s_lshl_b32 s88, s87, 14\n"
+        "s_nop 1\n"
+        "v_cmp_ne_u32 vcc, s87, v122\n"
+        "s_cbranch_vccnz .Lout%=\n"
+        "s_add_u32 s72, s72, 8\n"
+        "s_and_b32 s72, s72, 0x3fff\n"
+        "s_or_b32 s72, s72, s88\n"
+        "s_load_dwordx4 s[76:79], s[70:71], s72\n" HL_WAIT HL_TGT("s76") HL_GO(3)
+        // --- ADC of groups with lanes in decimal mode (do_adc): operand in v123, or s86.
+        // v124: the binary sum, v116 its low byte, v120 its overflow
+        ".Ldadci%=:\n"
+        "v_mov_b32 v123, s86\n"
+        ".Ldadc%=:\n"
+        "v_add3_u32 v124, %[a], v123, %[c]\n"
+        "v_bitop3_b32 v120, %[a], v123, v124 bitop3:0x42\n"
+        "v_and_b32 v116, 0xff, v124\n"
+        "v_and_b32 v122, 15, %[a]\n"
+        "v_and_b32 v125, 15, v123\n"
+        "v_add3_u32 v122, v122, v125, %[c]\n"     // the low digits
+        "v_cmp_lt_u32 vcc, 9, v122\n"
+        "v_add_u32 v125, 6, v122\n"
+        "v_and_b32 v125, 15, v125\n"
+        "v_or_b32 v125, 16, v125\n"
+        "v_cndmask_b32 v122, v122, v125, vcc\n"
+        "v_and_b32 v125, 0xf0, %[a]\n"
+        "v_and_b32 v126, 0xf0, v123\n"
+        "v_bfe_i32 v118, v125, 0, 8\n"
+        "v_bfe_i32 v119, v126, 0, 8\n"
+        "v_add3_u32 v119, v118, v119, v122\n"     // the signed sum: N, V
+        "v_add3_u32 v125, v125, v126, v122\n"
+        "v_cmp_lt_u32 vcc, 0x9f, v125\n"
+        "v_add_u32 v126, 0x60, v125\n"
+        "v_add_u32 v117, 0x80, v119\n"
+        "v_cndmask_b32 v125, v125, v126, vcc\n"
+        "v_lshrrev_b32 v118, 8, v125\n"
+        "v_min_u32 v118, 1, v118\n"
+        "v_and_b32 v117, 0xffffff00, v117\n"
+        "v_min_u32 v117, 0x80, v117\n"
+        "v_min_u32 v115, 1, v116\n"               // Z by the binary sum
+        "v_and_b32 v119, 0x80, v119\n"
+        "v_lshl_or_b32 v115, v119, 1, v115\n"
+        "v_and_b32 v125, 0xff, v125\n"
+        "v_lshrrev_b32 v124, 8, v124\n"
+        "v_cndmask_b32 %[a], v116, v125, s[50:51]\n"
+        "v_cndmask_b32 %[c], v124, v118, s[50:51]\n"
+        "v_cndmask_b32 %[v], v120, v117, s[50:51]\n"
+        "v_cndmask_b32 %[nz], v116, v115, s[50:51]\n" HL_JUMP
+        // --- SBC of such groups (do_sbc): all flags by the binary difference
+        ".Ldsbci%=:\n"
+        "v_mov_b32 v123, s86\n"
+        ".Ldsbc%=:\n"
+        "v_xor_b32 v126, 0xff, v123\n"
+        "v_add3_u32 v124, %[a], v126, %[c]\n"
+        "v_bitop3_b32 %[v], %[a], v126, v124 bitop3:0x42\n"
+        "v_and_b32 v122, 15, %[a]\n"
+        "v_and_b32 v125, 15, v123\n"
+        "v_sub_u32 v122, v122, v125\n"
+        "v_add3_u32 v122, v122, %[c], -1\n"
+        "v_cmp_gt_i32 vcc, 0, v122\n"
+        "v_add_u32 v125, -6, v122\n"
+        "v_and_b32 v125, 15, v125\n"
+        "v_add_u32 v125, -16, v125\n"
+        "v_cndmask_b32 v122, v122, v125, vcc\n"
+        "v_and_b32 v125, 0xf0, %[a]\n"
+        "v_and_b32 v117, 0xf0, v123\n"
+        "v_sub_u32 v125, v125, v117\n"
+        "v_add_u32 v125, v125, v122\n"
+        "v_cmp_gt_i32 vcc, 0, v125\n"
+        "v_add_u32 v117, 0xffffffa0, v125\n"
+        "v_and_b32 %[nz], 0xff, v124\n"
+        "v_cndmask_b32 v125, v125, v117, vcc\n"
+        "v_and_b32 v125, 0xff, v125\n"
+        "v_lshrrev_b32 %[c], 8, v124\n"
+        "v_cndmask_b32 %[a], %[nz], v125, s[50:51]\n" HL_JUMP
         // --- handlers
         ".p2align 7\n"
         ".Lhb%=:\n"
-        HL_BLOCK(".Lhb", HL_TIA_LOG, HL_TIAX_LOG, HL_GRP0_LOG, HL_GRP1_LOG, HL_XY_LOG, HL_FLAG_LOG)
+        HL_BLOCK(".Lhb", HL_TIA_LOG, HL_TIAX_LOG, HL_GRP0_LOG, HL_GRP1_LOG, HL_XY_LOG, HL_FLAG_LOG, HL_RES_LOG, HL_FXY_LOG,
+                 HL_ATIA_LOG)
         ".p2align 7\n"
         ".Lhu%=:\n"
-        HL_BLOCK(".Lhu", HL_TIA_NOLOG, HL_TIAX_NOLOG, HL_GRP0_NOLOG, HL_GRP1_NOLOG, HL_XY_NOLOG, HL_FLAG_NOLOG)
+        HL_BLOCK(".Lhu", HL_TIA_NOLOG, HL_TIAX_NOLOG, HL_GRP0_NOLOG, HL_GRP1_NOLOG, HL_XY_NOLOG, HL_FLAG_NOLOG, HL_RES_NOLOG,
+                 HL_FXY_NOLOG, HL_ATIA_NOLOG)
         ".Lend%=:\n"
         "s_mov_b64 exec, s[44:45]\n"
         "s_mov_b32 m0, s43\n"
@@ -859,12 +1390,13 @@ __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uin
         : "+{s[48:49]}"(lanes), "+{s57}"(passes), "+{s58}"(rounds), [po] "+v"(H.po), [acc] "+v"(H.acc),
           [lines] "+v"(H.lines), [orow] "+v"(H.orow), "+{v[100:101]}"(H.lp), [obase] "+v"(H.obase), [a] "+v"(a),
           [x] "+v"(x), [y] "+v"(y), [p] "+v"(p), [nz] "+v"(nz), [c] "+v"(c), [v] "+v"(v), [hmp0] "+v"(hmp0),
-          [hmp1] "+v"(hmp1), [vsync] "+v"(vsync), [ic] "+v"(ic)
-        : "{s[70:71]}"(table), "{s[40:41]}"(rom), [key] "v"(H.key), [inpt4] "v"(inpt4), [swcha] "v"(swcha), [ram] "v"(ram), [tia] "v"(tia), [log] "v"(log),
+          [hmp1] "+v"(hmp1), [vsync] "+v"(vsync), [ic] "+v"(ic), [sp] "+v"(sp)
+        : "{s[70:71]}"(table), "{s[40:41]}"(rom), "{s39}"(R.lds), "{s42}"(R.span), "{s92}"(R.first),
+          [tm] "v"(T.tm), [tv] "v"(T.tv), [tsh] "v"(T.tshift), [key] "v"(H.key), [inpt4] "v"(inpt4), [swcha] "v"(swcha), [ram] "v"(ram), [tia] "v"(tia), [log] "v"(log),
           [log0] "v"((uint32_t)log), [xram] "v"(xram)
         : "memory", "scc", "vcc", "s43", "s44", "s45", "s46", "s47", "s50", "s51", "s52", "s53", "s54", "s55", "s56",
           "s59", "s60", "s61", "s62", "s63", "s64", "s65", "s66", "s67", "s68", "s69", "s72", "s73", "s74", "s75",
-          "s76", "s77", "s78", "s79", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89", "s93",
+          "s76", "s77", "s78", "s79", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89", "s90", "s91", "s93",
           "s94", "s95", "s96", "s97", "s98", "s99", "v102", "v103", "v104", "v105", "v106", "v107", "v108", "v111", "v112",
           "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", "v123", "v124", "v125",
           "v126");

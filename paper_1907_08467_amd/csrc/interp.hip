@@ -1135,13 +1135,55 @@ __device__ __forceinline__ uint32_t cart_store_class(const Wave& W, uint32_t a) 
 // Predecoded word: store class (7 bits) | slot << 7 | b1 << 16 | b2 << 24.  The
 // slot is the hot loop's handler (hotloop.h); a HOT_REAL word carries the
 // opcode in bits 0-6 and 15 instead of a class.
+//
+// The two-step reads' operation (HW_*), and the modes whose slots they have.
+constexpr uint32_t hot_work(int mn) {
+    switch (mn) {
+    case LDA: return HW_LDA; case LDX: return HW_LDX; case LDY: return HW_LDY; case AND: return HW_AND;
+    case ORA: return HW_ORA; case EOR: return HW_EOR; case CMP: return HW_CMP; case CPX: return HW_CPX;
+    case CPY: return HW_CPY; case BIT: return HW_BIT; case ADC: return HW_ADC; case SBC: return HW_SBC;
+    case ASL: return HW_ASL; case ROL: return HW_ROL; case LSR: return HW_LSR; case ROR: return HW_ROR;
+    case DEC: return HW_DEC; case INC: return HW_INC;
+    }
+    return HW_NONE;
+}
+constexpr uint32_t kTwoStepFirst = HOT_Z_CONST, kTwoStepEnd = HOT_SEG_Y + 1;
+constexpr int two_step_mode(uint32_t slot) {
+    switch (slot) {
+    case HOT_Z_CONST: case HOT_Z_INPT4: return ZP;
+    case HOT_ZX: case HOT_ZX_RMW: return ZPX;
+    case HOT_ZY: return ZPY;
+    case HOT_AX_ROM: case HOT_AX_RAM: case HOT_SEG_X: return ABX;
+    case HOT_AY_ROM: case HOT_AY_RAM: case HOT_SEG_Y: return ABY;
+    case HOT_IY_ROM: return IZY;
+    default: return ABS;
+    }
+}
+// The opcode a slot runs, whole words for the scalar unit: op[slot], two[32
+// (slot - kTwoStepFirst) + operation] for the two-step reads, st[register] for
+// stores of any register (the class's bits 5-6: A, X, Y).
 struct HotOps {
-    uint32_t op[kHotSlots];                      // whole words: the scalar unit loads them
-    constexpr HotOps() : op() {
+    uint32_t op[kHotSlots], two[32 * (kTwoStepEnd - kTwoStepFirst)], st_zp[4], st_abs[4];
+    constexpr HotOps() : op(), two(), st_zp(), st_abs() {
         for (uint32_t i = 0; i < kHotSlots; ++i) op[i] = kHotSlotOp[i];
+        for (uint32_t o = 0; o < 256; ++o) {
+            const OpInfo I = decode((int)o);
+            const uint32_t w = hot_work(I.mn);
+            for (uint32_t s = kTwoStepFirst; w != HW_NONE && s < kTwoStepEnd; ++s)
+                if (two_step_mode(s) == I.md) two[32 * (s - kTwoStepFirst) + w] = o;
+        }
+        st_zp[0] = 0x85; st_zp[1] = 0x86; st_zp[2] = 0x84;
+        st_abs[0] = 0x8D; st_abs[1] = 0x8E; st_abs[2] = 0x8C;
     }
 };
 __constant__ HotOps kHotOps = HotOps();
+struct HotWorks {                                // an opcode's operation
+    uint8_t w[256];
+    constexpr HotWorks() : w() {
+        for (int i = 0; i < 256; ++i) w[i] = (uint8_t)hot_work(decode(i).mn);
+    }
+};
+__constant__ HotWorks kHotWorkOf = HotWorks();
 struct HotSlots {                                // an opcode's slot (hot_slot)
     uint8_t s[256];
     constexpr HotSlots() : s() {
@@ -1152,7 +1194,11 @@ __constant__ HotSlots kHotSlot = HotSlots();
 __device__ __forceinline__ uint32_t pre_slot(uint32_t q) { return (q >> 7) & 0xFF; }
 __device__ __forceinline__ uint32_t pre_op(uint32_t q) {
     const uint32_t slot = pre_slot(q);
-    return slot == HOT_REAL ? (q & 0x7F) | ((q >> 8) & 0x80) : kHotOps.op[slot];
+    if (slot == HOT_REAL) return (q & 0x7F) | ((q >> 8) & 0x80);
+    if (slot - kTwoStepFirst < kTwoStepEnd - kTwoStepFirst) return kHotOps.two[32 * (slot - kTwoStepFirst) + (q & 31)];
+    if (slot == HOT_RESP || slot == HOT_RESM) return kHotOps.st_zp[(q >> 5) & 3];
+    if (slot == HOT_HS_ST) return kHotOps.st_abs[(q >> 5) & 3];
+    return kHotOps.op[slot];
 }
 
 // Write of per-lane value v to TIA register class `sc` (SC_TIA/S/G | code) at
@@ -1611,11 +1657,14 @@ __device__ __forceinline__ uint32_t fop(Cpu& c, const Wave& W, Fast& F, uint32_t
 #define VCS_FAST_16(o) VCS_FAST_4(o) VCS_FAST_4((o) + 4) VCS_FAST_4((o) + 8) VCS_FAST_4((o) + 12)
 #define VCS_FAST_64(o) VCS_FAST_16(o) VCS_FAST_16((o) + 16) VCS_FAST_16((o) + 32) VCS_FAST_16((o) + 48)
 
-// Runs the instruction at the place of the lanes in exec (one group of the hot
-// loop, at a place inside the cartridge window) through the full dispatch.
-// Returns false when the per-lane path must execute it.
+// Runs instructions of the lanes in exec (one group of the hot loop, at a place
+// inside the cartridge window) through the full dispatch: the one that the loop
+// left, and those after it up to one that the loop runs (the way there and back
+// costs about three instructions here), a place the per-lane path must take, a
+// branch that parts the lanes, or, when others wait (`partial`), the next line.
+// Returns how many it ran; 0: the per-lane path must execute the first.
 template <bool TRACK>
-__device__ __forceinline__ bool run_cold(Cpu& c, const Wave& W) {
+__device__ __forceinline__ uint32_t run_cold(Cpu& c, const Wave& W, uint32_t partial) {
     Fast F;
     F.pc = rfl(c.pc);
     F.bank = rfl(c.bank);
@@ -1623,25 +1672,34 @@ __device__ __forceinline__ bool run_cold(Cpu& c, const Wave& W) {
     F.fl = rfl(c.fl);
     F.orow = (uint32_t)(rfl(c.open_row) + 1);
     F.logon = rfl(c.log != nullptr ? 1u : 0u);
-    uint32_t st = FS_EXIT;
-    const uint32_t q = rfl(W.pre[(F.bank << 12) | (F.pc & 0xFFF)]);
-    const uint32_t op = pre_op(q), b1 = (q >> 16) & 0xFF, b2 = q >> 24;
-    switch (op) {
-        VCS_FAST_64(0x00)
-        VCS_FAST_64(0x40)
-        VCS_FAST_64(0x80)
-        VCS_FAST_64(0xC0)
+    const uint32_t cap = rfl(c.cap), stop = partial ? min(cap, 76 * (F.cyc / 76 + 1)) : cap;
+    uint32_t st, n = 0;
+    uint32_t q = rfl(W.pre[(F.bank << 12) | (F.pc & 0xFFF)]);
+    for (;;) {
+        const uint32_t op = pre_op(q), b1 = (q >> 16) & 0xFF, b2 = q >> 24;
+        st = FS_EXIT;
+        switch (op) {
+            VCS_FAST_64(0x00)
+            VCS_FAST_64(0x40)
+            VCS_FAST_64(0x80)
+            VCS_FAST_64(0xC0)
+        }
+        if (st == FS_EXIT) break;
+        ++n;
+        if (st == FS_LANE || F.cyc >= stop || (F.pc & 0x1FFF) - 0x1000u > 0xFFCu) break;
+        q = rfl(W.pre[(F.bank << 12) | (F.pc & 0xFFF)]);
+        if (pre_slot(q) != HOT_REAL) break;
     }
-    if (st == FS_EXIT) return false;
-    if (st == FS_NEXT) {                      // pc and cycle are still common to all lanes
+    if (n == 0) return 0;
+    if (st != FS_LANE) {                      // pc and cycle are still common to all lanes
         c.pc = F.pc;
         c.cyc = F.cyc;
     }
-    c.icount++;
-    c.ucount++;
+    c.icount += n;
+    c.ucount += n;
     c.bank = F.bank;
     c.open_row = (int32_t)F.orow - 1;
-    return true;
+    return n;
 }
 #undef VCS_FAST_64
 #undef VCS_FAST_16
@@ -1835,6 +1893,14 @@ __global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes) k_interp
         const uint64_t pre_addr = (uint64_t)W.pre, rom_addr = (uint64_t)(A.roms + (size_t)rom_id * kRomSlot);
         const uint64_t table = (uint64_t)rfl((uint32_t)pre_addr) | ((uint64_t)rfl((uint32_t)(pre_addr >> 32)) << 32);
         const uint64_t rom_hbm = (uint64_t)rfl((uint32_t)rom_addr) | ((uint64_t)rfl((uint32_t)(rom_addr >> 32)) << 32);
+        const uint32_t sc_end = cm_sc(W) ? 0x100u : 0u, hs_n = (W.cm.a >> 4) & 15;
+        HotRom hot_rom{RC > 0 ? (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)s_rom : ~0u, sc_end,
+                       (hs_n ? W.cm.a >> 8 : 0x1000u) - sc_end};
+        if (cm_kind(W) == CART_E0) hot_rom.span = 0;
+        if (cm_kind(W) == CART_3F) {
+            hot_rom.first = W.cm.b & 0xFFFF;
+            hot_rom.span = 1;
+        }
         // ---------------------------------------------------------- main loop
         while (__any(active)) {
             uint32_t op = 0, b1 = 0, b2 = 0;
@@ -1854,11 +1920,14 @@ __global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes) k_interp
             H.key = ((c.pc >> 12) << 28) | (c.log ? kHotLogged : 0u) | ((uint32_t)c.fl & (kHotLogged - 1));
             uint32_t nzv = ((c.p & FN) << 1) | (((c.p >> 1) & 1) ^ 1), cf = c.p & FC, vf = c.p << 1;
             uint32_t ic = 0, hot_passes = 0, hot_rounds = 0;
+            // (a timer that ran out long ago is kept in 32 bits: only the low byte of its age shows)
+            const int64_t age = (int64_t)c.base - c.tbase;
+            const HotTimer timer{age < (1 << 30) ? (uint32_t)age : (1u << 30) + ((uint32_t)age & 0xFF), c.tv, c.tshift};
             const uint64_t group =
                 hot_wave(__builtin_amdgcn_ballot_w64(active), table, rom_hbm, H, c.a, c.x, c.y, c.p, nzv, cf, vf, c.hmp0, c.hmp1, c.vsync, c.inpt4,
                          c.swcha, ic,
                          hot_passes, hot_rounds, W.ram_lds + c.ram_off, W.tia_lds + c.tia_off, (uint64_t)c.log,
-                         (uint64_t)c.xram);
+                         (uint64_t)c.xram, c.sp, timer, hot_rom);
             passes += hot_passes;
             rounds += hot_rounds;
             if (active) {
@@ -1876,13 +1945,13 @@ __global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes) k_interp
                 c.open_base = H.obase - kSnapArea / 4;
             }
             const bool in = group ? __builtin_amdgcn_inverse_ballot_w64(group) : active;
-            bool uni = false;
-            if (group != 0 && in && hot && c.cyc < c.cap) uni = run_cold<TRACK>(c, W);
-            const bool ran_uniform = __any(uni);
-            if (ran_uniform) {
+            uint32_t cold = 0;
+            const uint32_t partial = __builtin_amdgcn_ballot_w64(active) != group ? 1u : 0u;
+            if (group != 0 && in && hot && c.cyc < c.cap) cold = run_cold<TRACK>(c, W, partial);
+            if (__any(cold != 0)) {
                 // Nothing else happens this round (no per-lane pass, no frame
                 // change): the next one starts at once.
-                ++passes;
+                passes += (uint32_t)__builtin_amdgcn_readlane((int)cold, (int)__builtin_ctzll(group));
                 continue;
             }
             const bool go = in;
@@ -1984,7 +2053,7 @@ __global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes) k_interp
             // Every iteration moves some lane on (the earliest lane always
             // runs); if none moved, stop the wave's frames with an error
             // instead of spinning.
-            if (!__any(ran_lane != 0 || uni || ended) && active) {
+            if (!__any(ran_lane != 0 || ended) && active) {
                 c.err |= ERR_FRAME_CAP;
                 ended = true;
                 end_t = c.cyc;
@@ -2087,7 +2156,7 @@ __global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes) k_interp
 // registers kept as they are, GRP0 / GRP1, WSYNC or nothing emulated (object
 // resets, enables and what the per-lane path takes are not).  Entries past
 // offset $FFD are never used.
-__global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre) {
+__global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre, uint32_t track) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= R.n_vbanks * 4096u) return;
     const uint32_t bank = i >> 12, off = i & 0xFFF;
@@ -2095,7 +2164,8 @@ __global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre) {
     const uint32_t b1 = off + 1 < 4096 ? rom[cart_rom_off(R, bank, 0x1000 | (off + 1))] : 0;
     const uint32_t b2 = off + 2 < 4096 ? rom[cart_rom_off(R, bank, 0x1000 | (off + 2))] : 0;
     const uint32_t d = kDecode.w[op];
-    const uint32_t md = d & 15, len = (d >> DW_LEN) & 3;
+    const uint32_t md = d & 15, len = (d >> DW_LEN) & 3, work = kHotWorkOf.w[op];
+    const bool st_abs = op == 0x8C || op == 0x8D || op == 0x8E;
     uint32_t slot = HOT_REAL, cls = 0;
     if (off + len <= 0xFFC) {                          // (the hot loop loads four words from there)
         const bool st = op == 0x84 || op == 0x85 || op == 0x86;
@@ -2106,7 +2176,16 @@ __global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre) {
             else if (cls == SC_WSYNC) slot = HOT_WSYNC;
             else if (cls == SC_IGNORE) slot = HOT_ST_NOP;
             else if (cls >= SC_TIA && cls < SC_TIAS) slot = k ? k : hot_tia_slot(cls & 0x1F);
-            else if (op == 0x85 && cls >= (SC_TIAS | kScFlag0) && cls < SC_TIAG) slot = HOT_FLAG + 2 * ((cls & 0x1F) - kScFlag0);
+            else if (cls >= (SC_TIAS | kScFlag0) && cls < SC_TIAG) {
+                const uint32_t f = (cls & 0x1F) - kScFlag0;
+                slot = op == 0x85 ? HOT_FLAG + 2 * f : (op == 0x86 ? HOT_FLAG_X : HOT_FLAG_Y) + f;
+            } else if (cls >= SC_TIAS && cls < SC_TIAG) {      // an object reset
+                slot = (cls & 0x1F) <= R_P1X ? HOT_RESP : HOT_RESM;
+                cls = (cls & 0x1F) | ((op == 0x85 ? 0u : op == 0x86 ? 1u : 2u) << 5);
+            } else if (cls == SC_3F) {
+                slot = HOT_3F + (op == 0x85 ? 0 : op == 0x86 ? 1 : 2);
+                cls = R.tf_mask;
+            }
             else if (cls == SC_EXIT && ((b1 & 0x3E) == 0x20 || ((b1 & 0x3F) == 0 && op == 0x85)) &&
                      !(R.kind == CART_3F && b1 <= 0x3F))   // HMP0, HMP1, VSYNC
                 slot = (b1 & 0x3F) == 0 ? HOT_VSYNC : HOT_HMP + (op == 0x85 ? 0 : op == 0x86 ? 2 : 4) + (b1 & 1);
@@ -2117,27 +2196,92 @@ __global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre) {
             const uint32_t k = op >> 5;
             const uint32_t cross = HOT_BPL_X + k;
             if (t <= 0xFFC) slot = ((t ^ next) & 0xF00) ? cross : kHotSlot.s[op];
-        } else if (op == 0x4C) {                       // JMP: the target's window
+        } else if (op == 0x4C || op == 0x20) {         // JMP, JSR: the target's window
             const uint32_t t = (b1 | (b2 << 8)) & 0x1FFF;
-            if (t - 0x1000u <= 0xFFCu) slot = kHotSlot.s[op];
-        } else if (md == ABS) {
+            if (t - 0x1000u <= 0xFFCu) slot = op == 0x4C ? kHotSlot.s[op] : HOT_JSR;
+        } else if (md == ABS && st_abs) {
+            const uint32_t a = (b1 | (b2 << 8)) & 0x1FFF, r = op == 0x8D ? 0u : op == 0x8E ? 1u : 2u;
+            cls = cart_store_class(R.kind, R.sc, a);
+            if (cls == SC_RAM) slot = HOT_STA_A + r;
+            else if (cls >= SC_TIA && cls < SC_TIAS) slot = HOT_A_TIA + 3 * r;
+            else if (cls == (SC_TIAG | R_GRP0)) slot = HOT_A_TIA + 3 * r + 1;
+            else if (cls == (SC_TIAG | R_GRP1)) slot = HOT_A_TIA + 3 * r + 2;
+            else if (cls == SC_XRAM) {
+                if (!(a & 0x80) && op == 0x8D) slot = HOT_XW;
+            } else if ((a & 0x1000) && R.kind == CART_LINEAR) {
+                const uint32_t to = cart_hotspot(R.kind, R.hs_first, R.hs_n, 8, a);
+                if (to < 8) {
+                    slot = HOT_HS_ST;
+                    cls = to | (r << 5);
+                }
+            }
+        } else if (md == ABS && work > HW_SBC && work <= HW_INC) {
+            cls = work;
+            if (((b1 | (b2 << 8)) & 0x1280) == 0x0080) slot = HOT_A_RMW;
+        } else if (md == ABS && work <= HW_SBC) {
             const uint32_t a = (b1 | (b2 << 8)) & 0x1FFF;
-            if ((a & 0x1000) && R.sc && !(a & 0xF00)) {    // Superchip RAM: reads of the read port, writes of the other
+            cls = work;
+            if ((a & 0x1000) && R.sc && !(a & 0xF00)) {    // Superchip RAM: reads of the read port
                 if (a & 0x80)
                     slot = op == 0xAD ? HOT_XR_LDA : op == 0x6D ? HOT_XR_ADC : op == 0x2D ? HOT_XR_AND
                          : op == 0x4D ? HOT_XR_EOR : op == 0x0D ? HOT_XR_ORA : HOT_REAL;
-                else if (op == 0x8D)
-                    slot = HOT_XW;
-            } else if ((a & 0x1000) && op == 0xAD && R.kind == CART_LINEAR) {
-                const uint32_t to = cart_hotspot(R.kind, R.hs_first, R.hs_n, 8, a);
-                slot = to < 8 ? HOT_HS : HOT_ABS;
-                cls = to & 7;
-            } else if ((a & 0x1287) == 0x0280 && (op == 0xAD || op == 0x4D)) {
-                slot = op == 0xAD ? HOT_SWCHA_LDA : HOT_SWCHA_EOR;
+            } else if (a & 0x1000) {
+                if (R.kind == CART_LINEAR) {
+                    const uint32_t to = cart_hotspot(R.kind, R.hs_first, R.hs_n, 8, a);
+                    if (to >= 8) slot = op == 0xAD ? HOT_ABS : HOT_A_ROM;
+                    else if (op == 0xAD) {
+                        slot = HOT_HS;
+                        cls = to;
+                    }
+                } else if (R.kind == CART_E0 && op == 0xAD && (a & 0xFFF) - 0xFE0u < 24u) {
+                    slot = HOT_E0;
+                } else if (cart_hotspot(R.kind, R.hs_first, R.hs_n, bank, a) == bank &&
+                           !(R.kind == CART_E0 && (a & 0xFFF) >= 0xFE0)) {
+                    slot = HOT_SEG;
+                }
+            } else if (!(a & 0x80)) {                      // TIA
+                if ((a & 0xF) != 0xC && ((a & 0xF) >= 8 || !track)) {
+                    slot = HOT_A_CONST;
+                    cls |= (a & 0xF) == 0xD ? 1u << 5 : 0u;
+                }
+            } else if (!(a & 0x200)) {
+                slot = HOT_A_RAM;
+            } else if (!(a & 4)) {                         // the ports
+                if ((a & 3) == 0) slot = op == 0xAD ? HOT_SWCHA_LDA : op == 0x4D ? HOT_SWCHA_EOR : HOT_A_SWCHA;
+                else slot = HOT_A_CONST;
+                if ((a & 3) == 2) cls |= 2u << 5;
+            } else if (!(a & 1)) {
+                slot = HOT_A_INTIM;
             }
-        } else if (op == 0xA5 && b1 < 0x80 && (b1 & 0xF) == 0xC) {
-            slot = HOT_INPT4;
-        } else if (md != ZP || b1 >= 0x80) {
+        } else if (md == ZP && work <= HW_SBC && b1 < 0x80) {  // a TIA read
+            cls = work;
+            if ((b1 & 0xF) == 0xC) {
+                slot = op == 0xA5 ? HOT_INPT4 : HOT_Z_INPT4;
+            } else if ((b1 & 0xF) >= 8 || !track) {
+                slot = HOT_Z_CONST;
+                cls |= (b1 & 0xF) == 0xD ? 1u << 5 : 0u;
+            }
+        } else if (md == ZPX || md == ZPY) {
+            cls = work;
+            if (work <= HW_SBC) slot = md == ZPX ? HOT_ZX : HOT_ZY;
+            else if (work <= HW_INC && md == ZPX) slot = HOT_ZX_RMW;
+            else slot = op == 0x95 ? HOT_STA_ZX : op == 0x94 ? HOT_STY_ZX : op == 0x96 ? HOT_STX_ZY : HOT_REAL;
+        } else if (md == ABX || md == ABY) {
+            const uint32_t base = (b1 | (b2 << 8)) & 0x1FFF;
+            cls = work;
+            if (base >= 0x80 && base <= 0xFF) {            // RAM, as far as the index leaves it there
+                if (work <= HW_SBC) slot = md == ABX ? HOT_AX_RAM : HOT_AY_RAM;
+                else slot = op == 0x9D ? HOT_STA_AX : op == 0x99 ? HOT_STA_AY : HOT_REAL;
+            } else if ((base & 0x1000) && work <= HW_SBC) {
+                if (R.kind == CART_LINEAR) slot = md == ABX ? HOT_AX_ROM : HOT_AY_ROM;
+                else slot = md == ABX ? HOT_SEG_X : HOT_SEG_Y;
+            }
+        } else if (md == IZY && R.kind == CART_LINEAR && work <= HW_SBC && b1 >= 0x80 && b1 < 0xFF) {
+            slot = HOT_IY_ROM;
+            cls = work;
+        } else if (op == 0x08 || op == 0x28) {
+            slot = op == 0x08 ? HOT_PHP : HOT_PLP;
+        } else if (md == IMP || md == ACC || md == IMM || (md == ZP && b1 >= 0x80)) {
             slot = kHotSlot.s[op];
         }
     }
@@ -2145,9 +2289,9 @@ __global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre) {
     pre[i] = low | (slot << 7) | (b1 << 16) | (b2 << 24);
 }
 
-void launch_predecode(const uint8_t* rom, const RomInfo& info, uint32_t* pre, hipStream_t s) {
+void launch_predecode(const uint8_t* rom, const RomInfo& info, uint32_t* pre, uint32_t track, hipStream_t s) {
     const uint32_t n = info.n_vbanks * 4096u;
-    hipLaunchKernelGGL(k_predecode, dim3((n + 255) / 256), dim3(256), 0, s, rom, info, pre);
+    hipLaunchKernelGGL(k_predecode, dim3((n + 255) / 256), dim3(256), 0, s, rom, info, pre, track);
 }
 
 // Waves per block of a launch that tracks collisions: as many as the chip can
