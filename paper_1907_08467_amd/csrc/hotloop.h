@@ -224,7 +224,7 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     "s_cselect_b32 s87, s9" tk ", (2<<25)+1\n"             \
     "s_cselect_b64 s[96:97], exec, 0\n"                    \
     "s_cmp_lg_u64 vcc, s[96:97]\n"                         \
-    "s_cbranch_scc1 .Lpart" tk "%=\n"                      \
+    "s_cbranch_scc1 .Lpart" tk "_%=\n"                      \
     "s_cmp_eq_u64 s[96:97], exec\n" HL_WAIT                \
     "s_cselect_b64 s[76:77], s[60:61], s[76:77]\n"         \
     "s_cselect_b64 s[78:79], s[62:63], s[78:79]\n"         \
@@ -322,24 +322,24 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     "s_cselect_b32 s87, -9, s80\n"                         \
     "s_lshr_b32 s88, s73, 25\n"                            \
     "s_cmp_lt_u32 s88, 75\n"                               \
-    "s_cbranch_scc1 .Lhbl" id "%=\n"                       \
+    "s_cbranch_scc1 .Lhbl" id "_%=\n"                       \
     "s_cmp_lg_u32 s87, s83\n"                              \
     "s_mul_i32 s87, s88, 3\n"                              \
-    "s_cbranch_scc1 .Lrow" id "%=\n"                       \
-    ".Lent" id "%=:\n"                                     \
+    "s_cbranch_scc1 .Lrow" id "_%=\n"                       \
+    ".Lent" id "_%=:\n"                                     \
     "s_add_u32 s87, s87, " code8 "\n"                      \
     "v_lshl_or_b32 v123, " val ", 16, s87\n"               \
     "global_store_dword v[100:101], v123, off\n"           \
     "v_lshl_add_u64 v[100:101], 1, 2, v[100:101]\n"        \
-    ".Lreg" id "%=:\n" write HL_JUMP                       \
-    ".Lhbl" id "%=:\n"                                     \
+    ".Lreg" id "_%=:\n" write HL_JUMP                       \
+    ".Lhbl" id "_%=:\n"                                     \
     "s_add_u32 s87, s87, 1\n"                              \
     "s_cmp_lg_u32 s87, s83\n"                              \
-    "s_cbranch_scc1 .Lrow" id "%=\n" write HL_JUMP         \
-    ".Lrow" id "%=:\n"                                     \
+    "s_cbranch_scc1 .Lrow" id "_%=\n" write HL_JUMP         \
+    ".Lrow" id "_%=:\n"                                     \
     "s_swappc_b64 s[96:97], s[64:65]\n"                    \
-    "s_cbranch_scc0 .Lent" id "%=\n"                       \
-    "s_branch .Lreg" id "%=\n"
+    "s_cbranch_scc0 .Lent" id "_%=\n"                       \
+    "s_branch .Lreg" id "_%=\n"
 #define HL_TIA_LOG(B, slot, code)                          \
     HL_ORG(B, slot) HL_WAIT HL_TGT("s78") HL_FETCH(2)      \
     HL_LOGGED("t" #code, "%[a]", #code "*256-224", "ds_write_b8 %[tia], %[a] offset:" #code "\n")
@@ -1105,10 +1105,10 @@ __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uin
         "s_cselect_b32 s83, -2, s83\n"
         HL_WAIT HL_TGT("s76") HL_JUMP
         // --- lanes part at a branch (vcc: taken): the others wait
-        ".Lpart8%=:\n"
+        ".Lpart8_%=:\n"
         "s_mov_b32 s94, 3<<25\n"
         "s_branch .Lpart%=\n"
-        ".Lpart9%=:\n"
+        ".Lpart9_%=:\n"
         "s_mov_b32 s94, 4<<25\n"
         ".Lpart%=:\n"
         HL_WAIT
@@ -1142,7 +1142,7 @@ __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uin
         ".Lsync%=:\n"
         HL_WAIT
         "s_add_u32 s87, s73, 2<<25\n"
-        "s_cbranch_scc1 .Lsync2%=\n"
+        "s_cbranch_scc1 .Lstall%=\n"
         "s_and_b32 s73, s73, 0x1ffffff\n"
         "s_add_u32 s73, s73, (52<<25)+1\n"
         "s_cmp_eq_u32 s80, 0\n"
@@ -1166,7 +1166,7 @@ __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uin
         "v_writelane_b32 v102, s86, m0\n"
         "v_writelane_b32 v103, s87, m0\n"
         "s_branch .Lpick%=\n"
-        ".Lsync2%=:\n"                             // a write at the line's end stalls a line longer
+        ".Lstall%=:\n"                             // a write at the line's end stalls a line longer
         "s_add_u32 s80, s80, 1\n"
         "s_sub_u32 s72, s72, 8\n"
         "s_branch .Lout%=\n"

@@ -120,3 +120,12 @@ def test_the_check_sees_a_missing_write(line, reg):
     assert line in lines
     found = unwritten([l for l in lines if l != line], pinned)
     assert any(r == reg for r, _ in found) == (reg is not None)
+
+
+def test_labels_differ_in_every_copy():
+    """The compiler appends a number to each label of a copy of the block: a label
+    that ends in a digit could become another one's (.Lsync2 of copy 0, .Lsync of 20)."""
+    src = open(os.path.join(CSRC, "hotloop.h")).read()
+    labels = set(re.findall(r"(\.L\w*)%=", src))
+    assert len(labels) > 20 and not [l for l in labels if l[-1].isdigit()]
+    assert not re.search(r'(?:#?\b(?:id|tk|code|k|slot)) "%=', src)     # a macro's argument at the end
