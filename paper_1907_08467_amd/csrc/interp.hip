@@ -781,7 +781,7 @@ constexpr uint32_t kCxPre = 8;
 // mostly log the same registers at the same pixels of a row, so a wave's lanes
 // draw the same objects anew at the same time (lanes on different rows of one
 // env took 3 times as long).
-__device__ __attribute__((noinline)) void cx_scan_share(CxJob* jobs, uint32_t m, uint32_t tid, uint32_t n_threads) {
+__device__ __forceinline__ void cx_scan_rows(CxJob* jobs, uint32_t m, uint32_t tid, uint32_t n_threads) {
     const uint32_t runs = n_threads / m, run = tid / m;
     if (run >= runs) return;
     CxJob& J = jobs[tid - run * m];
@@ -871,8 +871,18 @@ __device__ __attribute__((noinline)) void cx_scan_share(CxJob* jobs, uint32_t m,
     if (cx) atomicOr(&J.cx, cx);
 }
 
+// The emulating wave's own share: a call, so that the scan's registers are not
+// added to those of the emulation (which then spills some around it).
+__device__ __attribute__((noinline)) void cx_scan_share(CxJob* jobs, uint32_t m, uint32_t n_threads) {
+    cx_scan_rows(jobs, m, threadIdx.x, n_threads);
+}
+
+// Who scans: nobody, every wave of the block, or the helper waves alone.
+enum : int { TRACK_NONE = 0, TRACK_ALL = 1, TRACK_HELPERS = 2 };
+
 // Scan for the lanes with `scan` up to (row_end, x_end).  Called by the whole
 // emulating wave; `jobs` has a place per lane, *n_jobs is the helpers' word.
+template <int TRACK>
 __device__ __forceinline__ void cx_scan(Cpu& c, CxJob* jobs, uint32_t* n_jobs, bool scan, int32_t row_end,
                                         int32_t x_end) {
     if (row_end >= kRows) {
@@ -892,7 +902,7 @@ __device__ __forceinline__ void cx_scan(Cpu& c, CxJob* jobs, uint32_t* n_jobs, b
     *n_jobs = m;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the log's stores, the hot loop's too
     __syncthreads();
-    cx_scan_share(jobs, m, threadIdx.x, blockDim.x);
+    if constexpr (TRACK == TRACK_ALL) cx_scan_share(jobs, m, blockDim.x);
     __syncthreads();
     if (work) {
         c.cx |= jobs[place].cx;
@@ -904,13 +914,14 @@ __device__ __forceinline__ void cx_scan(Cpu& c, CxJob* jobs, uint32_t* n_jobs, b
 // Scan the pixels through colour clock `through` (relative to the base line)
 // into the latches, for the lanes with `scan`; the rows the beam has reached
 // get their snapshots first (as the next logged write would take them).
+template <int TRACK>
 __device__ __forceinline__ void cx_catch_up(Cpu& c, const Wave& W, CxJob* jobs, uint32_t* n_jobs, bool scan,
                                             int32_t through) {
     const int32_t line = through / 228, h = through % 228;
     const int32_t row = line - c.fl - kFirstRow;
     scan = scan && row >= 0;
     if (scan) log_advance(c, W, h >= 68 ? row : row - 1);
-    cx_scan(c, jobs, n_jobs, scan, row, h >= 68 ? h - 68 + 1 : 0);
+    cx_scan<TRACK>(c, jobs, n_jobs, scan, row, h >= 68 ? h - 68 + 1 : 0);
 }
 
 // Position a RESPx (players, +5) or RESMx / RESBL (+4) write at cycle t sets.
@@ -1733,13 +1744,16 @@ constexpr int kScanWaves = 8;
 // from its HBM slot through the caches (launches with a ROM larger than 8 KB,
 // which would otherwise need 32 KB of LDS per wave and cut the waves per CU
 // by three).
-// TRACK: collision latches tracked (the scan code exists only in that
-// instantiation, so the other keeps its registers).  NOOPS: the reset no-op
+// TRACK: collision latches tracked (TRACK_NONE has no scan code and keeps its
+// registers; in TRACK_HELPERS the scan's registers are not the emulating wave's,
+// so nothing spills).  NOOPS: the reset no-op
 // frames of restarted envs (envs with no frames to run leave at once, the
 // step counter stays); a separate instantiation, so the step's kernel keeps
-// its code.
-template <int LL, int RC, bool TRACK, bool NOOPS>
-__global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes) k_interp(InterpArgs A, const uint32_t* __restrict__ pre_all) {
+// its code.  Registers for three waves per SIMD where the LDS holds as many (no
+// latches; 170 were 2 too many), else for two.
+template <int LL, int RC, int TRACK, bool NOOPS>
+__global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes, TRACK ? 2 : 3)
+    k_interp(InterpArgs A, const uint32_t* __restrict__ pre_all) {
     __shared__ uint32_t s_rom[RC ? RC / 4 + 4 : 1];
     __shared__ uint32_t s_ram[(LL + 1) * kRamStride / 4];
     __shared__ uint32_t s_tia[(LL + 1) * kTiaStride / 4];
@@ -1751,7 +1765,8 @@ __global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes) k_interp
                 __syncthreads();
                 const uint32_t m = __builtin_amdgcn_readfirstlane(s_njobs);
                 if (m == 0) return;
-                cx_scan_share(s_jobs, m, threadIdx.x, blockDim.x);
+                constexpr uint32_t first = TRACK == TRACK_HELPERS ? kLanes : 0;
+                cx_scan_rows(s_jobs, m, threadIdx.x - first, blockDim.x - first);
                 __syncthreads();
             }
         }
@@ -1947,7 +1962,7 @@ __global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes) k_interp
             const bool in = group ? __builtin_amdgcn_inverse_ballot_w64(group) : active;
             uint32_t cold = 0;
             const uint32_t partial = __builtin_amdgcn_ballot_w64(active) != group ? 1u : 0u;
-            if (group != 0 && in && hot && c.cyc < c.cap) cold = run_cold<TRACK>(c, W, partial);
+            if (group != 0 && in && hot && c.cyc < c.cap) cold = run_cold<TRACK != TRACK_NONE>(c, W, partial);
             if (__any(cold != 0)) {
                 // Nothing else happens this round (no per-lane pass, no frame
                 // change): the next one starts at once.
@@ -1960,7 +1975,7 @@ __global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes) k_interp
                 // bytes fetched from the TIA read registers show the latches
                 // through the fetch cycle's pixels, 3t+2
                 const bool scan = go && away && c.cyc < c.cap;
-                if (__any(scan)) cx_catch_up(c, W, s_jobs, &s_njobs, scan, 3 * (int32_t)c.cyc + 2);
+                if (__any(scan)) cx_catch_up<TRACK>(c, W, s_jobs, &s_njobs, scan, 3 * (int32_t)c.cyc + 2);
             }
             if (go) {
                 if (c.cyc >= c.cap) {
@@ -2006,7 +2021,7 @@ __global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes) k_interp
                 if constexpr (TRACK) {
                     const bool again = todo && c.cx_need >= 0;   // an instruction that read the latches runs again
                     if (__any(again)) {
-                        cx_catch_up(c, W, s_jobs, &s_njobs, again, c.cx_need);
+                        cx_catch_up<TRACK>(c, W, s_jobs, &s_njobs, again, c.cx_need);
                         if (again) c.cx_need = -1;
                     }
                 }
@@ -2066,7 +2081,7 @@ __global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes) k_interp
                         log_close(c, W, end_t);
                         c.log = lg;
                     }
-                    cx_scan(c, s_jobs, &s_njobs, close, kRows, 0);
+                    cx_scan<TRACK>(c, s_jobs, &s_njobs, close, kRows, 0);
                     if (close) c.log = nullptr;
                 }
             }
@@ -2300,7 +2315,7 @@ static int scan_waves(uint32_t tiles) {
     return tiles <= 256 ? 8 : (tiles <= 512 ? 4 : (tiles <= 1024 ? 2 : 1));
 }
 
-template <bool TRACK, bool NOOPS>
+template <int TRACK, bool NOOPS>
 static void launch_interp_t(const InterpArgs& a, uint32_t grid, uint32_t tile_envs, uint32_t rom_lds, hipStream_t s) {
     const dim3 block(TRACK ? kLanes * scan_waves(grid) : kLanes);
     if (rom_lds == 0) {
@@ -2315,14 +2330,21 @@ static void launch_interp_t(const InterpArgs& a, uint32_t grid, uint32_t tile_en
     }
 }
 
+template <int TRACK>
+static void launch_interp_n(const InterpArgs& a, uint32_t grid, uint32_t tile_envs, uint32_t rom_lds, hipStream_t s) {
+    if (a.count_step) launch_interp_t<TRACK, false>(a, grid, tile_envs, rom_lds, s);
+    else launch_interp_t<TRACK, true>(a, grid, tile_envs, rom_lds, s);
+}
+
+// With 8 waves the helpers alone scan: the emulating wave is one of eight, and
+// without the scan's call it spills nothing.  With fewer, its share is worth
+// more.  Steps of 4,096 / 16,384 / 24,576 / 49,152 envs with objects (8, 8, 4, 2
+// waves), ms, helpers alone against every wave: 2.07 / 2.09, 3.71 / 3.76, 5.19 /
+// 5.10, 9.93 / 9.32.
 void launch_interp(const InterpArgs& a, uint32_t grid, uint32_t tile_envs, uint32_t rom_lds, hipStream_t s) {
-    if (a.track) {
-        if (a.count_step) launch_interp_t<true, false>(a, grid, tile_envs, rom_lds, s);
-        else launch_interp_t<true, true>(a, grid, tile_envs, rom_lds, s);
-    } else {
-        if (a.count_step) launch_interp_t<false, false>(a, grid, tile_envs, rom_lds, s);
-        else launch_interp_t<false, true>(a, grid, tile_envs, rom_lds, s);
-    }
+    if (!a.track) launch_interp_n<TRACK_NONE>(a, grid, tile_envs, rom_lds, s);
+    else if (scan_waves(grid) == kScanWaves) launch_interp_n<TRACK_HELPERS>(a, grid, tile_envs, rom_lds, s);
+    else launch_interp_n<TRACK_ALL>(a, grid, tile_envs, rom_lds, s);
 }
 
 }  // namespace vcs
