@@ -211,8 +211,9 @@ def interp_latency(kern, passes, rounds, env_rom, tile=64):
     """The interpreter's own bound, the latency of each wave's instruction
     stream: cycles per wave instruction pass if every wave lived the whole
     launch (an upper bound: waves that end early leave their SIMDs idle),
-    next to the cost of a pass for a wave on the plain step (SQ counters:
-    158 cycles) and the scheduling rounds."""
+    next to the cost of a pass for a wave on the plain step (SQ_WAVE_CYCLES
+    over the step's passes, profiles/plain_batch_4096_sq_counters.md: 158
+    cycles) and the scheduling rounds."""
     t = kern["k_interp"]["mean_ms"] * 1e-3
     counts = np.bincount(np.asarray(env_rom, dtype=np.int64))
     waves = int(sum((int(c) + tile - 1) // tile for c in counts if c))

@@ -248,7 +248,10 @@ int vcs_last_step_instructions(vcs_ctx* ctx, uint64_t* out);
 
 /* out2[0]: instructions emulated by the last vcs_step; out2[1]: how many of
    them ran in wave-uniform mode (every lane of a wave at the same PC, bank
-   and cycle, so fetch, decode and timing ran once for the wave).
+   and cycle, so fetch, decode and timing ran once for the wave).  Nearly all
+   do; none at all means that the library's code was loaded across a 4 GB
+   boundary, where the interpreter's hot loop cannot run and steps take many
+   times as long (same results): load the library again.
    Synchronises. */
 int vcs_last_step_stats(vcs_ctx* ctx, uint64_t* out2);
 

@@ -9,7 +9,8 @@
 // What bounds it: the latency of one wave's instruction stream (at most one
 // wave per SIMD runs, and each pass depends on the one before).  On gfx950 an
 // instruction issues every 4 cycles, a taken branch to another cache line
-// costs 40-80 (instruction fetch), a scalar load that hits 40, an LDS read 60.
+// costs 50-100 (instruction fetch), a scalar load that hits 40, an LDS read 60,
+// a comparison's way to the scalar unit 24-32, v_readlane 28.
 // A compiled loop takes several far branches per pass (compare chain, skipped
 // cases, back edge: 471 cycles a pass on the step of 4,096 envs of one 4 KB
 // cartridge, k_interp 2.62 ms); here a handler ends by jumping straight to the
@@ -34,8 +35,15 @@
 //    and the frame row of the current line is 286 - L.
 //
 // It stops before an instruction it does not cover (any word whose slot is
-// HOT_REAL), an ADC or SBC in decimal mode, a store whose effect falls on the
-// next line or finds its log row full, and at the frame's cycle cap.
+// HOT_REAL), one whose lanes a handler cannot take together (an index out of RAM
+// or plain ROM, a page crossed by some, a return to different places, a slice
+// that differs, the stack outside RAM), a store whose effect falls on the next
+// line or finds its log row full, and at the frame's cycle cap.  The way out and
+// back costs some 2,000 cycles.
+//
+// Where it was loaded across a 4 GB boundary its 32-bit jumps would miss: it then
+// does nothing, and every instruction runs per lane (the step's count of
+// instructions on the wave-uniform path is 0).
 //
 // Every wait that a load needs is inside the block, in the handler that uses
 // the value or before the block's end.
@@ -53,9 +61,15 @@ namespace vcs {
 // bank hotspot (the new bank in the word's low bits); HOT_HMP + 2 r + i is a
 // store of A, X, Y (r) to HMP0 / HMP1 (i), HOT_VSYNC one of A to VSYNC (left to
 // the full dispatch when a lane sets bit 1), HOT_INPT4 and HOT_SWCHA_* read the
-// joystick; HOT_WSYNC
-// and HOT_ST_NOP (nothing emulated changes) stand for a store of A, X or Y; the
-// *_X branches cross a page when taken.  Long handlers have several slots.
+// joystick; HOT_WSYNC and HOT_ST_NOP (nothing emulated changes) stand for a store
+// of A, X or Y; the *_X branches (HOT_BPL_X + condition) cross a page when taken.
+// HOT_RESP / HOT_RESM are a store of any register to RESPx / RESMx, RESBL (the
+// class: the register's code | which store << 5); HOT_FLAG_X / _Y + i the flags
+// above from X or Y; HOT_3F + r a store that selects a 3F slice; HOT_E0 LDA from
+// an E0 hotspot; HOT_HS_ST a store to a linear scheme's (the class: the bank |
+// which store << 5); HOT_A_TIA + 3 r + i an absolute store of register r to a TIA
+// register kept as is (i = 0), GRP0 or GRP1; the others are named for operation
+// and mode.  Long handlers have several slots (the opcode of the later ones: 0).
 constexpr uint32_t HOT_REAL = 0, HOT_STA_TIA = 1,
                    HOT_STA_GRP0 = 27, HOT_STA_GRP1 = 30, HOT_STX_TIA = 33, HOT_STX_GRP0 = 34, HOT_STX_GRP1 = 35,
                    HOT_STY_TIA = 36, HOT_STY_GRP0 = 37, HOT_STY_GRP1 = 38, HOT_FLAG = 41, HOT_XR_LDA = 53,

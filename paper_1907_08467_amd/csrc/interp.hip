@@ -27,10 +27,11 @@
 // group, which the hot loop (hotloop.h) runs as threaded code with its control
 // state in scalars, one group after the other in order of emulated time; groups
 // part at data-dependent branches and meet again there.  An instruction the hot
-// loop does not cover goes once through the full scalar dispatch (run_cold).
-// What that refuses -- undocumented opcodes, latch reads, lanes that disagree
-// about a bank or the decimal mode, code outside the cartridge window -- goes
-// through the per-lane path: the wave executes one opcode at a time for all
+// loop does not cover goes through the full scalar dispatch (run_cold), which
+// goes on to the next one that the loop covers.  What that refuses --
+// undocumented opcodes, indirect jumps and stores, latch reads, timer writes,
+// HMOVE, lanes that disagree about a bank, code outside the cartridge window --
+// goes through the per-lane path: the wave executes one opcode at a time for all
 // lanes that share it (readfirstlane + compare), so the opcode's decode word is
 // a scalar and the addressing-mode and operation switches of the one generic
 // executor are scalar branches; TIA writes are queued during the pass and
@@ -1054,21 +1055,18 @@ __device__ __forceinline__ void apply_queue(Cpu& c, const Wave& W, uint32_t t) {
 }
 
 __device__ __forceinline__ uint32_t rfl(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
-__device__ __forceinline__ uint32_t rdl(uint32_t v, int lane) { return (uint32_t)__builtin_amdgcn_readlane((int)v, lane); }
-__device__ __forceinline__ int32_t rdl(int32_t v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
 __device__ __forceinline__ int32_t rfl(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // ------------------------------------------------------- wave-uniform path
 //
-// When every running lane of the wave is at the same PC, bank, cycle, frame
-// line and row-log position, those stay in scalar registers: one scalar load
-// of the predecoded ROM gives opcode, operands and decode word, addressing
-// and timing run on the scalar unit, and only the data (A, X, Y, P, SP, RAM,
-// TIA registers, log stores) is per lane.  Branches whose outcome differs,
-// page-crossing penalties or stack targets that differ, and frames that end
-// in some lanes only hand the wave back to the per-lane path; so do the
-// instructions this path does not cover (indirect modes, JMP (ind), RTI, BRK,
-// indexed accesses outside RAM/cartridge), which the per-lane path executes.
+// The full dispatch of a group of lanes at one place (run_cold): bank, pc, cycle,
+// frame line and open row are scalars (Fast), the predecoded word gives opcode
+// and operands, addressing and timing run on the scalar unit, and only the data
+// (A, X, Y, P, SP, RAM, TIA registers, log position and stores) is per lane.
+// Branches whose outcome differs end the run with the lanes parted; penalties or
+// stack targets that differ leave the instruction to the per-lane path, as do
+// those not covered here (indirect modes, JMP (ind), RTI, BRK, indexed accesses
+// outside RAM and cartridge).
 struct Fast {
     uint32_t pc, bank, cyc, orow;
     int32_t fl;
@@ -1077,10 +1075,9 @@ struct Fast {
 
 __device__ __forceinline__ bool all_lanes(bool p) { return __builtin_amdgcn_ballot_w64(!p) == 0; }
 
-// Stores the scalar path leaves to the per-lane path: VSYNC (it may end the
-// frame), the motion registers, HMOVE, HMCLR, RESMP, CXCLR and timer writes.
-// Keeping them out leaves the per-lane VSYNC, motion, collision and timer
-// state untouched inside the scalar loop.
+// Stores that the full dispatch leaves to the per-lane path: VSYNC (it may end
+// the frame), the motion registers, HMOVE, HMCLR, RESMP, CXCLR and timer writes.
+// (The hot loop takes HMP0, HMP1 and a VSYNC that ends no frame itself.)
 __device__ __forceinline__ bool tia_exit_reg(uint32_t reg) {
     return reg == 0x00 || (reg >= 0x20 && reg <= 0x24) || reg == 0x28 || reg == 0x29 || reg == 0x2A || reg == 0x2B ||
            reg == 0x2C;
@@ -1092,14 +1089,14 @@ __device__ __forceinline__ uint32_t fast_store_ok(uint32_t a) {
     return (a & 0x14) != 0x14 ? 1u : 0u;                  // RIOT: everything but the timer
 }
 
-// Store classes of a static address, kept in the predecoded ROM word of a
-// store instruction (its byte 3) so the scalar path needs no address decode.
+// Store classes of a static address (cart_store_class): the full dispatch's
+// cases, and what k_predecode picks a store's hot-loop slot by.
 constexpr uint32_t SC_RAM = 0, SC_WSYNC = 1, SC_IGNORE = 2, SC_EXIT = 3, SC_CART = 4, SC_TIA = 0x20;
 // SC_TIA | code: a register stored as is; SC_TIAS | code: a position from
 // the cycle or a flags byte; SC_TIAG | code: GRP0 / GRP1 (the delayed copies)
 constexpr uint32_t SC_TIAS = 0x40, SC_TIAG = 0x60;
-// predecoded classes that depend on the cartridge: an absolute access to the
-// Superchip RAM window, and a 3F slice-select store to an ignored TIA register
+// classes that depend on the cartridge: an absolute access to the Superchip RAM
+// window, and a 3F slice-select store to an ignored TIA register
 constexpr uint32_t SC_XRAM = 5, SC_3F = 6;
 // TIA store codes past the snapshot registers: ENAM0, ENAM1, ENABL, VDELP0,
 // VDELP1, VDELBL (SC_TIAS | kScFlag0 + i), written as their full byte and a
@@ -2164,13 +2161,13 @@ __global__ void __launch_bounds__(TRACK ? kLanes * kScanWaves : kLanes, TRACK ? 
 // Predecoded ROM: for every virtual bank and offset, the word (pre_op) of the
 // instruction that starts there, each byte read through the bank's mapping, so
 // instructions that cross an E0 or 3F segment boundary decode exactly.  An
-// instruction gets a hot-loop slot when the loop runs it and leaves the pc
-// inside $000-$FFC of the bank: it does not end past $FFC, and a
-// branch's or jump's target is inside; zero-page accesses are to RAM (a read
-// below $80 is a TIA read, perhaps a tracked latch), or stores to TIA
-// registers kept as they are, GRP0 / GRP1, WSYNC or nothing emulated (object
-// resets, enables and what the per-lane path takes are not).  Entries past
-// offset $FFD are never used.
+// instruction gets a hot-loop slot when the loop has a handler for what it does
+// at that address (HOT_REAL otherwise) and leaves the pc inside $000-$FFC of the
+// bank: it does not end past $FFC, and a branch's, jump's or call's target is
+// inside.  What the address does not settle -- an index that leads elsewhere, a
+// stack outside RAM -- the handler finds out and leaves.  track: collision
+// latches are tracked, so a read of one needs the scan.  Entries past offset
+// $FFD are never used.
 __global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre, uint32_t track) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= R.n_vbanks * 4096u) return;
