@@ -59,7 +59,8 @@ namespace vcs {
 // each); HOT_XR_* and HOT_XW access Superchip RAM through its read and write
 // port; HOT_ABS is LDA from a linearly mapped cartridge, HOT_HS the same from a
 // bank hotspot (the new bank in the word's low bits); HOT_HMP + 2 r + i is a
-// store of A, X, Y (r) to HMP0 / HMP1 (i), HOT_VSYNC one of A to VSYNC (left to
+// store of A, X, Y (r) to HMP0 / HMP1 (i), HOT_HMM + i one of A to HMM0, HMM1,
+// HMBL, HOT_HMCLR one of any register to HMCLR (the class: which << 5), HOT_VSYNC one of A to VSYNC (left to
 // the full dispatch when a lane sets bit 1), HOT_INPT4 and HOT_SWCHA_* read the
 // joystick; HOT_WSYNC and HOT_ST_NOP (nothing emulated changes) stand for a store
 // of A, X or Y; the *_X branches (HOT_BPL_X + condition) cross a page when taken.
@@ -83,11 +84,12 @@ constexpr uint32_t HOT_REAL = 0, HOT_STA_TIA = 1,
                    HOT_ZY = 179, HOT_ZX_RMW = 180, HOT_AX_ROM = 181, HOT_AY_ROM = 183, HOT_AX_RAM = 185,
                    HOT_AY_RAM = 186, HOT_IY_ROM = 187, HOT_A_RMW = 189, HOT_SEG = 190, HOT_SEG_X = 191, HOT_SEG_Y = 192,
                    HOT_STA_ZX = 193, HOT_STY_ZX = 194, HOT_STX_ZY = 195, HOT_STA_AX = 196, HOT_STA_AY = 197,
-                   HOT_STA_A = 198, HOT_STX_A = 199, HOT_STY_A = 200, HOT_A_TIA = 201, HOT_PHP = 210, HOT_PLP = 212;
+                   HOT_STA_A = 198, HOT_STX_A = 199, HOT_STY_A = 200, HOT_A_TIA = 201, HOT_PHP = 210, HOT_PLP = 212,
+                   HOT_HMM = 214, HOT_HMCLR = 217;
 // The two-step reads: HOT_Z_CONST .. HOT_SEG_Y fetch the operand (the word's
 // class: the operation's number, and for the constants which one << 5) and go
 // on to the operation, slot kHotWork + its number.
-constexpr uint32_t kHotWork = 214, kHotWorks = 18;
+constexpr uint32_t kHotWork = 218, kHotWorks = 18;
 enum : uint32_t { HW_LDA, HW_LDX, HW_LDY, HW_AND, HW_ORA, HW_EOR, HW_CMP, HW_CPX, HW_CPY, HW_BIT, HW_ADC, HW_SBC,
                   HW_ASL, HW_ROL, HW_LSR, HW_ROR, HW_DEC, HW_INC, HW_NONE };
 constexpr uint32_t kHotSlots = kHotWork + kHotWorks;
@@ -105,8 +107,8 @@ constexpr uint8_t kHotSlotOp[kHotSlots] = {
     0x84, 0x84, 0x84, 0x85, 0x86, 0x84, 0xAD, 0x00, 0x8D, 0xA5, 0xA5, 0xAD, 0xAD, 0xAD, 0x00, 0xAD,
     0x00, 0xAD, 0xB5, 0xB6, 0x16, 0xBD, 0x00, 0xB9, 0x00, 0xBD, 0xB9, 0xB1, 0x00, 0x0E, 0xAD, 0xBD,
     0xB9, 0x95, 0x94, 0x96, 0x9D, 0x99, 0x8D, 0x8E, 0x8C, 0x8D, 0x8D, 0x8D, 0x8E, 0x8E, 0x8E, 0x8C,
-    0x8C, 0x8C, 0x08, 0x00, 0x28, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00,
-    0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00,
+    0x8C, 0x8C, 0x08, 0x00, 0x28, 0x00, 0x85, 0x85, 0x85, 0x85, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00,
+    0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00, 0x00,
 };
 // The slot that runs opcode `op` without a page-crossing branch or a TIA store
 // (HOT_REAL: none).
@@ -287,6 +289,15 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     "s_load_dwordx4 s[76:79], s[70:71], s72\n" HL_ABSBYTE HL_TGT("s76") HL_GO(4)
 // motion registers and VSYNC: no log entry, kept per lane
 #define HL_HMP(B, slot, reg, hmp) HL_ORG(B, slot) HL_WAIT HL_TGT("s78") HL_FETCH(2) "v_mov_b32 " hmp ", " reg "\n" HL_GO(3)
+#define HL_HMM(B, slot, reg) HL_ORG(B, slot) HL_WAIT "ds_write_b8 %[tia], %[a] offset:" #reg "\n" HL_TGT("s78") HL_FETCH(2) HL_GO(3)
+#define HL_HMCLR(B, slot)                                  \
+    HL_ORG(B, slot) HL_WAIT                                \
+    "v_mov_b32 v122, 0\n"                                  \
+    "v_mov_b32 %[hmp0], 0\n"                               \
+    "v_mov_b32 %[hmp1], 0\n"                               \
+    "ds_write_b8 %[tia], v122 offset:41\n"                 \
+    "ds_write_b8 %[tia], v122 offset:42\n"                 \
+    "ds_write_b8 %[tia], v122 offset:43\n" HL_TGT("s78") HL_FETCH(2) HL_GO(3)
 #define HL_VSYNC(B, slot)                                  \
     HL_ORG(B, slot) HL_WAIT                                \
     "v_and_b32 v122, 2, %[a]\n"                            \
@@ -626,7 +637,7 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     "s_and_b32 s90, s76, 31\n"                             \
     "s_lshl_b32 s90, s90, 7\n"                             \
     "s_add_u32 s90, s90, s84\n"                            \
-    "s_add_u32 s90, s90, 128*214\n"
+    "s_add_u32 s90, s90, 128*218\n"
 #define HL_DO "s_setpc_b64 s[90:91]\n"
 #define HL_WORK(B, slot, work) HL_ORG(B, slot) work HL_JUMP
 // constants: 0, $80, $0B (SWCHB)
@@ -906,24 +917,28 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     ATIA(B)                                                                                          /* absolute stores to TIA registers */ \
     HL_PHP(B, 210)                                                                                   /* $08 */ \
     HL_PLP(B, 212)                                                                                   /* $28 */ \
-    HL_WORK(B, 214, HL_LDV)                                                                          /* LDA */ \
-    HL_WORK(B, 215, "v_mov_b32 %[x], v123\n" HL_NZ("v123"))                                          /* LDX */ \
-    HL_WORK(B, 216, "v_mov_b32 %[y], v123\n" HL_NZ("v123"))                                          /* LDY */ \
-    HL_WORK(B, 217, HL_AND("v123"))                                                                  /* AND */ \
-    HL_WORK(B, 218, HL_ORA("v123"))                                                                  /* ORA */ \
-    HL_WORK(B, 219, HL_EOR("v123"))                                                                  /* EOR */ \
-    HL_WORK(B, 220, HL_CMP("%[a]", "v123"))                                                          /* CMP */ \
-    HL_WORK(B, 221, HL_CMP("%[x]", "v123"))                                                          /* CPX */ \
-    HL_WORK(B, 222, HL_CMP("%[y]", "v123"))                                                          /* CPY */ \
-    HL_WORK(B, 223, HL_BIT)                                                                          /* BIT */ \
-    HL_WORK(B, 224, HL_ADCV)                                                                         /* ADC */ \
-    HL_WORK(B, 225, HL_SBCV)                                                                         /* SBC */ \
-    HL_WORK(B, 226, HL_ASL("v123") "ds_write_b8 v122, v123\n")                                       /* ASL */ \
-    HL_WORK(B, 227, HL_ROL("v123") "ds_write_b8 v122, v123\n")                                       /* ROL */ \
-    HL_WORK(B, 228, HL_LSR("v123") "ds_write_b8 v122, v123\n")                                       /* LSR */ \
-    HL_WORK(B, 229, HL_ROR("v123") "ds_write_b8 v122, v123\n")                                       /* ROR */ \
-    HL_WORK(B, 230, HL_DEC("v123") "ds_write_b8 v122, v123\n")                                       /* DEC */ \
-    HL_WORK(B, 231, HL_INC("v123") "ds_write_b8 v122, v123\n")                                       /* INC */
+    HL_HMM(B, 214, 41)                                                                               /* STA HMM0 */ \
+    HL_HMM(B, 215, 42)                                                                               /* STA HMM1 */ \
+    HL_HMM(B, 216, 43)                                                                               /* STA HMBL */ \
+    HL_HMCLR(B, 217)                                                                                 /* HMCLR */ \
+    HL_WORK(B, 218, HL_LDV)                                                                          /* LDA */ \
+    HL_WORK(B, 219, "v_mov_b32 %[x], v123\n" HL_NZ("v123"))                                          /* LDX */ \
+    HL_WORK(B, 220, "v_mov_b32 %[y], v123\n" HL_NZ("v123"))                                          /* LDY */ \
+    HL_WORK(B, 221, HL_AND("v123"))                                                                  /* AND */ \
+    HL_WORK(B, 222, HL_ORA("v123"))                                                                  /* ORA */ \
+    HL_WORK(B, 223, HL_EOR("v123"))                                                                  /* EOR */ \
+    HL_WORK(B, 224, HL_CMP("%[a]", "v123"))                                                          /* CMP */ \
+    HL_WORK(B, 225, HL_CMP("%[x]", "v123"))                                                          /* CPX */ \
+    HL_WORK(B, 226, HL_CMP("%[y]", "v123"))                                                          /* CPY */ \
+    HL_WORK(B, 227, HL_BIT)                                                                          /* BIT */ \
+    HL_WORK(B, 228, HL_ADCV)                                                                         /* ADC */ \
+    HL_WORK(B, 229, HL_SBCV)                                                                         /* SBC */ \
+    HL_WORK(B, 230, HL_ASL("v123") "ds_write_b8 v122, v123\n")                                       /* ASL */ \
+    HL_WORK(B, 231, HL_ROL("v123") "ds_write_b8 v122, v123\n")                                       /* ROL */ \
+    HL_WORK(B, 232, HL_LSR("v123") "ds_write_b8 v122, v123\n")                                       /* LSR */ \
+    HL_WORK(B, 233, HL_ROR("v123") "ds_write_b8 v122, v123\n")                                       /* ROR */ \
+    HL_WORK(B, 234, HL_DEC("v123") "ds_write_b8 v122, v123\n")                                       /* DEC */ \
+    HL_WORK(B, 235, HL_INC("v123") "ds_write_b8 v122, v123\n")                                       /* INC */
 
 // Fold the current group's instruction count into its lanes' counts and the
 // wave's passes (exec: the group).
@@ -1023,7 +1038,7 @@ __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uin
     static_assert(R_GRP0 == 10 && R_GRP1 == 11 && R_GRP0_OLD == 16 && R_GRP1_OLD == 17 && R_FLAGS == 23 &&
                       R_ENAM0 == 32 && R_ENABL == 34 && R_ENABL_OLD == 35 && R_VDELBL == 38,
                   "the block's register offsets");
-    static_assert(kHotWork == 214 && HW_INC == kHotWorks - 1 && (HW_NONE | 3 << 5) < 128 && kHotSlots * 128 < 0x8000,
+    static_assert(kHotWork == 218 && R_HMM0 == 41 && HW_INC == kHotWorks - 1 && (HW_NONE | 3 << 5) < 128 && kHotSlots * 128 < 0x8000,
                   "the block's slots");
     asm volatile(
         // --- entry: block bases, line-change and row addresses, constants

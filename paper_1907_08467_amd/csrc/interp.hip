@@ -1077,7 +1077,8 @@ __device__ __forceinline__ bool all_lanes(bool p) { return __builtin_amdgcn_ball
 
 // Stores that the full dispatch leaves to the per-lane path: VSYNC (it may end
 // the frame), the motion registers, HMOVE, HMCLR, RESMP, CXCLR and timer writes.
-// (The hot loop takes HMP0, HMP1 and a VSYNC that ends no frame itself.)
+// (The hot loop takes the motion registers, HMCLR and a VSYNC that ends no frame
+// itself.)
 __device__ __forceinline__ bool tia_exit_reg(uint32_t reg) {
     return reg == 0x00 || (reg >= 0x20 && reg <= 0x24) || reg == 0x28 || reg == 0x29 || reg == 0x2A || reg == 0x2B ||
            reg == 0x2C;
@@ -1204,7 +1205,7 @@ __device__ __forceinline__ uint32_t pre_op(uint32_t q) {
     const uint32_t slot = pre_slot(q);
     if (slot == HOT_REAL) return (q & 0x7F) | ((q >> 8) & 0x80);
     if (slot - kTwoStepFirst < kTwoStepEnd - kTwoStepFirst) return kHotOps.two[32 * (slot - kTwoStepFirst) + (q & 31)];
-    if (slot == HOT_RESP || slot == HOT_RESM) return kHotOps.st_zp[(q >> 5) & 3];
+    if (slot == HOT_RESP || slot == HOT_RESM || slot == HOT_HMCLR) return kHotOps.st_zp[(q >> 5) & 3];
     if (slot == HOT_HS_ST) return kHotOps.st_abs[(q >> 5) & 3];
     return kHotOps.op[slot];
 }
@@ -2198,9 +2199,16 @@ __global__ void k_predecode(const uint8_t* rom, RomInfo R, uint32_t* pre, uint32
                 slot = HOT_3F + (op == 0x85 ? 0 : op == 0x86 ? 1 : 2);
                 cls = R.tf_mask;
             }
-            else if (cls == SC_EXIT && ((b1 & 0x3E) == 0x20 || ((b1 & 0x3F) == 0 && op == 0x85)) &&
-                     !(R.kind == CART_3F && b1 <= 0x3F))   // HMP0, HMP1, VSYNC
-                slot = (b1 & 0x3F) == 0 ? HOT_VSYNC : HOT_HMP + (op == 0x85 ? 0 : op == 0x86 ? 2 : 4) + (b1 & 1);
+            else if (cls == SC_EXIT && !(R.kind == CART_3F && b1 <= 0x3F)) {   // VSYNC, motion registers
+                const uint32_t reg = b1 & 0x3F, r = op == 0x85 ? 0u : op == 0x86 ? 1u : 2u;
+                if (reg == 0 && r == 0) slot = HOT_VSYNC;
+                else if (reg == 0x20 || reg == 0x21) slot = HOT_HMP + 2 * r + (reg & 1);
+                else if (reg >= 0x22 && reg <= 0x24 && r == 0) slot = HOT_HMM + reg - 0x22;
+                else if (reg == 0x2B) {
+                    slot = HOT_HMCLR;
+                    cls = r << 5;
+                }
+            }
             else if (cls == (SC_TIAG | R_GRP0)) slot = k ? k + 1 : HOT_STA_GRP0;
             else if (cls == (SC_TIAG | R_GRP1)) slot = k ? k + 2 : HOT_STA_GRP1;
         } else if ((op & 0x1F) == 0x10) {              // conditional branch

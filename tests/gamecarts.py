@@ -121,6 +121,8 @@ SRC = {
                  "    ldy $9A,x\n    sty COLUBK\n    ldx $90\n"),
     "resets": plain("    lda $80\n    sta RESP0\n    sta COLUBK\n    sta RESM0\n    sta RESBL\n    sta $8B\n"
                     "    sta RESP1\n"),
+    "motion": plain("    lda $80\n    sta HMP0\n    sta HMM0\n    stx HMP1\n    sta HMBL\n    sty COLUBK\n    sta HMM1\n    cpx #90\n"
+                    "    bcs mo\n    stx HMCLR\n    sta HMM1\nmo:\n"),
     "decimal": plain("    sed\n    clc\n    lda $8C\n    adc #$19\n    sta $8C\n    lda $8D\n    adc $8C\n    sta $8D\n"
                      "    sec\n    sbc #$07\n    sta COLUBK\n    cld\n"),
     "ports": plain("    lda SWCHB\n    and #$08\n    sta $8E\n    bit INPT4\n    bpl po\n    inc $8F\npo:\n"
@@ -141,7 +143,7 @@ SRC = {
                     "    lda ($F0),y\n    sta PF2\n    lda tab+64,x\n    sta COLUPF\n",
                     vblank="    jsr sub\n    jsr sub2\n    lda SWCHA\n    and #$10\n    bne v1\n    inc $91\nv1:\n    lda $91\n"
                            "    and #7\n    tax\n    lda tab,x\n    sta $92\n    sed\n    clc\n    lda $93\n    adc #1\n    sta $93\n"
-                           "    cld\n    lda #$20\n    sta HMP0\n    sta WSYNC\n    sta HMOVE\n    sta WSYNC\n    sta RESP0\n"
+                           "    cld\n    lda #$20\n    sta HMP0\n    sta HMM0\n    sta HMBL\n    sta WSYNC\n    sta HMOVE\n    sta WSYNC\n    sty HMCLR\n    sta HMM1\n    sta RESP0\n"
                            "    lda $94,x\n    sta $96,x\n    ldy #9\n",
                     overscan="    lda INPT4\n    bmi o1\n    jsr sub\no1:\n    lda CXP0FB\n    sta $98\n    sta CXCLR\n    dec $99\n"),
 }

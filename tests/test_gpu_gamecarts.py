@@ -32,7 +32,8 @@ def test_against_the_oracle(name, n, mode, collisions, big):
     o.close()
 
 
-@pytest.mark.parametrize("name", ["timer", "tables", "pointers", "calls", "resets", "decimal", "rare"])
+@pytest.mark.parametrize("name", ["timer", "tables", "pointers", "calls", "resets", "motion", "decimal", "rare", "stack",
+                                  "absolute"])
 def test_the_hot_loop_is_not_left(name):
     """Envs of these run in lockstep: what is left to the other paths is a few
     instructions of each frame, whatever its lines are made of."""
