@@ -153,9 +153,11 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
 #define HL_IMM(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_IMM_(work)
 #define HL_IMMD(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_B1_8 HL_TGT("s78") HL_FETCH(2) HL_ACC(2) work HL_JUMP
 // zero-page read whose result the handler needs: operand in v123
-#define HL_ZPR_(work)                                                                              \
-    HL_B1_7 HL_RAMADDR "ds_read_u8 v123, v122\n" HL_TGT("s78") HL_FETCH(2) HL_ACC(3) HL_WAIT work HL_JUMP
-#define HL_ZPR(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_ZPR_(work)
+#define HL_ZPR_(test, work)                                                                              \
+    HL_B1_7 HL_RAMADDR "ds_read_u8 v123, v122\n" HL_TGT("s78") HL_FETCH(2) HL_ACC(3) test HL_WAIT work HL_JUMP
+#define HL_ZPR(B, slot, work) HL_ORG(B, slot) HL_WAIT HL_ZPR_("", work)
+// ADC, SBC: whether a lane is in decimal mode is found out while the operand comes
+#define HL_ZPRD(B, slot, to, work) HL_ORG(B, slot) HL_WAIT HL_ZPR_(HL_BIN(to), work)
 // zero-page load: lands in the register and nz before the next handler's wait ends
 #define HL_ZPL(B, slot, reg)                                                                       \
     HL_ORG(B, slot) HL_WAIT HL_B1_7 HL_RAMADDR "ds_read_u8 " reg ", v122\n"                        \
@@ -833,7 +835,7 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     HL_IMP(B, 97, HL_LSR("%[a]"))                                                                    /* $4A */ \
     HL_JMP(B, 98)                                                                                    /* $4C */ \
     HL_BR(B, 99, HL_T_EQ("0x80", "%[v]"), "8")                                                       /* $50 */ \
-    HL_ZPR(B, 100, HL_ADCV)                                                                          /* $65 */ \
+    HL_ZPRD(B, 100, ".Ldadc", HL_ADC("v123"))                                                        /* $65 */ \
     HL_ZPM(B, 101, HL_ROR("v123"))                                                                   /* $66 */ \
     HL_IMMD(B, 102, HL_ADCI)                                                                         /* $69 */ \
     HL_IMP(B, 103, HL_ROR("%[a]"))                                                                   /* $6A */ \
@@ -866,7 +868,7 @@ constexpr uint32_t kAccBias = 52, kAccShift = 25, kAccCount = (1u << kAccShift) 
     HL_IMP(B, 130, "s_andn2_b64 s[50:51], s[50:51], exec\n")                                         /* $D8 */ \
     HL_IMM(B, 131, HL_CMP_S("%[x]"))                                                                 /* $E0 */ \
     HL_ZPR(B, 132, HL_CMP("%[x]", "v123"))                                                           /* $E4 */ \
-    HL_ZPR(B, 133, HL_SBCV)                                                                          /* $E5 */ \
+    HL_ZPRD(B, 133, ".Ldsbc", "v_xor_b32 v123, 0xff, v123\n" HL_ADC("v123"))                         /* $E5 */ \
     HL_ZPM(B, 134, HL_INC("v123"))                                                                   /* $E6 */ \
     HL_IMP(B, 135, HL_INC("%[x]"))                                                                   /* $E8 */ \
     HL_IMMD(B, 136, HL_SBCI)                                                                         /* $E9 */ \
@@ -1338,7 +1340,7 @@ __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uin
         // v124: the binary sum, v116 its low byte, v120 its overflow
         ".Ldadci%=:\n"
         "v_mov_b32 v123, s86\n"
-        ".Ldadc%=:\n"
+        ".Ldadc%=:\n" HL_WAIT
         "v_add3_u32 v124, %[a], v123, %[c]\n"
         "v_bitop3_b32 v120, %[a], v123, v124 bitop3:0x42\n"
         "v_and_b32 v116, 0xff, v124\n"
@@ -1376,7 +1378,7 @@ __device__ __forceinline__ uint64_t hot_wave(uint64_t lanes, uint64_t table, uin
         // --- SBC of such groups (do_sbc): all flags by the binary difference
         ".Ldsbci%=:\n"
         "v_mov_b32 v123, s86\n"
-        ".Ldsbc%=:\n"
+        ".Ldsbc%=:\n" HL_WAIT
         "v_xor_b32 v126, 0xff, v123\n"
         "v_add3_u32 v124, %[a], v126, %[c]\n"
         "v_bitop3_b32 %[v], %[a], v126, v124 bitop3:0x42\n"
