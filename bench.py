@@ -40,14 +40,14 @@ KERNELS = {0: "k_interp", 1: "k_render_frames", 2: "k_render_obs", 3: "k_reset"}
 # step and on the 65,536-env batching workload; reported only while the
 # kernel source and the headers it includes are the ones they were taken on
 # (sha256 prefix of the files concatenated), otherwise null.
-_INTERP_SRC = ("interp.hip", "tia_draw.h", "vcs_device.h")
+_INTERP_SRC = ("interp.hip", "hotloop.h", "tia_draw.h", "vcs_device.h")
 _RENDER_SRC = ("render.hip", "tia_draw.h", "vcs_device.h")
 MEASURED_TRAFFIC = {
-    ("k_interp", "plain_4096"): (_INTERP_SRC, "437de748e86a04c8", (1273.0 * 2.0 + 162348.0) * 1024),
-    ("k_render_frames", "plain_4096"): (_RENDER_SRC, "f7363e502d223ad4", (41151.0 * 2.0 + 268800.0) * 1024),
-    ("k_render_obs", "plain_4096"): (_RENDER_SRC, "f7363e502d223ad4", (41137.2 * 2.0 + 297222.0) * 1024),
-    ("k_interp", "batching_65536"): (_INTERP_SRC, "437de748e86a04c8", (17241.2 * 2.0 + 1648190.0) * 1024),
-    ("k_render_obs", "batching_65536"): (_RENDER_SRC, "f7363e502d223ad4", (606480.0 * 2.0 + 452608.0) * 1024),
+    ("k_interp", "plain_4096"): (_INTERP_SRC, "d435fe4402dc3b50", (1625.1 * 2.0 + 162348.0) * 1024),
+    ("k_render_frames", "plain_4096"): (_RENDER_SRC, "bd195aeb1509f4ae", (41165.0 * 2.0 + 268800.0) * 1024),
+    ("k_render_obs", "plain_4096"): (_RENDER_SRC, "bd195aeb1509f4ae", (41132.4 * 2.0 + 297247.0) * 1024),
+    ("k_interp", "batching_65536"): (_INTERP_SRC, "d435fe4402dc3b50", (18228.8 * 2.0 + 1635950.0) * 1024),
+    ("k_render_obs", "batching_65536"): (_RENDER_SRC, "bd195aeb1509f4ae", (606449.0 * 2.0 + 452608.0) * 1024),
 }
 # MI355X: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz integer VALU lane-ops
 ALU_LANE_OPS_PEAK = 256 * 4 * 16 * 2.4e9
@@ -212,7 +212,7 @@ def interp_latency(kern, passes, rounds, env_rom, tile=64):
     stream: cycles per wave instruction pass if every wave lived the whole
     launch (an upper bound: waves that end early leave their SIMDs idle),
     next to the cost of a pass for a wave on the plain step (SQ_WAVE_CYCLES
-    over the step's passes, profiles/plain_batch_4096_sq_counters.md: 158
+    over the step's passes, profiles/plain_batch_4096_sq_counters.md: 157
     cycles) and the scheduling rounds."""
     t = kern["k_interp"]["mean_ms"] * 1e-3
     counts = np.bincount(np.asarray(env_rom, dtype=np.int64))
@@ -220,7 +220,7 @@ def interp_latency(kern, passes, rounds, env_rom, tile=64):
     cyc = t * CLOCK_HZ * waves / passes if passes else None
     return {"bound": "latency", "waves": waves, "wave_passes": passes, "scheduling_rounds": rounds,
             "passes_per_round": passes / rounds if rounds else None,
-            "cycles_per_pass_if_all_waves_lived_the_launch": cyc, "cycles_per_pass_plain_step_counters": 158}
+            "cycles_per_pass_if_all_waves_lived_the_launch": cyc, "cycles_per_pass_plain_step_counters": 157}
 
 
 def lane_util(instr, passes):

@@ -14,7 +14,7 @@
 // A compiled loop takes several far branches per pass (compare chain, skipped
 // cases, back edge: 471 cycles a pass on the step of 4,096 envs of one 4 KB
 // cartridge, k_interp 2.62 ms); here a handler ends by jumping straight to the
-// next instruction's handler, so a pass has one: 158 cycles, 0.88 ms.
+// next instruction's handler, so a pass has one: 157 cycles, 0.87 ms.
 //
 // How it is laid out:
 //  * a predecoded word (k_predecode) holds its handler's slot: handler address
