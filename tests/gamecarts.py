@@ -5,6 +5,8 @@ INTIM through the vertical blank and the overscan, and draws 180 lines of
 `body` (X: the line), so all envs of one cartridge stay in lockstep unless
 `body` looks at the joystick.
 """
+import random
+
 from helpers import cart
 
 HEAD = """
@@ -151,3 +153,57 @@ SRC = {
 
 def rom(name):
     return cart(SRC[name])[0]
+
+
+# ---- random frames of the same instructions, branching on the joystick
+_TIA = ["COLUBK", "COLUPF", "COLUP0", "GRP0", "GRP1", "PF0", "PF1", "PF2", "ENAM0", "ENAM1", "ENABL", "NUSIZ0", "CTRLPF",
+        "REFP0", "VDELP0", "VDELBL", "HMP0", "HMP1", "HMM0", "HMM1", "HMBL", "RESP0", "RESP1", "RESM0", "RESBL", "HMCLR",
+        "AUDV0"]
+_ALU = ["lda", "and", "ora", "eor", "cmp", "adc", "sbc"]
+_READ = _ALU + ["ldx", "ldy", "cpx", "cpy", "bit"]
+_RMW = ["inc", "dec", "asl", "lsr", "rol", "ror"]
+
+
+def _random_body(r, k):
+    def ram():
+        return f"${r.randint(0x80, 0xBF):02X}"
+
+    def store():
+        return r.choice(["sta", "stx", "sty"])
+
+    out = []
+    for i in range(r.randint(6, 16)):
+        out += r.choice([
+            lambda: [f"{r.choice(_READ)} {ram()}"],
+            lambda: [f"{r.choice(_READ)}.w $00{r.randint(0x80, 0xBF):02X}"],
+            lambda: [f"{r.choice(_READ)} tab+{r.randint(0, 200)}"],
+            lambda: [f"{r.choice(_ALU + ['ldy'])} tab+{r.randint(0, 190)},x"],
+            lambda: [f"{r.choice(_ALU + ['ldx'])} tab+{r.randint(0, 190)},y"],
+            lambda: [f"{r.choice(_ALU)} ($F0),y"],
+            lambda: [f"ldx #{r.randint(0, 40)}", f"{r.choice(_ALU + _RMW + ['ldy', 'sta', 'sty'])} ${r.randint(0x80, 0xA0):02X},x"],
+            lambda: [f"ldy #{r.randint(0, 40)}", f"{r.choice(_ALU + ['sta'])}.w $00{r.randint(0x80, 0xA0):02X},y"],
+            lambda: [f"{store()}{r.choice(['', '', '.w'])} {r.choice(_TIA)}"],
+            lambda: [f"{store()}{r.choice(['', '.w'])} $0090"],
+            lambda: [r.choice(["jsr sub", "jsr sub2"])],
+            lambda: [r.choice(["pha", "php"]), r.choice(["inx", "iny", "clc"]), r.choice(["pla", "plp"])],
+            lambda: [r.choice(["sed", "cld", "sec", "clc", "clv", "tsx", "tya", "txa", "tax", "tay", "asl", "ror"])],
+            lambda: [f"{r.choice(['adc', 'sbc'])} #{r.randint(0, 255)}"],
+            lambda: [f"{r.choice(_ALU + ['bit'])} {r.choice(['SWCHA', 'SWCHB', 'INTIM', 'INPT4', 'TIMINT', '$0D', '$03'])}"],
+            lambda: [f"{r.choice(_RMW)}{r.choice(['', '.w'])} $00{r.randint(0x80, 0xBF):02X}"],
+            lambda: [f"lda {r.choice(['INPT4', 'SWCHA'])}", r.choice(["asl", "lsr", "nop"]),
+                     f"{r.choice(['bpl', 'bmi', 'bcc', 'bcs'])} q{k}_{i}", f"inc {ram()}", r.choice(["nop", "jsr sub"]),
+                     f"sta {r.choice(_TIA)}", f"q{k}_{i}:"],
+            lambda: [r.choice(["sta HMOVE", "sta TIM8T", "sta WSYNC", f"lda ({ram()}),y", "dey", "nop"])],
+        ])()
+    return "".join((l if l.endswith(":") else "    " + l) + "\n" for l in out)
+
+
+def random_rom(seed):
+    """Loops of such bodies, some of them a line each, and lines to the frame's end."""
+    r = random.Random(seed)
+    src = HEAD + ("    lda #<tab\n    sta $F0\n    lda #>tab\n    sta $F1\n    ldx #$E8\n    txs\n    cld\n"
+                  "    lda #44\n    sta TIM64T\n")
+    for k in range(r.randint(2, 4)):
+        src += f"    lda #{r.randint(10, 40)}\n    sta $C{k}\nL{k}:\n" + _random_body(r, k)
+        src += ("    sta WSYNC\n" if r.random() < 0.75 else "") + f"    dec $C{k}\n    beq E{k}\n    jmp L{k}\nE{k}:\n"
+    return cart(src + "    jmp frame\n" + TAIL)[0]

@@ -32,6 +32,22 @@ def test_against_the_oracle(name, n, mode, collisions, big):
     o.close()
 
 
+@pytest.mark.parametrize("seed", range(1, 17))
+def test_random_frames(seed):
+    """The same instructions in random order; envs part on their joysticks and meet again."""
+    n, collisions = (70, 5, 64, 33)[seed % 4], seed % 3 == 0
+    print(f"case: random game cartridge {seed}, {n} envs, collisions {collisions}", flush=True)
+    o, g = make_pair([(gamecarts.random_rom(seed), 0)], np.zeros(n, np.uint16), seed=seed, frameskip=3,
+                     render_mode=seed % 2, collisions=collisions)
+    rng = np.random.default_rng(seed)
+    for s in range(5):
+        step_both(o, g, rng.integers(0, 18, n), want_frames=True, tag=f"{seed} step {s}")
+    compare_all(o, g, n, f"random {seed}")
+    assert g.poll_errors() == o.poll_errors()
+    g.close()
+    o.close()
+
+
 @pytest.mark.parametrize("name", ["timer", "tables", "pointers", "calls", "resets", "motion", "decimal", "rare", "stack",
                                   "absolute"])
 def test_the_hot_loop_is_not_left(name):
